@@ -242,12 +242,16 @@ k_minus_identity(const double2* __restrict__ A, double2* __restrict__ D, int m,
   if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
+// out[0] = sum of part[0 .. nb): lane t of one wave adds t, t + 64, ... in
+// order, then a fixed butterfly (a one-thread loop over 256 partials is a
+// serial chain of loads: 18 us; SUMPARTS_US).
 __global__ void k_sum_parts(const double* __restrict__ part, int nb, double* __restrict__ out, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  if (threadIdx.x) return;
   double s = 0.0;
-  for (int b = 0; b < nb; ++b) s += part[b];
-  out[0] = s;
+  for (int b = threadIdx.x; b < nb; b += 64) s += part[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if (threadIdx.x == 0) out[0] = s;
 }
 
 // P = a D + c 1
@@ -478,13 +482,20 @@ __global__ void k_offnorm(const double2* __restrict__ A, int mp, double* __restr
   }
 }
 
+// Sums of the block partials, one wave, as k_sum_parts.
 __global__ void k_offnorm_final(const double* __restrict__ part, int nb, double* __restrict__ out, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  if (threadIdx.x) return;
   double o = 0.0, d = 0.0;
-  for (int b = 0; b < nb; ++b) { o += part[2 * b]; d += part[2 * b + 1]; }
-  out[0] = o;
-  out[1] = d;
+  for (int b = threadIdx.x; b < nb; b += 64) { o += part[2 * b]; d += part[2 * b + 1]; }
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) {
+    o += __shfl_down(o, k, 64);
+    d += __shfl_down(d, k, 64);
+  }
+  if (threadIdx.x == 0) {
+    out[0] = o;
+    out[1] = d;
+  }
 }
 
 // Pad-copy A (m x m) into Ap (mp x mp) with zero coupling, V = identity.

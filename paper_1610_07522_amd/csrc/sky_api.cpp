@@ -394,8 +394,8 @@ int check_info(sky_ctx* c, const char* what) {
   return SKY_OK;
 }
 
-// Step 3a of species q: I and H (lower triangles by the GEMMs, then
-// mirrored).  Launches only, so that it can be captured in a graph.
+// Step 3a of species q: I and H (lower triangles by the GEMMs, mirrored by
+// their reduction).  Launches only, so that it can be captured in a graph.
 void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
                        bool scales_ready = false) {
   const int q = s & 1;
@@ -429,8 +429,6 @@ void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
   else
     overlap_lower(phi, phi, hphi, m, c->V, c->g.dV, I, H, c->at(c->lay.gemm_part), st,
                   c->timing ? ev : nullptr, c->tune.ovl[q]);
-  hermitian_fill(I, m, st);
-  hermitian_fill(H, m, st);
 }
 
 // Steps 3b-3d of set s on the host-driven path: an orthonormalising
@@ -482,7 +480,6 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
     gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
     gemm_square(T, 0, Linv, 1, Hp, m, st, sq, 1, sqs);
   }
-  hermitian_fill(Hp, m, st);   // exact Hermitian symmetry of H' before the eigensolver
   if (terms <= 0) {   // only the Cholesky path can report a non-positive overlap
     int rc = check_info(c, "cholesky");
     if (rc) return rc;
@@ -529,7 +526,6 @@ void subspace_solve_dev(sky_ctx* c, int s) {
     GateScope g(fl + F_ACTIVE);
     gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
     gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
-    hermitian_fill(Hp, m, st);
   }
   refine_eigh_dev(Hp, m, c->at<double>(c->lay.ritz[s]), Z, c->at(c->lay.ref_work),
                   c->prec ? REFINE_MIXED : REFINE_FP64,
@@ -752,7 +748,6 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   } else
     overlap_lower(phi, phi, nullptr, m, c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st,
                   nullptr, c->tune.ovl[q]);
-  hermitian_fill(I, m, st);
   int its = jacobi_checked(c, I, m, w, X);
   if (its < 0) return its;
   // C = X diag(w^-1/2) X^H

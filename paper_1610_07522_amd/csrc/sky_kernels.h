@@ -146,8 +146,9 @@ int energy_nblocks(int n);
 size_t mean_field_scratch_bytes(int n);
 
 // ---- dense complex matrices (k_gemm.hip); complex128, row-major
-// C[a][b] = scale * sum_v conj(A[a][v]) B[b][v] for b <= a (lower triangle),
-// for two right operands at once (B0 -> C0, B1 -> C1, B1 may be null).
+// C[a][b] = scale * sum_v conj(A[a][v]) B[b][v] for b <= a, the upper triangle
+// mirrored from the lower one (C Hermitian, its diagonal real), for two right
+// operands at once (B0 -> C0, B1 -> C1, B1 may be null).
 // part: split * 2 * ntile_pairs * 64*64 complex scratch.
 size_t overlap_scratch_bytes(int m, long k);
 // ev (may be null): events recorded right before / after the GEMM kernel.
@@ -156,7 +157,8 @@ int overlap_split_candidates(int m, long k, int* out);
 void overlap_lower(const void* A, const void* B0, const void* B1, int m, long k, double scale,
                    void* C0, void* C1, void* part, hipStream_t st, hipEvent_t* ev = nullptr,
                    int split_req = 0);
-// FP64 reduction of split-K partials into the lower tiles of C0 (and C1).
+// FP64 reduction of split-K partials into C0 (and C1), lower triangle and its
+// mirror image.
 void overlap_reduce(const void* part, int npair, int split, int m, double scale, void* C0,
                     void* C1, int nz, hipStream_t st);
 // Mixed precision (k_gemm_mixed.hip): complex64 operands split once into
@@ -185,7 +187,8 @@ void split_planes_t(const void* x, int x_is_c128, int rows, long cols, const uns
 // matrix (rows x k) from one read of it.
 void split_planes_both(const void* x, int rows, long k, const unsigned int* mx, void* P, void* PT,
                        hipStream_t st);
-// C0 = scale * conj(A) B0^T (and C1 with B1), lower 64-tiles, from NT planes.
+// C0 = scale * conj(A) B0^T (and C1 with B1) from NT planes: the lower
+// triangle, mirrored to the upper one.
 // split_req > 0 overrides the split-K factor (one of overlap_split_candidates_mixed).
 int overlap_split_candidates_mixed(int m, long k, int* out);
 void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,

@@ -1,0 +1,46 @@
+"""Subspace matrices at the edges of their tiles, against numpy in FP64."""
+import numpy as np
+import pytest
+
+from gpu_util import to_dev, to_host
+from paper_1610_07522_amd import inputs, sky
+
+pytestmark = pytest.mark.gpu
+
+
+def _box(n, m, precision=sky.SKY_FP64):
+    return sky.Box(sky.desc_from_workload(inputs.small_workload("edge", n, m, 1),
+                                          precision=precision))
+
+
+def _states(rng, m, n, dtype):
+    x = rng.standard_normal((m, 2, n, n, n, 2))
+    psi = (x[..., 0] + 1j * x[..., 1]).astype(np.complex128)
+    psi /= np.sqrt((np.abs(psi) ** 2).sum(axis=(1, 2, 3, 4), keepdims=True))
+    return psi.astype(dtype)
+
+
+# 16: a block of the reduction; 64 and 128: tiles of the FP64 and plane products
+@pytest.mark.parametrize("precision", [sky.SKY_FP64, sky.SKY_MIXED])
+@pytest.mark.parametrize("m", [1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129])
+def test_overlap_and_h_matrices(m, precision):
+    """I and H: entries, exact Hermitian symmetry, real diagonal."""
+    n = 8
+    mixed = precision == sky.SKY_MIXED
+    rng = np.random.default_rng(100 + m)
+    dt = np.complex64 if mixed else np.complex128
+    phi, hphi = _states(rng, m, n, dt), _states(rng, m, n, dt)
+    box = _box(n, m, precision)
+    out = to_dev(np.zeros_like(phi))
+    box.orthonormalize(0, to_dev(phi), to_dev(hphi), out)
+    f, h = (x.reshape(m, -1).astype(np.complex128) for x in (phi, hphi))
+    # unit vectors, 1024 products per entry: at most 1024 ulps of 1 in FP64;
+    # the two-term split carries 2^-22 per operand of an entry at most 1
+    tol = 1e-6 if mixed else 1024 * 2.0 ** -53
+    for view, right in (("overlap", f), ("hsub", h)):
+        got = to_host(box.view(view))
+        ref = f.conj() @ right.T
+        low = np.tril_indices(m)
+        assert np.abs(got[low] - ref[low])[low[0] != low[1]].max(initial=0.0) <= tol
+        assert np.abs(np.diag(got).real - np.diag(ref).real).max() <= tol
+        assert np.array_equal(got, got.conj().T)
