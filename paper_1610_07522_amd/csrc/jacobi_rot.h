@@ -46,6 +46,36 @@ __device__ inline Rot make_rot(double a, double b, double2 apq) {
   return g;
 }
 
+// The same rotation for the blocked solver's pair sub-problems.
+// With d = (b - a) / 2 and h = sqrt(d^2 + r^2): c^2 = (1 + |d| / h) / 2 and
+// s = sign(d) r / (2 h c), from three reciprocal square roots.  The rotation
+// is a serial chain on the critical path of every Jacobi round, and divisions
+// and scaled hypots made up most of it (see k_jacobi_pair).  The
+// refinement's cluster solves keep make_rot: the mixed form iterates at the
+// rounding floor of H', where the basis they pick inside a degenerate shell is
+// carried from step to step.
+__device__ inline Rot make_rot_rsq(double a, double b, double2 apq) {
+  Rot g;
+  // Couplings below 1e-18 of the diagonal scale are treated as converged (no
+  // rotation), and so are those whose square leaves the normal range: e^{i phi}
+  // from an underflowed r^2 would not have modulus 1.
+  const double r2 = apq.x * apq.x + apq.y * apq.y;
+  const double scale = 1e-18 * (fabs(a) + fabs(b));
+  if (!(r2 > scale * scale) || r2 < 1e-290) {
+    g.c = 1.0; g.s = 0.0; g.er = 1.0; g.ei = 0.0;
+    return g;
+  }
+  const double d = 0.5 * (b - a);
+  const double ir = rsqrt(r2), ih = rsqrt(d * d + r2);
+  g.er = apq.x * ir;
+  g.ei = apq.y * ir;
+  const double c2 = 0.5 + 0.5 * fabs(d) * ih;
+  const double ic = rsqrt(c2);
+  g.c = c2 * ic;
+  g.s = copysign(0.5 * (r2 * ir) * ih * ic, d >= 0.0 ? 1.0 : -1.0);
+  return g;
+}
+
 // Round-robin partner pairs of round r among np players: pair i -> (p, q).
 __device__ inline void rr_pair(int np, int r, int i, int& p, int& q) {
   const int n1 = np - 1;

@@ -3,8 +3,8 @@
 // transform), and a Hermitian eigensolver for the subspace Hamiltonian.
 //
 // The eigensolver is a blocked two-sided Jacobi method: the matrix is cut
-// into 32-wide blocks, block pairs are visited in round-robin order, each
-// 64x64 pair sub-matrix is diagonalised inside one workgroup (cyclic Jacobi
+// into 16-wide blocks, block pairs are visited in round-robin order, each
+// 32x32 pair sub-matrix is diagonalised inside one workgroup (cyclic Jacobi
 // in LDS), and the resulting unitaries are applied to the whole matrix and
 // to the eigenvector accumulator.  Jacobi suits this step because the
 // subspace Hamiltonian is nearly diagonal after the first iterations, and
@@ -29,10 +29,15 @@ constexpr int JB = 16;    // Jacobi block (pair sub-problem = 2*JB)
 constexpr int JP = 2 * JB;
 constexpr int JE = JP * JP / 256;   // pair-matrix elements per thread (256 threads)
 constexpr int RV = 64;              // rows of V per workgroup in the V update
-// Cyclic sweeps per pair sub-problem and round.  The pair tolerance is 100x
-// tighter than the global one so that the ~(n/32)^2/2 converged pair blocks
-// together stay below the global off-diagonal bound.
-constexpr int JACOBI_INNER = 3;
+// Cyclic sweeps per pair sub-problem and round: one, since a pair meets its
+// other partners before a second sweep on it pays (24^3 initialisation with
+// 151 + 50 states: 9.5, 7.5 and 5.6 ms with 3, 2 and 1; 48^3 with 1600 + 400:
+// 308, 276 and 249 ms).  Two blocks (m <= 32) are one pair for good: it runs to
+// convergence in one launch.  The pair tolerance is 100x tighter than the
+// global one so that the ~(n/32)^2/2 converged pair blocks together stay below
+// the global off-diagonal bound.
+constexpr int JACOBI_INNER = 1;
+constexpr int JACOBI_INNER_ONE_PAIR = 12;
 
 // ------------------------------------------------------------------ Cholesky
 // Factor the kw x kw diagonal block at (k0, k0) in LDS and invert it:
@@ -272,187 +277,207 @@ __global__ void k_add_identity(double2* __restrict__ P, double c, int m, const i
 }
 
 // ------------------------------------------------------------------ Jacobi
-// Diagonalise the 64x64 pair sub-matrix of blocks (P, Q) of A (ld = mp)
-// and write its unitary J (64x64, row-major, local index l < 32 -> block P).
+// Diagonalise the 32x32 pair sub-matrix of blocks (P, Q) of A (ld = mp)
+// and write its unitary J (32x32, row-major, local index l < 16 -> block P).
+// A round rotates 16 disjoint index pairs at once; thread (u, v) owns the 2x2
+// block of row pair u and column pair v, and two rows of J for column pair v.
+// A workgroup is alone on its CU and bound by the latency of a round, so a
+// round is kept to one barrier: every lane computes the rotation of its own
+// column pair (the sixteen rotations once per 16 lanes, shared with the row
+// pairs by a shuffle) straight from the matrix, which is written to the other
+// of two buffers; the pairs of every round come from a table.  With rotations
+// made by 16 threads between two barriers, divisions and index arithmetic in
+// every round, a sweep of 31 rounds took 42 us, now 28 with its loads.
 constexpr int JT = 256;    // threads of a pair sub-problem workgroup
 __global__ void __launch_bounds__(JT)
 k_jacobi_pair(const double2* __restrict__ A, int mp, const int2* __restrict__ pairs,
               double2* __restrict__ Jout, int* __restrict__ rotated, double tol, int max_inner, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double2 S[JP][JP + 1];
+  static_assert(JT == JB * JB && JB == 16, "one thread per 2x2 block, 16 pairs per quarter wave");
+  __shared__ double2 S[2][JP][JP + 1];
   __shared__ double2 J[JP][JP + 1];
-  __shared__ Rot rot[JB];
+  __shared__ unsigned short sched[JP - 1][JB];
   __shared__ double red[JT / 64][2];
-  __shared__ int done, any_rot;
   const int2 pq = pairs[blockIdx.x];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < JP * JP; e += blockDim.x) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int u = tid / JB, v = tid % JB;
+  for (int e = tid; e < JP * JP; e += JT) {
     int i = e / JP, j = e % JP;
     int gi = (i < JB ? pq.x * JB + i : pq.y * JB + i - JB);
     int gj = (j < JB ? pq.x * JB + j : pq.y * JB + j - JB);
-    S[i][j] = A[size_t(gi) * mp + gj];
+    S[0][i][j] = A[size_t(gi) * mp + gj];
     J[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
   }
-  if (tid == 0) any_rot = 0;
+  for (int e = tid; e < (JP - 1) * JB; e += JT) {
+    int p, q;
+    rr_pair(JP, e / JB, e % JB, p, q);
+    sched[e / JB][e % JB] = (unsigned short)(p < q ? p | (q << 8) : q | (p << 8));
+  }
   __syncthreads();
+  int cur = 0, any_rot = 0;
   for (int sweep = 0; sweep < max_inner; ++sweep) {
-    // convergence test on the sub-matrix
+    // convergence test on the sub-matrix (the same value in every thread)
     double off = 0.0, dia = 0.0;
-    for (int e = tid; e < JP * JP; e += blockDim.x) {
+    for (int e = tid; e < JP * JP; e += JT) {
       int i = e / JP, j = e % JP;
-      double v = S[i][j].x * S[i][j].x + S[i][j].y * S[i][j].y;
-      if (i == j) dia += v; else off += v;
+      const double2 x = S[cur][i][j];
+      double w = x.x * x.x + x.y * x.y;
+      if (i == j) dia += w; else off += w;
     }
     for (int o = 32; o > 0; o >>= 1) {
       off += __shfl_down(off, o, 64);
       dia += __shfl_down(dia, o, 64);
     }
-    if ((tid & 63) == 0) { red[tid >> 6][0] = off; red[tid >> 6][1] = dia; }
+    if (lane == 0) { red[tid >> 6][0] = off; red[tid >> 6][1] = dia; }
     __syncthreads();
-    if (tid == 0) {
-      double o = 0.0, d = 0.0;
-      for (int w = 0; w < JT / 64; ++w) { o += red[w][0]; d += red[w][1]; }
-      done = (o <= tol * tol * d) || (o < 1e-300);
-    }
-    __syncthreads();
-    if (done) break;
-    if (tid == 0) any_rot = 1;
+    double o = 0.0, d = 0.0;
+    for (int w = 0; w < JT / 64; ++w) { o += red[w][0]; d += red[w][1]; }
+    if ((o <= tol * tol * d) || (o < 1e-300)) break;
+    any_rot = 1;
     for (int r = 0; r < JP - 1; ++r) {
-      if (tid < JB) {
-        int p, q;
-        rr_pair(JP, r, tid, p, q);
-        if (p > q) { int t = p; p = q; q = t; }
-        rot[tid] = make_rot(S[p][p].x, S[q][q].x, S[p][q]);
-      }
-      __syncthreads();
-      // S <- G^H S G on 2x2 blocks (pair u rows, pair v cols)
-      for (int e = tid; e < JB * JB; e += blockDim.x) {
-        int u = e / JB, v = e % JB;
-        int pu, qu, pv, qv;
-        rr_pair(JP, r, u, pu, qu);
-        rr_pair(JP, r, v, pv, qv);
-        if (pu > qu) { int t = pu; pu = qu; qu = t; }
-        if (pv > qv) { int t = pv; pv = qv; qv = t; }
-        Rot gu = rot[u], gv = rot[v];
-        double2 epu = make_double2(gu.er, gu.ei), epv = make_double2(gv.er, gv.ei);
-        double2 x00 = S[pu][pv], x01 = S[pu][qv], x10 = S[qu][pv], x11 = S[qu][qv];
-        // right multiply by G_v: col p' = e c col_p - s col_q ; col q' = e s col_p + c col_q
-        double2 y00 = csub(cscale(gv.c, cmul(x00, epv)), cscale(gv.s, x01));
-        double2 y01 = cadd(cscale(gv.s, cmul(x00, epv)), cscale(gv.c, x01));
-        double2 y10 = csub(cscale(gv.c, cmul(x10, epv)), cscale(gv.s, x11));
-        double2 y11 = cadd(cscale(gv.s, cmul(x10, epv)), cscale(gv.c, x11));
-        // left multiply by G_u^H: row p' = conj(e) c row_p - s row_q ; row q' = conj(e) s row_p + c row_q
-        S[pu][pv] = csub(cscale(gu.c, cmulc(y00, epu)), cscale(gu.s, y10));
-        S[pu][qv] = csub(cscale(gu.c, cmulc(y01, epu)), cscale(gu.s, y11));
-        S[qu][pv] = cadd(cscale(gu.s, cmulc(y00, epu)), cscale(gu.c, y10));
-        S[qu][qv] = cadd(cscale(gu.s, cmulc(y01, epu)), cscale(gu.c, y11));
-      }
+      const int cu = sched[r][u], cv = sched[r][v];
+      const int pu = cu & 255, qu = cu >> 8, pv = cv & 255, qv = cv >> 8;
+      const double2 (*X)[JP + 1] = S[cur];
+      const double2 x00 = X[pu][pv], x01 = X[pu][qv], x10 = X[qu][pv], x11 = X[qu][qv];
+      const double2 j00 = J[2 * u][pv], j01 = J[2 * u][qv];
+      const double2 j10 = J[2 * u + 1][pv], j11 = J[2 * u + 1][qv];
+      const Rot gv = make_rot_rsq(X[pv][pv].x, X[qv][qv].x, X[pv][qv]);
+      Rot gu;
+      gu.c = __shfl(gv.c, u, 64);
+      gu.s = __shfl(gv.s, u, 64);
+      gu.er = __shfl(gv.er, u, 64);
+      gu.ei = __shfl(gv.ei, u, 64);
+      const double2 epu = make_double2(gu.er, gu.ei), epv = make_double2(gv.er, gv.ei);
+      // right multiply by G_v: col p' = e c col_p - s col_q ; col q' = e s col_p + c col_q
+      const double2 z00 = cmul(x00, epv), z10 = cmul(x10, epv);
+      const double2 y00 = csub(cscale(gv.c, z00), cscale(gv.s, x01));
+      const double2 y01 = cadd(cscale(gv.s, z00), cscale(gv.c, x01));
+      const double2 y10 = csub(cscale(gv.c, z10), cscale(gv.s, x11));
+      const double2 y11 = cadd(cscale(gv.s, z10), cscale(gv.c, x11));
+      // left multiply by G_u^H: row p' = conj(e) c row_p - s row_q ; row q' = conj(e) s row_p + c row_q
+      const double2 w00 = cmulc(y00, epu), w01 = cmulc(y01, epu);
+      double2 (*Y)[JP + 1] = S[cur ^ 1];
+      Y[pu][pv] = csub(cscale(gu.c, w00), cscale(gu.s, y10));
+      Y[pu][qv] = csub(cscale(gu.c, w01), cscale(gu.s, y11));
+      Y[qu][pv] = cadd(cscale(gu.s, w00), cscale(gu.c, y10));
+      Y[qu][qv] = cadd(cscale(gu.s, w01), cscale(gu.c, y11));
       // J <- J G
-      for (int e = tid; e < JP * JB; e += blockDim.x) {
-        int i = e / JB, v = e % JB;
-        int pv, qv;
-        rr_pair(JP, r, v, pv, qv);
-        if (pv > qv) { int t = pv; pv = qv; qv = t; }
-        Rot gv = rot[v];
-        double2 epv = make_double2(gv.er, gv.ei);
-        double2 x0 = J[i][pv], x1 = J[i][qv];
-        J[i][pv] = csub(cscale(gv.c, cmul(x0, epv)), cscale(gv.s, x1));
-        J[i][qv] = cadd(cscale(gv.s, cmul(x0, epv)), cscale(gv.c, x1));
-      }
+      const double2 k0 = cmul(j00, epv), k1 = cmul(j10, epv);
+      J[2 * u][pv] = csub(cscale(gv.c, k0), cscale(gv.s, j01));
+      J[2 * u][qv] = cadd(cscale(gv.s, k0), cscale(gv.c, j01));
+      J[2 * u + 1][pv] = csub(cscale(gv.c, k1), cscale(gv.s, j11));
+      J[2 * u + 1][qv] = cadd(cscale(gv.s, k1), cscale(gv.c, j11));
+      cur ^= 1;
       __syncthreads();
     }
   }
-  __syncthreads();
   if (tid == 0) rotated[blockIdx.x] = any_rot;
-  if (!any_rot) return;   // J = identity: the apply kernels skip this pair
+  if (!any_rot) return;   // J = identity: the apply kernel skips this pair
   double2* out = Jout + size_t(blockIdx.x) * JP * JP;
-  for (int e = tid; e < JP * JP; e += blockDim.x) out[e] = J[e / JP][e % JP];
+  for (int e = tid; e < JP * JP; e += JT) out[e] = J[e / JP][e % JP];
 }
 
-// A[{Pu,Qu}][{Pv,Qv}] <- J_u^H A[..][..] J_v for the pair pairs u >= v (block
-// number -> (u, v)); the mirrored block (v, u) gets the conjugate transpose,
-// since A stays Hermitian.  Pairs whose J is the identity are skipped.
+// One round's unitaries applied to A and to the eigenvector accumulator V, one
+// launch for both (they touch different matrices; at a few hundred states
+// each is a handful of workgroups and costs a launch's latency).
+//   Workgroups 0 .. np (np + 1) / 2 - 1: A[{Pu,Qu}][{Pv,Qv}] <- J_u^H A J_v for
+//   the pair pairs u >= v (number -> (u, v)); the mirrored block (v, u) gets
+//   the conjugate transpose, since A stays Hermitian.
+//   The rest: V[rows][{P,Q}] <- V[rows][{P,Q}] J, RV rows and one pair each.
+// Pairs whose J is the identity are skipped.  Each thread forms outputs of one
+// column, so that an element of the unitary is read from LDS once for all of
+// them (12 + 12 us in two launches at 151 states, now 10.7; at 1600 states
+// 28 + 34 us before).  The product loops stay rolled: unrolled in full they
+// spill.
 __global__ void __launch_bounds__(256)
-k_jacobi_apply_a(double2* __restrict__ A, int mp, const int2* __restrict__ pairs,
-                 const double2* __restrict__ Jall, const int* __restrict__ rotated, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double2 X[JP][JP + 1];
-  __shared__ double2 M[JP][JP + 1];
-  int b = blockIdx.x, u = 0;
-  while ((u + 1) * (u + 2) / 2 <= b) ++u;
-  const int v = b - u * (u + 1) / 2;
-  const int ru = rotated[u], rv = rotated[v];
-  if (!ru && !rv) return;
-  const int2 pu = pairs[u], pv = pairs[v];
-  const int tid = threadIdx.x;
-  auto gidx = [&](int2 p, int l) { return l < JB ? p.x * JB + l : p.y * JB + l - JB; };
-  const double2* Ju = Jall + size_t(u) * JP * JP;
-  const double2* Jv = Jall + size_t(v) * JP * JP;
-  for (int e = tid; e < JP * JP; e += blockDim.x) {
-    int i = e / JP, j = e % JP;
-    X[i][j] = A[size_t(gidx(pu, i)) * mp + gidx(pv, j)];
-    if (rv) M[i][j] = Jv[e];
-  }
-  __syncthreads();
-  double2 y[JE];
-  if (rv) {
-    for (int q = 0; q < JE; ++q) {        // Y = X Jv
-      int e = tid + q * 256, i = e / JP, j = e % JP;
-      double2 s = make_double2(0, 0);
-      for (int l = 0; l < JP; ++l) s = cadd(s, cmul(X[i][l], M[l][j]));
-      y[q] = s;
-    }
-  } else {
-    for (int q = 0; q < JE; ++q) {
-      int e = tid + q * 256;
-      y[q] = X[e / JP][e % JP];
-    }
-  }
-  __syncthreads();
-  for (int q = 0; q < JE; ++q) {
-    int e = tid + q * 256;
-    X[e / JP][e % JP] = y[q];
-    if (ru) M[e / JP][e % JP] = Ju[e];
-  }
-  __syncthreads();
-  for (int q = 0; q < JE; ++q) {        // T = Ju^H Y
-    int e = tid + q * 256, i = e / JP, j = e % JP;
-    double2 s;
-    if (ru) {
-      s = make_double2(0, 0);
-      for (int l = 0; l < JP; ++l) s = cadd(s, cconjmul(M[l][i], X[l][j]));
-    } else {
-      s = X[i][j];
-    }
-    A[size_t(gidx(pu, i)) * mp + gidx(pv, j)] = s;
-    if (u != v) A[size_t(gidx(pv, j)) * mp + gidx(pu, i)] = make_double2(s.x, -s.y);
-  }
-}
-
-// V[rows][{P,Q}] <- V[rows][{P,Q}] J for an RV-row block and one pair.
-__global__ void __launch_bounds__(256)
-k_jacobi_apply_v(double2* __restrict__ V, int mp, const int2* __restrict__ pairs,
-                 const double2* __restrict__ Jall, const int* __restrict__ rotated, const int* __restrict__ sky_gate) {
+k_jacobi_apply(double2* __restrict__ A, double2* __restrict__ V, int mp, int np,
+               const int2* __restrict__ pairs, const double2* __restrict__ Jall,
+               const int* __restrict__ rotated, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   __shared__ double2 X[RV][JP + 1];
   __shared__ double2 M[JP][JP + 1];
-  const int v = blockIdx.y, r0 = blockIdx.x * RV;
-  if (!rotated[v]) return;
-  const int2 pv = pairs[v];
-  const int tid = threadIdx.x;
-  auto gcol = [&](int l) { return l < JB ? pv.x * JB + l : pv.y * JB + l - JB; };
-  const double2* Jv = Jall + size_t(v) * JP * JP;
-  for (int e = tid; e < RV * JP; e += blockDim.x) {
-    int i = e / JP, j = e % JP;
-    X[i][j] = (r0 + i < mp) ? V[size_t(r0 + i) * mp + gcol(j)] : make_double2(0, 0);
+  const int tid = threadIdx.x, j = tid % JP, i0 = tid / JP;   // column; rows i0 + 8 q
+  auto gidx = [&](int2 p, int l) { return l < JB ? p.x * JB + l : p.y * JB + l - JB; };
+  const int na = np * (np + 1) / 2;
+  if (int(blockIdx.x) >= na) {
+    constexpr int NQ = RV * JP / 256;
+    const int nv = int(blockIdx.x) - na, v = nv % np, r0 = (nv / np) * RV;
+    if (!rotated[v]) return;
+    const int col = gidx(pairs[v], j);
+    const double2* Jv = Jall + size_t(v) * JP * JP;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int i = i0 + 8 * q;
+      X[i][j] = (r0 + i < mp) ? V[size_t(r0 + i) * mp + col] : make_double2(0, 0);
+    }
+    for (int e = tid; e < JP * JP; e += 256) M[e / JP][e % JP] = Jv[e];
+    __syncthreads();
+    double2 s[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) s[q] = make_double2(0, 0);
+#pragma unroll 2
+    for (int l = 0; l < JP; ++l) {
+      const double2 w = M[l][j];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) s[q] = cadd(s[q], cmul(X[i0 + 8 * q][l], w));
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (r0 + i0 + 8 * q < mp) V[size_t(r0 + i0 + 8 * q) * mp + col] = s[q];
+    return;
   }
-  for (int e = tid; e < JP * JP; e += blockDim.x) M[e / JP][e % JP] = Jv[e];
+  int u = 0;
+  while ((u + 1) * (u + 2) / 2 <= int(blockIdx.x)) ++u;
+  const int v = int(blockIdx.x) - u * (u + 1) / 2;
+  const int ru = rotated[u], rv = rotated[v];
+  if (!ru && !rv) return;
+  const int2 pu = pairs[u], pv = pairs[v];
+  const double2* Ju = Jall + size_t(u) * JP * JP;
+  const double2* Jv = Jall + size_t(v) * JP * JP;
+  const int col = gidx(pv, j);
+#pragma unroll
+  for (int q = 0; q < JE; ++q) {
+    const int i = i0 + 8 * q;
+    X[i][j] = A[size_t(gidx(pu, i)) * mp + col];
+    if (rv) M[i][j] = Jv[i * JP + j];
+  }
   __syncthreads();
-  for (int e = tid; e < RV * JP; e += blockDim.x) {
-    int i = e / JP, j = e % JP;
-    double2 s = make_double2(0, 0);
-    for (int l = 0; l < JP; ++l) s = cadd(s, cmul(X[i][l], M[l][j]));
-    if (r0 + i < mp) V[size_t(r0 + i) * mp + gcol(j)] = s;
+  double2 y[JE];
+  if (rv) {                               // Y = X Jv
+#pragma unroll
+    for (int q = 0; q < JE; ++q) y[q] = make_double2(0, 0);
+#pragma unroll 2
+    for (int l = 0; l < JP; ++l) {
+      const double2 w = M[l][j];
+#pragma unroll
+      for (int q = 0; q < JE; ++q) y[q] = cadd(y[q], cmul(X[i0 + 8 * q][l], w));
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < JE; ++q) y[q] = X[i0 + 8 * q][j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < JE; ++q) {
+    X[i0 + 8 * q][j] = y[q];
+    if (ru) M[i0 + 8 * q][j] = Ju[(i0 + 8 * q) * JP + j];
+  }
+  __syncthreads();
+  if (ru) {                               // T = Ju^H Y
+#pragma unroll
+    for (int q = 0; q < JE; ++q) y[q] = make_double2(0, 0);
+#pragma unroll 2
+    for (int l = 0; l < JP; ++l) {
+      const double2 w = X[l][j];
+#pragma unroll
+      for (int q = 0; q < JE; ++q) y[q] = cadd(y[q], cconjmul(M[l][i0 + 8 * q], w));
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < JE; ++q) {
+    const int row = gidx(pu, i0 + 8 * q);
+    A[size_t(row) * mp + col] = y[q];
+    if (u != v) A[size_t(col) * mp + row] = make_double2(y[q].x, -y[q].y);
   }
 }
 
@@ -664,11 +689,11 @@ int jacobi_eigh(void* Av, int m, double* w, void* Zv, void* work, double tol, in
     for (int r = 0; r < nb - 1; ++r) {
       const int2* pr = pairs + size_t(r) * np;
       hipLaunchKernelGGL(k_jacobi_pair, dim3(np), dim3(JT), 0, st, (const double2*)Ap, mp, pr,
-                         Jall, rotated, tol * 1e-2, JACOBI_INNER, g_launch_gate);
-      hipLaunchKernelGGL(k_jacobi_apply_a, dim3(np * (np + 1) / 2), dim3(256), 0, st, Ap, mp, pr,
-                         (const double2*)Jall, (const int*)rotated, g_launch_gate);
-      hipLaunchKernelGGL(k_jacobi_apply_v, dim3((mp + RV - 1) / RV, np), dim3(256), 0, st, V, mp, pr,
-                         (const double2*)Jall, (const int*)rotated, g_launch_gate);
+                         Jall, rotated, tol * 1e-2, np == 1 ? JACOBI_INNER_ONE_PAIR : JACOBI_INNER,
+                         g_launch_gate);
+      hipLaunchKernelGGL(k_jacobi_apply, dim3(np * (np + 1) / 2 + (mp + RV - 1) / RV * np),
+                         dim3(256), 0, st, Ap, V, mp, np, pr, (const double2*)Jall,
+                         (const int*)rotated, g_launch_gate);
     }
   }
   hipLaunchKernelGGL(k_jacobi_sort, dim3(m), dim3(256), 0, st, (const double2*)Ap,

@@ -209,6 +209,7 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
   __shared__ double2 J[KMAX][KMAX + 1];
   __shared__ double2 P[KMAX][KMAX + 1];
   __shared__ Rot rot[KMAX / 2];
+  __shared__ int2 pair[KMAX / 2];   // index pairs of the round
   __shared__ int idx[KMAX];
   __shared__ double red[4][2];
   __shared__ int done;
@@ -279,17 +280,14 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
         int p, q;
         rr_pair(np, r, tid, p, q);
         if (p > q) { const int t = p; p = q; q = t; }
+        pair[tid] = make_int2(p, q);
         rot[tid] = make_rot(M[p][p].x, M[q][q].x, M[p][q]);
       }
       __syncthreads();
       // M <- G^H M G on the 2x2 blocks (rotation u rows, rotation v columns)
       for (int e = tid; e < nh * nh; e += blockDim.x) {
         const int u = e / nh, v = e % nh;
-        int pu, qu, pv, qv;
-        rr_pair(np, r, u, pu, qu);
-        rr_pair(np, r, v, pv, qv);
-        if (pu > qu) { const int t = pu; pu = qu; qu = t; }
-        if (pv > qv) { const int t = pv; pv = qv; qv = t; }
+        const int pu = pair[u].x, qu = pair[u].y, pv = pair[v].x, qv = pair[v].y;
         const Rot gu = rot[u], gv = rot[v];
         const double2 epu = make_double2(gu.er, gu.ei), epv = make_double2(gv.er, gv.ei);
         const double2 x00 = M[pu][pv], x01 = M[pu][qv], x10 = M[qu][pv], x11 = M[qu][qv];
@@ -305,9 +303,7 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
       // J <- J G
       for (int e = tid; e < np * nh; e += blockDim.x) {
         const int i = e / nh, v = e % nh;
-        int pv, qv;
-        rr_pair(np, r, v, pv, qv);
-        if (pv > qv) { const int t = pv; pv = qv; qv = t; }
+        const int pv = pair[v].x, qv = pair[v].y;
         const Rot gv = rot[v];
         const double2 epv = make_double2(gv.er, gv.ei);
         const double2 x0 = J[i][pv], x1 = J[i][qv];

@@ -44,7 +44,7 @@ constexpr int PC_CAP = 16384;     // sample rows of the learned preconditioner
 constexpr int PC_HOLD = 10;       // iterations on plain damping after a rise of the residual
 constexpr int PC_RETRAIN_STEPS = 20;   // Adam steps of each online training
 constexpr double JACOBI_TOL = 1e-12;   // relative off-diagonal Frobenius norm
-constexpr int JACOBI_SWEEPS = 30;
+constexpr int JACOBI_SWEEPS = 60;      // one cyclic sweep per pair and round each
 constexpr int REFINE_ITERS = 10;     // refinement steps before the Jacobi fallback
 // refinement steps of the device-decided iteration before it hands the set
 // to the host path (which takes up to REFINE_ITERS, then Jacobi)

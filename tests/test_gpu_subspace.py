@@ -44,3 +44,27 @@ def test_overlap_and_h_matrices(m, precision):
         assert np.abs(got[low] - ref[low])[low[0] != low[1]].max(initial=0.0) <= tol
         assert np.abs(np.diag(got).real - np.diag(ref).real).max() <= tol
         assert np.array_equal(got, got.conj().T)
+
+
+# 16: a Jacobi block; 32: one pair of blocks; 33, 49: an odd block count, padded
+@pytest.mark.parametrize("m", [1, 2, 16, 17, 31, 32, 33, 48, 49, 97])
+def test_jacobi_eigenpairs(m):
+    """Loewdin of random states: the overlap's eigenpairs and psi = phi I^-1/2."""
+    n = 8
+    rng = np.random.default_rng(200 + m)
+    phi = _states(rng, m, n, np.complex128)
+    box = _box(n, m)
+    out = to_dev(np.zeros_like(phi))
+    box.orthonormalize(0, to_dev(phi), None, out)
+    f = phi.reshape(m, -1)
+    I = f.conj() @ f.T
+    lam, z = np.linalg.eigh(I)
+    # off-diagonal norm at most 1e-12 of the matrix norm (sqrt(m) to 2 sqrt(m))
+    tol = 2e-12 * np.sqrt(m)
+    assert np.abs(to_host(box.view("ritz")) - lam).max() <= tol
+    v = to_host(box.view("evec"))
+    assert np.abs(v.conj().T @ v - np.eye(m)).max() <= 1e-13 * max(m, 8)
+    assert np.abs(I @ v - v * to_host(box.view("ritz"))).max() <= tol
+    psi = to_host(out).reshape(m, -1)
+    ref = ((z * lam ** -0.5) @ z.conj().T).T @ f
+    assert np.abs(psi - ref).max() <= tol
