@@ -15,7 +15,13 @@
 // runs the same stages backwards, so a derivative F^-1[m(k) F psi] costs two
 // LDS exchanges and returns the result to the same thread/positions that
 // loaded the input.  Forward sign: X[k] = sum_n x[n] exp(-2 pi i n k / N);
-// the inverse carries the 1/N.
+// neither direction scales: the 1/N of the inverse goes into the multiplier.
+//
+// The complex64 passes issue as many vector instructions as their memory time
+// holds (48^3: about 1500 per line pair and pass, 1.17 ms for 1600 states at
+// one per cycle, against 1.2 to 1.9 ms per pass), so the transforms are kept
+// lean: twiddle-free and multiply-add forms of the small DFTs, no products
+// by w^0, one multiplier per frequency, twiddles from a table.
 #pragma once
 
 #include "sky_common.h"
@@ -23,23 +29,6 @@
 namespace sky {
 
 // ---------------------------------------------------------------- small DFTs
-// Twiddle exp(-+2 pi i m / R) for R in {6, 8}; forward sign unless INV.
-template <typename T, int R, bool INV> __device__ inline cpx<T> tw_small(int m) {
-  constexpr T s3 = T(0.86602540378443864676);  // sin(pi/3)
-  constexpr T r2 = T(0.70710678118654752440);  // 1/sqrt(2)
-  T c = 0, s = 0;  // exp(-2 pi i m / R) = c + i s
-  if constexpr (R == 6) {
-    const T C[6] = {T(1), T(0.5), T(-0.5), T(-1), T(-0.5), T(0.5)};
-    const T S[6] = {T(0), -s3, -s3, T(0), s3, s3};
-    c = C[m]; s = S[m];
-  } else {
-    const T C[8] = {T(1), r2, T(0), -r2, T(-1), -r2, T(0), r2};
-    const T S[8] = {T(0), -r2, T(-1), -r2, T(0), r2, T(1), r2};
-    c = C[m]; s = S[m];
-  }
-  return INV ? mk(c, -s) : mk(c, s);
-}
-
 template <typename T, int R, bool INV> struct DFT;
 
 template <typename T, bool INV> struct DFT<T, 1, INV> {
@@ -77,37 +66,45 @@ template <typename T, bool INV> struct DFT<T, 4, INV> {
   }
 };
 
-// Composite length P*Q: inner DFT_P over x[q + Q p], twiddle, outer DFT_Q.
-template <typename T, int P, int Q, bool INV> struct DFTComposite {
+// 6 = 2 * 3 as a prime-factor transform: with n = 3 n1 + 2 n2 and
+// k = 3 k1 + 4 k2 (mod 6) the two factors need no twiddles between them (36
+// real operations; the common-factor split took 44).
+template <typename T, bool INV> struct DFT<T, 6, INV> {
   __device__ static inline void run(cpx<T>* v) {
-    constexpr int R = P * Q;
-    cpx<T> y[Q][P];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-#pragma unroll
-      for (int p = 0; p < P; ++p) y[q][p] = v[q + Q * p];
-      DFT<T, P, INV>::run(y[q]);
-#pragma unroll
-      for (int kp = 1; kp < P; ++kp)
-        if (q > 0) y[q][kp] = y[q][kp] * tw_small<T, R, INV>(q * kp);
-    }
-#pragma unroll
-    for (int kp = 0; kp < P; ++kp) {
-      cpx<T> z[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) z[q] = y[q][kp];
-      DFT<T, Q, INV>::run(z);
-#pragma unroll
-      for (int kq = 0; kq < Q; ++kq) v[kp + P * kq] = z[kq];
-    }
+    cpx<T> s[3] = {v[0] + v[3], v[2] + v[5], v[4] + v[1]};
+    cpx<T> d[3] = {v[0] - v[3], v[2] - v[5], v[4] - v[1]};
+    DFT<T, 3, INV>::run(s);
+    DFT<T, 3, INV>::run(d);
+    v[0] = s[0]; v[4] = s[1]; v[2] = s[2];
+    v[3] = d[0]; v[1] = d[1]; v[5] = d[2];
   }
 };
 
-template <typename T, bool INV> struct DFT<T, 6, INV> {
-  __device__ static inline void run(cpx<T>* v) { DFTComposite<T, 2, 3, INV>::run(v); }
-};
+// 8 as even and odd 4-point transforms; the eighth-turn factors
+// (1 -+ i) / sqrt(2) enter the last additions as multiply-adds (52 real
+// operations; with general twiddle products 60).
 template <typename T, bool INV> struct DFT<T, 8, INV> {
-  __device__ static inline void run(cpx<T>* v) { DFTComposite<T, 2, 4, INV>::run(v); }
+  __device__ static inline void run(cpx<T>* v) {
+    constexpr T r2 = T(0.70710678118654752440);  // 1/sqrt(2)
+    cpx<T> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    DFT<T, 4, INV>::run(e);
+    DFT<T, 4, INV>::run(o);
+    // o[1] w, o[2] w^2, o[3] w^3 with w = exp(-+ i pi / 4); the first and last
+    // without their 1/sqrt(2)
+    const cpx<T> t1 = INV ? mk(o[1].re - o[1].im, o[1].im + o[1].re)
+                          : mk(o[1].re + o[1].im, o[1].im - o[1].re);
+    const cpx<T> t2 = INV ? mul_i(o[2]) : mk(o[2].im, -o[2].re);
+    const cpx<T> t3 = INV ? mk(-o[3].re - o[3].im, o[3].re - o[3].im)
+                          : mk(o[3].im - o[3].re, -o[3].re - o[3].im);
+    v[0] = e[0] + o[0];
+    v[4] = e[0] - o[0];
+    v[1] = mk(e[1].re + r2 * t1.re, e[1].im + r2 * t1.im);
+    v[5] = mk(e[1].re - r2 * t1.re, e[1].im - r2 * t1.im);
+    v[2] = e[2] + t2;
+    v[6] = e[2] - t2;
+    v[3] = mk(e[3].re + r2 * t3.re, e[3].im + r2 * t3.im);
+    v[7] = mk(e[3].re - r2 * t3.re, e[3].im - r2 * t3.im);
+  }
 };
 
 // ---------------------------------------------------------------- line engine
@@ -137,10 +134,8 @@ template <typename T, int N, int S> struct LineFFT {
       for (int s = 0; s < S; ++s) {
         DFT<T, R1, false>::run(va[s]);
 #pragma unroll
-        for (int k1 = 0; k1 < R1; ++k1) {
-          cpx<T> w = twN[j * k1];
-          Y[(s * R1 + k1) * YROW + j] = va[s][k1] * w;
-        }
+        for (int k1 = 0; k1 < R1; ++k1)
+          Y[(s * R1 + k1) * YROW + j] = k1 ? va[s][k1] * twN[j * k1] : va[s][k1];
       }
     }
     __syncthreads();
@@ -164,35 +159,34 @@ template <typename T, int N, int S> struct LineFFT {
         DFT<T, R2, true>::run(vb[s]);
 #pragma unroll
         for (int j2 = 0; j2 < R2; ++j2)
-          Y[(s * R1 + j) * YROW + j2] = vb[s][j2] * conj(twN[j2 * j]);
+          Y[(s * R1 + j) * YROW + j2] = j2 ? vb[s][j2] * conj(twN[j2 * j]) : vb[s][j2];
       }
     }
     __syncthreads();
     if (j < R2) {
-      constexpr T inv_n = T(1) / T(N);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
 #pragma unroll
         for (int k1 = 0; k1 < R1; ++k1) va[s][k1] = Y[(s * R1 + k1) * YROW + j];
         DFT<T, R1, true>::run(va[s]);
-#pragma unroll
-        for (int j1 = 0; j1 < R1; ++j1) va[s][j1] = inv_n * va[s][j1];
       }
     }
     __syncthreads();
   }
 
   // In-place spectral derivative i*(k + kshift) along the line, Nyquist kept
-  // (k = -N/2); kshift is the Bloch shift of twisted boundary conditions.
+  // (k = -N/2); kshift is the Bloch shift of twisted boundary conditions.  kun
+  // and ksn are the wave-number unit and kshift divided by N (the inverse's
+  // scale).  R2 is even, so whether a frequency wraps depends on k2 alone.
   __device__ static inline void deriv(cpx<T> (&va)[S][R1], cpx<T>* Y, int j,
-                                      const cpx<T>* twN, T kunit, T kshift = T(0)) {
+                                      const cpx<T>* twN, T kun, T ksn = T(0)) {
     cpx<T> vb[S][R2];
     forward(va, vb, Y, j, twN);
     if (j < R1) {
+      const T tj = T(j);
 #pragma unroll
       for (int k2 = 0; k2 < R2; ++k2) {
-        int f = j + R1 * k2;
-        T k = kunit * T(f < N / 2 ? f : f - N) + kshift;
+        const T k = kun * (tj + T(R1 * k2 - (k2 < R2 / 2 ? 0 : N))) + ksn;
 #pragma unroll
         for (int s = 0; s < S; ++s) vb[s][k2] = mul_i(k * vb[s][k2]);
       }
@@ -239,7 +233,8 @@ template <typename T, int N, int S> struct LineFFTInPlace {
       for (int s = 0; s < S; ++s) {
         DFT<T, R1, false>::run(va[s]);
 #pragma unroll
-        for (int k1 = 0; k1 < R1; ++k1) base[s * sp + (k1 * R2 + j) * es] = va[s][k1] * twN[j * k1];
+        for (int k1 = 0; k1 < R1; ++k1)
+          base[s * sp + (k1 * R2 + j) * es] = k1 ? va[s][k1] * twN[j * k1] : va[s][k1];
       }
     }
     __syncthreads();
@@ -264,31 +259,50 @@ template <typename T, int N, int S> struct LineFFTInPlace {
         DFT<T, R2, true>::run(vb[s]);
 #pragma unroll
         for (int j2 = 0; j2 < R2; ++j2)
-          base[s * sp + (j * R2 + j2) * es] = vb[s][j2] * conj(twN[j2 * j]);
+          base[s * sp + (j * R2 + j2) * es] = j2 ? vb[s][j2] * conj(twN[j2 * j]) : vb[s][j2];
       }
     }
     __syncthreads();
     if (j < R2) {
-      constexpr T inv_n = T(1) / T(N);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
 #pragma unroll
         for (int k1 = 0; k1 < R1; ++k1) va[s][k1] = base[s * sp + (k1 * R2 + j) * es];
         DFT<T, R1, true>::run(va[s]);
-#pragma unroll
-        for (int j1 = 0; j1 < R1; ++j1) va[s][j1] = inv_n * va[s][j1];
       }
     }
     __syncthreads();
   }
 };
 
-// exp(-2 pi i m / N), m < N, into LDS (all threads of the block help).
+// cos(2 pi m / 192), m = 0 .. 48 (192 is a multiple of every grid size).
+static __device__ const double TW_COS[49] = {
+    1.0, 0.99946458747636568, 0.99785892323860348, 0.99518472667219693,
+    0.99144486137381038, 0.98664333208487898, 0.98078528040323043, 0.97387697927733363,
+    0.96592582628906831, 0.95694033573220882, 0.94693012949510569, 0.93590592675732565,
+    0.92387953251128674, 0.91086382492117579, 0.89687274153268826, 0.88192126434835505,
+    0.8660254037844386, 0.84920218152657889, 0.83146961230254524, 0.81284668459161524,
+    0.79335334029123517, 0.77301045336273699, 0.75183980747897738, 0.72986407269783571,
+    0.70710678118654757, 0.68359230202287125, 0.65934581510006884, 0.63439328416364549,
+    0.60876142900872066, 0.58247769686780215, 0.55557023301960218, 0.52806785065036799,
+    0.5, 0.47139673682599764, 0.4422886902190013, 0.41270702980439472,
+    0.38268343236508978, 0.35225004792123349, 0.32143946530316159, 0.29028467725446239,
+    0.25881904510252074, 0.2270762630343732, 0.19509032201612828, 0.16289547339458874,
+    0.1305261922200516, 0.098017140329560604, 0.065403129230143062, 0.032719082821776144,
+    0.0};
+
+// exp(-2 pi i m / N), m < N, into LDS (all threads of the block help), from
+// the quarter-wave table: its loads overlap the caller's line loads, where
+// the sine and cosine of each workgroup's 48 angles cost its first wave about
+// 200 instructions.
 template <typename T, int N> __device__ inline void load_twiddles(cpx<T>* tw) {
+  static_assert(192 % N == 0, "the table holds the 192nd roots of unity");
   for (int m = threadIdx.x; m < N; m += blockDim.x) {
-    double s, c;
-    sincospi(-2.0 * double(m) / double(N), &s, &c);
-    tw[m] = mk(T(c), T(s));
+    const int i = m * (192 / N), q = i / 48, r = i % 48;
+    const double a = TW_COS[r], b = TW_COS[48 - r];   // cos, sin of the angle past quadrant q
+    const double c = q == 0 ? a : q == 1 ? -b : q == 2 ? -a : b;
+    const double s = q == 0 ? b : q == 1 ? a : q == 2 ? -b : -a;
+    tw[m] = mk(T(c), T(-s));
   }
   __syncthreads();
 }

@@ -565,12 +565,17 @@ k_overlap_planes(const unsigned short* __restrict__ PA, const unsigned short* __
 // element per thread, eight partials in flight: bound by the partials' read
 // (mean of 1600 and 400 states at 48^3, with the mirror kernels it replaces:
 // 162 -> 86 us); the mirrored block goes out through LDS, both writes
-// coalesced.
+// coalesced.  diag0, diag1 (may be null): diagonals summed in FP64 from the
+// states themselves.  A state's overlap with itself is where the split's errors
+// do not average out (the dropped l l' products are all of one sign, and a
+// nearly constant state repeats one rounding at every point); to first order
+// the subspace eigenvalues are these diagonals' ratios.
 constexpr int RB = BT / 16;   // 16 x 16 blocks per tile side
 __global__ void __launch_bounds__(256)
 k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, int m, double scale,
                         const unsigned int* __restrict__ mxA, const unsigned int* __restrict__ mxB0,
-                        const unsigned int* __restrict__ mxB1, double2* __restrict__ C0,
+                        const unsigned int* __restrict__ mxB1, const double* __restrict__ diag0,
+                        const double* __restrict__ diag1, double2* __restrict__ C0,
                         double2* __restrict__ C1, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   __shared__ double2 T[16][17];
@@ -603,7 +608,11 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
       re += double(v.x);
       im += double(v.y);
     }
-    const double2 v = make_double2(sc * re, col == row ? 0.0 : sc * im);
+    double2 v = make_double2(sc * re, sc * im);
+    if (col == row) {
+      const double* dg = z ? diag1 : diag0;
+      v = make_double2(dg != nullptr ? dg[row] : v.x, 0.0);
+    }
     C[size_t(row) * m + col] = v;
     T[r][c] = v;
   }
@@ -781,7 +790,7 @@ void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
                           const unsigned int* mxA, const unsigned int* mxB0,
                           const unsigned int* mxB1, int m, long k, double scale, void* C0,
                           void* C1, void* part, hipStream_t st, hipEvent_t* ev, int split_req,
-                          int waves) {
+                          int waves, const double* diag0, const double* diag1) {
   if (m <= 0) return;
   const int nt = (m + BT - 1) / BT;
   const int npair = nt * (nt + 1) / 2;
@@ -803,7 +812,7 @@ void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
   if (ev) hipEventRecord(ev[1], st);
   hipLaunchKernelGGL(k_overlap_reduce_planes, dim3(unsigned(npair * RB * RB), nz), dim3(256), 0, st,
                      (const float2*)part, npair, split, m, scale, mxA, mxB0, PB1 ? mxB1 : mxB0,
-                     (double2*)C0, (double2*)C1, g_launch_gate);
+                     diag0, diag1, (double2*)C0, (double2*)C1, g_launch_gate);
 }
 
 void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,

@@ -9,7 +9,6 @@
 
 namespace sky {
 
-// Spin-orbit matrix A_dir = (W x sigma)_dir = ax*sx + ay*sy + az*sz.
 // Field value at point r in the kernel's precision: complex64 kernels read
 // the FP32 copies (the same rounding as converting the FP64 value).
 template <typename T> __device__ inline T fld_U(const MeanFieldPtrs& m, size_t r) {
@@ -22,19 +21,40 @@ template <typename T> __device__ inline T fld_W(const MeanFieldPtrs& m, size_t r
   if constexpr (sizeof(T) == 4) return m.W32[r]; else return m.W[r];
 }
 
-template <int DIR, typename V> __device__ inline void so_coeffs(V wx, V wy, V wz, V& ax, V& ay, V& az) {
-  if (DIR == 0) { ax = 0.0; ay = -wz; az = wy; }
-  else if (DIR == 1) { ax = wz; ay = 0.0; az = -wx; }
-  else { ax = -wy; ay = wx; az = 0.0; }
+// i (A_dir / 2) applied to the spinor (p, q), A_dir = (W x sigma)_dir; a and b
+// are the halves of A_dir's two non-zero components: (-W_z, W_y) along
+// (sigma_y, sigma_z) for x, (W_z, -W_x) along (sigma_x, sigma_z) for y, and
+// (-W_y, W_x) along (sigma_x, sigma_y) for z.
+template <int DIR, typename T> __device__ inline void half_so(T a, T b, cpx<T> p, cpx<T> q,
+                                                              cpx<T>& op, cpx<T>& oq) {
+  if (DIR == 0) {
+    op = mk(a * q.re - b * p.im, a * q.im + b * p.re);
+    oq = mk(b * q.im - a * p.re, -a * p.im - b * q.re);
+  } else if (DIR == 1) {
+    op = mk(-b * p.im - a * q.im, b * p.re + a * q.re);
+    oq = mk(b * q.im - a * p.im, a * p.re - b * q.re);
+  } else {
+    op = mk(b * q.re - a * q.im, b * q.im + a * q.re);
+    oq = mk(-b * p.re - a * p.im, a * p.re - b * p.im);
+  }
 }
 
-// (a.sigma) chi for a real 3-vector a.
-template <typename T> __device__ inline void sigma_apply(T ax, T ay, T az, cpx<T> u, cpx<T> d,
-                                                         cpx<T>& ou, cpx<T>& od) {
-  // [[az, ax - i ay], [ax + i ay, -az]]
-  cpx<T> xm = mk(ax, -ay), xp = mk(ax, ay);
-  ou = az * u + xm * d;
-  od = xp * u - az * d;
+// The local terms of one direction of h at grid point r: (i/2) A D psi into
+// acc and g = (i/2) A psi - B D psi into d (D psi on entry).
+template <typename T, int N, int DIR>
+__device__ inline void h_local(const MeanFieldPtrs& mf, size_t r, cpx<T> vu, cpx<T> vd,
+                               cpx<T>& du, cpx<T>& dd, cpx<T>& au, cpx<T>& ad) {
+  constexpr int N3 = N * N * N;
+  const T B = fld_B<T>(mf, r);
+  T a, b;
+  if (DIR == 0) { a = T(-0.5) * fld_W<T>(mf, 2 * N3 + r); b = T(0.5) * fld_W<T>(mf, N3 + r); }
+  else if (DIR == 1) { a = T(0.5) * fld_W<T>(mf, 2 * N3 + r); b = T(-0.5) * fld_W<T>(mf, r); }
+  else { a = T(-0.5) * fld_W<T>(mf, N3 + r); b = T(0.5) * fld_W<T>(mf, r); }
+  cpx<T> gu, gd;
+  half_so<DIR>(a, b, du, dd, au, ad);
+  half_so<DIR>(a, b, vu, vd, gu, gd);
+  du = gu - B * du;
+  dd = gd - B * dd;
 }
 
 // Workgroup sum of one double per thread (blockDim <= 256), result in thread 0.
@@ -77,7 +97,8 @@ template <typename T> __device__ inline float cabs_max(cpx<T> z) {
 template <typename T, int N, int DIR, bool FIRST, bool LAST, int LP>
 __global__ void __launch_bounds__((LineCfg<N, LP>::THREADS))
 k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtrs mf,
-         GridArgs g, double* __restrict__ eps_part, unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
+         GridArgs g, double* __restrict__ eps_part, double* __restrict__ nrm_part,
+         unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N, LP>;
   using F = LineFFT<T, N, 2>;
@@ -86,7 +107,6 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   __shared__ cpx<T> tw[N];
   __shared__ cpx<T> Ybuf[C::LPW * YS];
   __shared__ double red[4];
-  load_twiddles<T, N>(tw);
 
   int line, j;
   thread_role<N, DIR, LP>(threadIdx.x, line, j);
@@ -97,8 +117,7 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   const cpx<T>* p = psi + soff;
   cpx<T>* hp = hpsi + soff;
   cpx<T>* Y = Ybuf + line * YS;
-  const T kunit = T(g.kunit);
-  const T kshift = T(g.tw[DIR]);
+  const T kun = T(g.kunit * (1.0 / N)), ksn = T(g.tw[DIR] * (1.0 / N));
 
   cpx<T> v[2][R1], d[2][R1];
   if (j < R2) {
@@ -111,7 +130,8 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
       d[1][j1] = v[1][j1];
     }
   }
-  F::deriv(d, Y, j, tw, kunit, kshift);
+  load_twiddles<T, N>(tw);
+  F::deriv(d, Y, j, tw, kun, ksn);
 
   // g (into d) and the accumulated local terms (into acc)
   cpx<T> acc[2][R1];
@@ -119,26 +139,17 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
-      const T B = fld_B<T>(mf, r);
-      T ax, ay, az;
-      so_coeffs<DIR>(fld_W<T>(mf, r), fld_W<T>(mf, N3 + r), fld_W<T>(mf, 2 * N3 + r), ax, ay, az);
-      cpx<T> au, ad, bu, bd;
-      sigma_apply<T>(T(ax), T(ay), T(az), d[0][j1], d[1][j1], au, ad);     // A D psi
-      sigma_apply<T>(T(ax), T(ay), T(az), v[0][j1], v[1][j1], bu, bd);     // A psi
-      acc[0][j1] = T(0.5) * mul_i(au);
-      acc[1][j1] = T(0.5) * mul_i(ad);
+      h_local<T, N, DIR>(mf, r, v[0][j1], v[1][j1], d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
       if (FIRST) {
         const T U = fld_U<T>(mf, r);
         acc[0][j1] = acc[0][j1] + U * v[0][j1];
         acc[1][j1] = acc[1][j1] + U * v[1][j1];
       }
-      d[0][j1] = T(0.5) * mul_i(bu) - B * d[0][j1];
-      d[1][j1] = T(0.5) * mul_i(bd) - B * d[1][j1];
     }
   }
-  F::deriv(d, Y, j, tw, kunit, kshift);
+  F::deriv(d, Y, j, tw, kun, ksn);
 
-  double dot = 0.0;
+  double dot = 0.0, nrm = 0.0;
   float am = 0.0f;
   if (j < R2) {
 #pragma unroll
@@ -149,7 +160,10 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
         cpx<T> t = acc[s][j1] + d[s][j1];
         if (!FIRST) t = t + hp[s * N3 + r];
         hp[s * N3 + r] = t;
-        if (LAST) dot += double(v[s][j1].re) * double(t.re) + double(v[s][j1].im) * double(t.im);
+        if (LAST && eps_part != nullptr)
+          dot += double(v[s][j1].re) * double(t.re) + double(v[s][j1].im) * double(t.im);
+        if (LAST && nrm_part != nullptr)
+          nrm += double(v[s][j1].re) * double(v[s][j1].re) + double(v[s][j1].im) * double(v[s][j1].im);
         if (LAST) am = fmaxf(am, cabs_max(t));
       }
     }
@@ -158,18 +172,81 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
     double sum = block_sum(dot, red);
     if (threadIdx.x == 0) eps_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
+  if (LAST && nrm_part != nullptr) {
+    double sum = block_sum(nrm, red);
+    if (threadIdx.x == 0) nrm_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
+  }
   if (LAST && amax != nullptr) block_amax(am, amax);
 }
 
-// Sum the per-workgroup partials of each state: out[s] = sum_t part[s][t].
-__global__ void k_sum_partials(const double* __restrict__ part, int ntile, int nstate,
-                               double* __restrict__ out, const int* __restrict__ sky_gate) {
+// Sums of the per-workgroup partials of each state, out[s] = sum_t part[s][t]:
+// one wave per state (lane t takes t, t + 64, ... in order, then a fixed
+// butterfly), blockIdx.y picks one of two sets.  (One thread per state walked
+// its 144 partials at 48^3 as a serial chain of loads, 9.3 us.)
+__global__ void __launch_bounds__(256)
+k_sum_partials(const double* __restrict__ part0, const double* __restrict__ part1, int ntile,
+               int nstate, double* __restrict__ out0, double* __restrict__ out1,
+               const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+  const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (s >= nstate) return;
+  const double* part = blockIdx.y ? part1 : part0;
   double acc = 0.0;
-  for (int t = 0; t < ntile; ++t) acc += part[size_t(s) * ntile + t];
-  out[s] = acc;
+  for (int t = lane; t < ntile; t += 64) acc += part[size_t(s) * ntile + t];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+  if (lane == 0) (blockIdx.y ? out1 : out0)[s] = acc;
+}
+
+static void sum_partials(const double* part0, const double* part1, int ntile, int nstate,
+                         double* out0, double* out1, hipStream_t st) {
+  hipLaunchKernelGGL(k_sum_partials, dim3(unsigned(nstate + 3) / 4, part1 ? 2 : 1), dim3(256), 0, st,
+                     part0, part1, ntile, nstate, out0, out1, g_launch_gate);
+}
+
+// Per workgroup of a grid (tiles, states): partials of Re <a|b> and <a|a> of a
+// state, and the largest |component| of a and of b merged into mx[0] and
+// mx[1] (b may be null: <a|a> and mx[0] only), for states whose producer did
+// not form them.
+__global__ void __launch_bounds__(256)
+k_state_dots(const float2* __restrict__ a, const float2* __restrict__ b, long V, double dV,
+             double* __restrict__ dot_part, double* __restrict__ nrm_part,
+             unsigned int* __restrict__ mx, const int* __restrict__ sky_gate) {
+  if (sky_gate != nullptr && *sky_gate == 0) return;
+  __shared__ double red[4];
+  const size_t off = size_t(blockIdx.y) * V;
+  double dot = 0.0, nrm = 0.0;
+  float ma = 0.0f, mb = 0.0f;
+  for (long i = long(blockIdx.x) * 256 + threadIdx.x; i < V; i += long(gridDim.x) * 256) {
+    const float2 x = a[off + i];
+    nrm += double(x.x) * double(x.x) + double(x.y) * double(x.y);
+    ma = fmaxf(ma, fmaxf(fabsf(x.x), fabsf(x.y)));
+    if (b != nullptr) {
+      const float2 y = b[off + i];
+      dot += double(x.x) * double(y.x) + double(x.y) * double(y.y);
+      mb = fmaxf(mb, fmaxf(fabsf(y.x), fabsf(y.y)));
+    }
+  }
+  const size_t at = size_t(blockIdx.y) * gridDim.x + blockIdx.x;
+  const double sn = block_sum(nrm, red);
+  if (threadIdx.x == 0) nrm_part[at] = sn * dV;
+  block_amax(ma, mx);
+  if (b == nullptr) return;
+  const double sd = block_sum(dot, red);
+  if (threadIdx.x == 0) dot_part[at] = sd * dV;
+  block_amax(mb, mx + 1);
+}
+
+void state_dots(const void* a, const void* b, int n, int nstate, double dV, double* part,
+                double* dot, double* nrm, unsigned int* mx, hipStream_t st) {
+  if (nstate <= 0) return;
+  const long V = 2L * n * n * n;
+  const int nt = std::min(grid_ntiles(n), 8);
+  double* npart = part + size_t(nstate) * nt;
+  hipLaunchKernelGGL(k_state_dots, dim3(nt, nstate), dim3(256), 0, st, (const float2*)a,
+                     (const float2*)b, V, dV, part, npart, mx, g_launch_gate);
+  if (b) sum_partials(part, npart, nt, nstate, dot, nrm, st);
+  else sum_partials(npart, nullptr, nt, nstate, nrm, nullptr, st);
 }
 
 // ------------------------------------------------------------------ xy planes
@@ -233,34 +310,22 @@ __device__ inline double tree_sum(double v, double* buf) {
 template <typename T, int N, int DIR>
 __device__ inline void h_dir_line(const cpx<T> (&v)[2][Fact<N>::R1], cpx<T> (&out)[2][Fact<N>::R1],
                                   const int (&r)[Fact<N>::R1], cpx<T>* Y, int j,
-                                  const cpx<T>* tw, T kunit, T kshift,
-                                  const MeanFieldPtrs& mf) {
+                                  const cpx<T>* tw, T kun, T ksn, const MeanFieldPtrs& mf) {
   using F = LineFFT<T, N, 2>;
-  constexpr int R1 = Fact<N>::R1, R2 = Fact<N>::R2, N3 = N * N * N;
+  constexpr int R1 = Fact<N>::R1, R2 = Fact<N>::R2;
   cpx<T> d[2][R1];
 #pragma unroll
   for (int j1 = 0; j1 < R1; ++j1) {
     d[0][j1] = v[0][j1];
     d[1][j1] = v[1][j1];
   }
-  F::deriv(d, Y, j, tw, kunit, kshift);
+  F::deriv(d, Y, j, tw, kun, ksn);
   if (j < R2) {
 #pragma unroll
-    for (int j1 = 0; j1 < R1; ++j1) {
-      const int q = r[j1];
-      const T B = fld_B<T>(mf, q);
-      T ax, ay, az;
-      so_coeffs<DIR>(fld_W<T>(mf, q), fld_W<T>(mf, N3 + q), fld_W<T>(mf, 2 * N3 + q), ax, ay, az);
-      cpx<T> au, ad, bu, bd;
-      sigma_apply<T>(T(ax), T(ay), T(az), d[0][j1], d[1][j1], au, ad);     // A D psi
-      sigma_apply<T>(T(ax), T(ay), T(az), v[0][j1], v[1][j1], bu, bd);     // A psi
-      out[0][j1] = T(0.5) * mul_i(au);
-      out[1][j1] = T(0.5) * mul_i(ad);
-      d[0][j1] = T(0.5) * mul_i(bu) - B * d[0][j1];
-      d[1][j1] = T(0.5) * mul_i(bd) - B * d[1][j1];
-    }
+    for (int j1 = 0; j1 < R1; ++j1)
+      h_local<T, N, DIR>(mf, r[j1], v[0][j1], v[1][j1], d[0][j1], d[1][j1], out[0][j1], out[1][j1]);
   }
-  F::deriv(d, Y, j, tw, kunit, kshift);
+  F::deriv(d, Y, j, tw, kun, ksn);
   if (j < R2) {
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
@@ -275,7 +340,8 @@ __device__ inline void h_dir_line(const cpx<T> (&v)[2][Fact<N>::R1], cpx<T> (&ou
 template <typename T, int N>
 __global__ void __launch_bounds__(PlaneCfg<N>::THREADS)
 k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtrs mf, GridArgs g,
-          double* __restrict__ eps_part, unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
+          double* __restrict__ eps_part, double* __restrict__ nrm_part,
+          unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = PlaneCfg<N>;
   using F = LineFFT<T, N, 2>;
@@ -285,7 +351,6 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
   __shared__ cpx<T> P[2 * SP];
   constexpr int XS = plane_xstride<T, N>(), YS = F::YSIZE;   // x- and y-line buffers
   __shared__ cpx<T> Ybuf[N * (XS > YS ? XS : YS)];
-  load_twiddles<T, N>(tw);
   const int zoff = blockIdx.x * N2;
   const size_t soff = size_t(blockIdx.y) * 2 * N3;
   const cpx<T>* p = psi + soff;
@@ -299,8 +364,8 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
       P[s * SP + (e / N) * PITCH + e % N] = p[s * N3 + zoff + e];
     }
   }
-  __syncthreads();
-  const T kunit = T(g.kunit);
+  load_twiddles<T, N>(tw);   // ends with a barrier
+  const T kun = T(g.kunit * (1.0 / N));
   // x lines: row ly, role jx (role fastest: consecutive threads, consecutive x)
   const int jx = threadIdx.x % RT, ly = threadIdx.x / RT;
   cpx<T> vx[2][R1], ax[2][R1];
@@ -314,7 +379,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
       vx[1][j1] = P[SP + ly * PITCH + x];
     }
   }
-  h_dir_line<T, N, 0>(vx, ax, rx, Ybuf + ly * XS, jx, tw, kunit, T(g.tw[0]), mf);
+  h_dir_line<T, N, 0>(vx, ax, rx, Ybuf + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)), mf);
   // y lines: column lx (line fastest: consecutive threads, consecutive x)
   const int lx = threadIdx.x % N, jy = threadIdx.x / N;
   cpx<T> vy[2][R1], ay[2][R1];
@@ -337,8 +402,8 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
     }
   }
   __syncthreads();
-  h_dir_line<T, N, 1>(vy, ay, ry, Ybuf + lx * YS, jy, tw, kunit, T(g.tw[1]), mf);
-  double dot = 0.0;
+  h_dir_line<T, N, 1>(vy, ay, ry, Ybuf + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)), mf);
+  double dot = 0.0, nrm = 0.0;
   float am = 0.0f;
   if (jy < R2) {
 #pragma unroll
@@ -348,7 +413,10 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
       for (int s = 0; s < 2; ++s) {
         const cpx<T> t = ay[s][j1] + P[s * SP + y * PITCH + lx] + hp[s * N3 + ry[j1]];
         hp[s * N3 + ry[j1]] = t;
-        dot += double(vy[s][j1].re) * double(t.re) + double(vy[s][j1].im) * double(t.im);
+        if (eps_part != nullptr)
+          dot += double(vy[s][j1].re) * double(t.re) + double(vy[s][j1].im) * double(t.im);
+        if (nrm_part != nullptr)
+          nrm += double(vy[s][j1].re) * double(vy[s][j1].re) + double(vy[s][j1].im) * double(vy[s][j1].im);
         am = fmaxf(am, cabs_max(t));
       }
     }
@@ -357,6 +425,11 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
     __syncthreads();   // P is free again: reuse it for the reduction
     const double sum = tree_sum(dot, reinterpret_cast<double*>(P));
     if (threadIdx.x == 0) eps_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
+  }
+  if (nrm_part != nullptr) {
+    __syncthreads();
+    const double sum = tree_sum(nrm, reinterpret_cast<double*>(P));
+    if (threadIdx.x == 0) nrm_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
   if (amax != nullptr) block_amax(am, amax);
 }
@@ -618,6 +691,18 @@ k_damp_y(cpx<T>* __restrict__ buf, const int* __restrict__ sky_gate) {
   }
 }
 
+// a / b in FP64; for complex64 states, which round the quotient to FP32, from
+// the reciprocal estimate and one Newton step (within 2^-45, a third of the
+// instructions of the exact division).
+template <typename T> __device__ inline double damp_quotient(double a, double b) {
+  if constexpr (sizeof(T) == 4) {
+    const double y = __builtin_amdgcn_rcp(b);
+    return a * (y * (2.0 - b * y));
+  } else {
+    return a / b;
+  }
+}
+
 // forward FFT along z, multiply by x0 / (E0 + hb2m |k|^2), inverse along z.
 // The line's x and y indices are frequency indices at this point.
 //   MODE 0: plain damping.
@@ -677,7 +762,8 @@ k_damp_z(cpx<T>* __restrict__ buf, GridArgs g, DampArgs d, const float* __restri
 #pragma unroll
         for (int s = 0; s < PC_SHELLS; ++s) lpow[s] += (s == sh) ? pw : 0.0;
       } else {
-        double mm = d.x0 / (d.e0 + d.hb2m * kk);
+        // the three inverse transforms' 1/N go into the filter
+        double mm = damp_quotient<T>(d.x0 / (double(N) * N * N), d.e0 + d.hb2m * kk);
         if (MODE == 2) mm *= double(gain[size_t(blockIdx.y) * PC_SHELLS + k_shell(m2, N)]);
         const T m = T(mm);
 #pragma unroll
@@ -775,7 +861,7 @@ k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restric
   int base, stride, a, b;
   line_geom<N, DIR>(L, base, stride, a, b);
   cpx<T>* Y = Ybuf + line * YS;
-  const T kunit = T(g.kunit);
+  const T kun = T(g.kunit * (1.0 / N));
 
   double acc[NS][R1];
 #pragma unroll
@@ -801,7 +887,7 @@ k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restric
   cpx<T> vn[2][R1];
   if (s0 < s1 && j < R2) load_line(s0, vn);
   for (int fs = s0; fs < s1; ++fs) {
-    const T kshift = T(grp.kshift[fs / nstate][DIR]);
+    const T ksn = T(grp.kshift[fs / nstate][DIR] * (1.0 / N));
     cpx<T> v[2][R1], d[2][R1];
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
@@ -809,7 +895,7 @@ k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restric
       v[1][j1] = d[1][j1] = vn[1][j1];
     }
     if (fs + 1 < s1 && j < R2) load_line(fs + 1, vn);
-    F::deriv(d, Y, j, tw, kunit, kshift);
+    F::deriv(d, Y, j, tw, kun, ksn);
     if (j < R2) {
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1) {
@@ -918,31 +1004,38 @@ template <int N> static constexpr bool lines_ok(int lp, int bytes_per_cpx) {
          lp * (2 * Fact<N>::R1 * (Fact<N>::R2 + 1) + 1) * bytes_per_cpx <= 96 * 1024;
 }
 
+// Partial sums the last pass forms (each may be null).
+struct HParts {
+  double *eps, *nrm;
+  unsigned int* amax;
+};
+
 template <typename T, int N, int LP>
 static void launch_h_lp(const void* psi, void* hpsi, int nstate, MeanFieldPtrs mf, GridArgs g,
-                        double* eps_part, unsigned int* amax, hipStream_t st) {
+                        HParts pt, hipStream_t st) {
   dim3 grid(N * N / LineCfg<N, LP>::LPW, nstate), block(LineCfg<N, LP>::THREADS);
   auto p = reinterpret_cast<const cpx<T>*>(psi);
   auto h = reinterpret_cast<cpx<T>*>(hpsi);
   hipLaunchKernelGGL((k_h_pass<T, N, 0, true, false, LP>), grid, block, 0, st, p, h, mf, g, nullptr,
-                     nullptr, g_launch_gate);
+                     nullptr, nullptr, g_launch_gate);
   hipLaunchKernelGGL((k_h_pass<T, N, 1, false, false, LP>), grid, block, 0, st, p, h, mf, g, nullptr,
-                     nullptr, g_launch_gate);
-  hipLaunchKernelGGL((k_h_pass<T, N, 2, false, true, LP>), grid, block, 0, st, p, h, mf, g, eps_part,
-                     amax, g_launch_gate);
+                     nullptr, nullptr, g_launch_gate);
+  hipLaunchKernelGGL((k_h_pass<T, N, 2, false, true, LP>), grid, block, 0, st, p, h, mf, g, pt.eps,
+                     pt.nrm, pt.amax, g_launch_gate);
 }
 
 // z pass (with U psi) by line pencils, then the x and y parts on LDS slices.
 template <typename T, int N>
 static void launch_h_plane(const void* psi, void* hpsi, int nstate, MeanFieldPtrs mf, GridArgs g,
-                           double* eps_part, unsigned int* amax, hipStream_t st) {
+                           HParts pt, hipStream_t st) {
   constexpr int D = LineCfg<N>::LPW;
   auto p = reinterpret_cast<const cpx<T>*>(psi);
   auto h = reinterpret_cast<cpx<T>*>(hpsi);
   hipLaunchKernelGGL((k_h_pass<T, N, 2, true, false, D>), dim3(N * N / D, nstate),
-                     dim3(LineCfg<N>::THREADS), 0, st, p, h, mf, g, nullptr, nullptr, g_launch_gate);
+                     dim3(LineCfg<N>::THREADS), 0, st, p, h, mf, g, nullptr, nullptr, nullptr,
+                     g_launch_gate);
   hipLaunchKernelGGL((k_h_plane<T, N>), dim3(N, nstate), dim3(PlaneCfg<N>::THREADS), 0, st, p, h,
-                     mf, g, eps_part, amax, g_launch_gate);
+                     mf, g, pt.eps, pt.nrm, pt.amax, g_launch_gate);
 }
 
 // lines: 0 = default, H_PLANE = x and y on LDS slices, else pencils per
@@ -950,7 +1043,7 @@ static void launch_h_plane(const void* psi, void* hpsi, int nstate, MeanFieldPtr
 // eps partials (workgroups) per state, or 0 if lines is not supported.
 template <typename T, int N>
 static int launch_apply_h(const void* psi, void* hpsi, int nstate, MeanFieldPtrs mf, GridArgs g,
-                          double* eps_part, int lines, unsigned int* amax, hipStream_t st) {
+                          HParts pt, int lines, hipStream_t st) {
   constexpr int D = LineCfg<N>::LPW;
   constexpr int H = (D / 2 > 0 && lines_ok<N>(D / 2, sizeof(cpx<T>))) ? D / 2 : D;
   constexpr int W = lines_ok<N>(2 * D, sizeof(cpx<T>)) ? 2 * D : D;
@@ -958,14 +1051,14 @@ static int launch_apply_h(const void* psi, void* hpsi, int nstate, MeanFieldPtrs
   if (lines == 0) lines = plane_default<T, N>() ? H_PLANE : D;
   if (lines == H_PLANE) {
     if constexpr (PL) {
-      launch_h_plane<T, N>(psi, hpsi, nstate, mf, g, eps_part, amax, st);
+      launch_h_plane<T, N>(psi, hpsi, nstate, mf, g, pt, st);
       return N;
     }
     return 0;
   }
-  if (lines == D) { launch_h_lp<T, N, D>(psi, hpsi, nstate, mf, g, eps_part, amax, st); return N * N / D; }
-  if (lines == H) { launch_h_lp<T, N, H>(psi, hpsi, nstate, mf, g, eps_part, amax, st); return N * N / H; }
-  if (lines == W) { launch_h_lp<T, N, W>(psi, hpsi, nstate, mf, g, eps_part, amax, st); return N * N / W; }
+  if (lines == D) { launch_h_lp<T, N, D>(psi, hpsi, nstate, mf, g, pt, st); return N * N / D; }
+  if (lines == H) { launch_h_lp<T, N, H>(psi, hpsi, nstate, mf, g, pt, st); return N * N / H; }
+  if (lines == W) { launch_h_lp<T, N, W>(psi, hpsi, nstate, mf, g, pt, st); return N * N / W; }
   return 0;
 }
 
@@ -1018,15 +1111,15 @@ int h_pass_default(int n, int prec) {
 
 int apply_h(int n, int prec, const void* psi, void* hpsi, int nstate, MeanFieldPtrs mf,
             GridArgs g, double* eps_part, double* eps, hipStream_t st, int lines,
-            unsigned int* amax) {
+            unsigned int* amax, double* nrm) {
   if (nstate <= 0) return 1;
   int nt = 0;
-  if (prec == 0) SKY_DISPATCH_N(n, nt = (launch_apply_h<double, NN>(psi, hpsi, nstate, mf, g, eps_part, lines, amax, st)))
-  else SKY_DISPATCH_N(n, nt = (launch_apply_h<float, NN>(psi, hpsi, nstate, mf, g, eps_part, lines, amax, st)))
+  double* np = nrm ? eps_part + size_t(nstate) * grid_ntiles(n) : nullptr;
+  const HParts pt{eps ? eps_part : nullptr, np, amax};
+  if (prec == 0) SKY_DISPATCH_N(n, nt = (launch_apply_h<double, NN>(psi, hpsi, nstate, mf, g, pt, lines, st)))
+  else SKY_DISPATCH_N(n, nt = (launch_apply_h<float, NN>(psi, hpsi, nstate, mf, g, pt, lines, st)))
   if (nt == 0) return 0;
-  if (eps_part && eps)
-    hipLaunchKernelGGL(k_sum_partials, dim3((nstate + 127) / 128), dim3(128), 0, st,
-                       (const double*)eps_part, nt, nstate, eps, g_launch_gate);
+  if (eps_part && eps) sum_partials(eps_part, np, nt, nstate, eps, nrm, st);
   return 1;
 }
 
@@ -1082,9 +1175,7 @@ void damped_step(int n, int prec, const void* psi, const void* hpsi, const doubl
     SKY_DISPATCH_N(n, nt = (damp_slices_fit<double, NN>() && (xy < 0 ? damp_slice_default<double, NN>() : xy != 0)) ? NN : ntiles<NN>())
   else
     SKY_DISPATCH_N(n, nt = (damp_slices_fit<float, NN>() && (xy < 0 ? damp_slice_default<float, NN>() : xy != 0)) ? NN : ntiles<NN>())
-  if (r2)
-    hipLaunchKernelGGL(k_sum_partials, dim3((nstate + 127) / 128), dim3(128), 0, st,
-                       (const double*)r2_part, nt, nstate, r2, g_launch_gate);
+  if (r2) sum_partials(r2_part, nullptr, nt, nstate, r2, nullptr, st);
 }
 
 template <typename T, int N>

@@ -92,6 +92,7 @@ struct Layout {
       pc_gain, pc_dscr, pc_gram, pc_idx, pc_beps, pc_b[4], pc_gpart;
   int pc_nb;   // largest sampled-state batch (states x shells)
   size_t plA, plB, plT, plU, plS;                  // FP16 split planes, scales (mixed only)
+  size_t sdiag;   // FP64 diagonals of I and H (mixed only, 2 x the most states of a set)
   size_t dens[2], der[2], mf[2], mf32[2], vc, fscratch, dens_part, epart, energy, info;
   size_t gflags, gdbl;   // flags and doubles of the device-decided iteration
   size_t total;
@@ -141,7 +142,8 @@ Layout plan(const sky_box_desc& d) {
   L.gauge = take(sizeof(int) * 3 * size_t(nmax));
   const int ntile = grid_ntiles(d.n);
   L.pc_nb = std::min(precond_ns_max(), nmax) * PC_SHELLS;
-  L.tiles = take(sizeof(double) * size_t(std::max(nmax, L.pc_nb)) * ntile);
+  // the mixed form sums two quantities per state in one pass
+  L.tiles = take(sizeof(double) * size_t(std::max(nmax, L.pc_nb)) * ntile * (mixed ? 2 : 1));
   const size_t mm = size_t(nmax) * nmax * c16;
   L.matI = take(mm);
   L.matH = take(mm);
@@ -164,6 +166,7 @@ Layout plan(const sky_box_desc& d) {
   L.plB = take(mixed ? planes_bytes_nt(nmax, long(V)) : 0);
   L.plT = take(mixed ? planes_bytes_t(nmax, long(V)) : 0);
   L.plU = take(mixed ? planes_bytes_t(nmax, nmax) : 0);
+  L.sdiag = take(mixed ? sizeof(double) * 2 * nmax : 0);
   L.plS = take(sizeof(unsigned int) * 4);   // largest |component| of phi, h phi, U
   L.chol_work = take(size_t((nmax + 63) / 64 + 1) * 64 * 64 * c16);
   L.jac_work = take(jacobi_scratch_bytes(nmax));
@@ -325,6 +328,9 @@ struct sky_ctx {
   char* phi(int s) const { return at(prec ? lay.phi32[s & 1] : lay.phi[s & 1]); }
   char* hphi(int s) const { return at(prec ? lay.hphi32[s & 1] : lay.hphi[s & 1]); }
   int m_of(int s) const { return nq[s & 1]; }
+  // diagonals of I and H of the set in flight (mixed)
+  double* diagI() const { return at<double>(lay.sdiag); }
+  double* diagH() const { return at<double>(lay.sdiag) + std::max(nq[0], nq[1]); }
   // mean field of the species of set s (shared by every twist)
   MeanFieldPtrs mfp(int s) const {
     const double* m = at<double>(lay.mf[s & 1]);
@@ -406,10 +412,10 @@ void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
   unsigned int* mx = c->at<unsigned int>(c->lay.plS);
   if (c->prec) {
     const int tp = t_begin(c, SKY_PHASE_SPLIT, q);
-    const size_t ne = size_t(m) * c->V;
-    if (!scales_ready) {   // else the producers of phi and h phi merged them
-      plane_scale(phi, 0, ne, mx, st);
-      plane_scale(hphi, 0, ne, mx + 1, st);
+    if (!scales_ready) {   // else the producers of phi and h phi formed them
+      clear_scales(mx, 2, st);
+      state_dots(phi, hphi, c->n, m, c->g.dV, c->at<double>(c->lay.tiles), c->diagH(), c->diagI(),
+                 mx, st);
     }
     split_planes_both(phi, m, c->V, mx, c->at(c->lay.plA), c->at(c->lay.plT), st);
     split_planes_nt(hphi, m, c->V, mx + 1, c->at(c->lay.plB), st);
@@ -425,7 +431,8 @@ void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
   if (c->prec)
     overlap_lower_planes(c->at(c->lay.plA), c->at(c->lay.plA), c->at(c->lay.plB), mx, mx, mx + 1,
                          m, c->V, c->g.dV, I, H, c->at(c->lay.gemm_part), st,
-                         c->timing ? ev : nullptr, c->tune.ovl[q], waves_of(c->tune.ovw[q]));
+                         c->timing ? ev : nullptr, c->tune.ovl[q], waves_of(c->tune.ovw[q]),
+                         c->diagI(), c->diagH());
   else
     overlap_lower(phi, phi, hphi, m, c->V, c->g.dV, I, H, c->at(c->lay.gemm_part), st,
                   c->timing ? ev : nullptr, c->tune.ovl[q]);
@@ -740,11 +747,13 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   hipMemsetAsync(info, 0, sizeof(int), st);
   unsigned int* mx = c->at<unsigned int>(c->lay.plS);
   if (c->prec) {
-    plane_scale(phi, 0, size_t(m) * c->V, mx, st);
+    clear_scales(mx, 1, st);
+    state_dots(phi, nullptr, c->n, m, c->g.dV, c->at<double>(c->lay.tiles), nullptr, c->diagI(), mx,
+               st);
     split_planes_both(phi, m, c->V, mx, c->at(c->lay.plA), c->at(c->lay.plT), st);
     overlap_lower_planes(c->at(c->lay.plA), c->at(c->lay.plA), nullptr, mx, mx, nullptr, m,
                          c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st, nullptr,
-                         c->tune.ovl[q]);
+                         c->tune.ovl[q], 8, c->diagI());
   } else
     overlap_lower(phi, phi, nullptr, m, c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st,
                   nullptr, c->tune.ovl[q]);
@@ -916,7 +925,8 @@ void step_a(sky_ctx* c, int s, bool learned, bool lagged) {
   double* eps = c->at<double>(c->lay.eps[s]);
   double* tiles = c->at<double>(c->lay.tiles);
   // mixed: the largest |component| of phi and h phi (split-plane scales) is
-  // merged by the kernels that write them
+  // merged by the kernels that write them, and the diagonals of I and H are
+  // summed by the last pass of h phi
   unsigned int* mx = c->prec ? c->at<unsigned int>(c->lay.plS) : nullptr;
   if (mx) clear_scales(mx, 2, st);
   if (lagged) {
@@ -935,8 +945,9 @@ void step_a(sky_ctx* c, int s, bool learned, bool lagged) {
                 tiles, c->at<double>(c->lay.r2[s]), st, nullptr, nullptr, 0, c->tune.damp_xy, mx);
   t_end(c, t1);
   int t2 = t_begin(c, SKY_PHASE_APPLY_H, q);
-  apply_h(c->n, c->prec, phi, hphi, m, c->mfp(s), gs, nullptr, nullptr, st, c->tune.lines,
-          mx ? mx + 1 : nullptr);
+  apply_h(c->n, c->prec, phi, hphi, m, c->mfp(s), gs, mx ? tiles : nullptr,
+          mx ? c->diagH() : nullptr, st, c->tune.lines, mx ? mx + 1 : nullptr,
+          mx ? c->diagI() : nullptr);
   t_end(c, t2);
   subspace_matrices(c, s, phi, hphi, mx != nullptr);
 }

@@ -56,11 +56,18 @@ int h_pass_lines(int n, int prec, int* out);
 int h_pass_default(int n, int prec);
 // 1 if the damped step has the LDS-slice variant on this grid and precision.
 int damp_slices_available(int n, int prec);
-// amax (optional): the largest |component| of h psi is merged into it (float
-// bits; clear it first), as plane_scale would compute it.
+// eps_part, eps (both or neither): Re <psi|h psi> per state.  amax (optional):
+// the largest |component| of h psi is merged into it (float bits; clear it
+// first), as plane_scale would compute it.  nrm (optional, with eps): <psi|psi>
+// per state; its partials follow those of eps (eps_part of twice the size).
 int apply_h(int n, int prec, const void* psi, void* hpsi, int nstate, MeanFieldPtrs mf,
             GridArgs g, double* eps_part, double* eps, hipStream_t st, int lines = 0,
-            unsigned int* amax = nullptr);
+            unsigned int* amax = nullptr, double* nrm = nullptr);
+// complex64 states a, b (b may be null): dot = Re <a|b>, nrm = <a|a> per state,
+// and the largest |component| of a and b merged into mx[0], mx[1] (clear them
+// first).  part: twice the partials of nstate states (grid_ntiles each).
+void state_dots(const void* a, const void* b, int n, int nstate, double dV, double* part,
+                double* dot, double* nrm, unsigned int* mx, hipStream_t st);
 // gain (optional, [state][PC_SHELLS]): multiplies the damping per |k| shell.
 // shell_pow (optional, [state][PC_SHELLS], accumulated: clear first): the
 // residual's spectral power per shell, from an extra read-only pass.
@@ -190,12 +197,15 @@ void split_planes_both(const void* x, int rows, long k, const unsigned int* mx, 
 // C0 = scale * conj(A) B0^T (and C1 with B1) from NT planes: the lower
 // triangle, mirrored to the upper one.
 // split_req > 0 overrides the split-K factor (one of overlap_split_candidates_mixed).
+// diag0, diag1 (optional): the diagonals of C0 and C1, formed from the complex64
+// operands in FP64, in place of the planes' ones.
 int overlap_split_candidates_mixed(int m, long k, int* out);
 void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
                           const unsigned int* mxA, const unsigned int* mxB0,
                           const unsigned int* mxB1, int m, long k, double scale, void* C0,
                           void* C1, void* part, hipStream_t st, hipEvent_t* ev = nullptr,
-                          int split_req = 0, int waves = 8);
+                          int split_req = 0, int waves = 8, const double* diag0 = nullptr,
+                          const double* diag1 = nullptr);
 // Y[b][v] = sum_a U[a][b] X[a][v] from the transposed planes of U (m x m)
 // and of X (m x k).  waves, for both plane products: 8 (32 x 64 per wave)
 // or 4 (64 x 64 per wave) per 128 x 128 output tile; both load their tiles

@@ -42,7 +42,8 @@ def test_overlap_and_h_matrices(m, precision):
         ref = f.conj() @ right.T
         low = np.tril_indices(m)
         assert np.abs(got[low] - ref[low])[low[0] != low[1]].max(initial=0.0) <= tol
-        assert np.abs(np.diag(got).real - np.diag(ref).real).max() <= tol
+        # diagonals are summed in FP64 from the states in both forms
+        assert np.abs(np.diag(got).real - np.diag(ref).real).max() <= 1024 * 2.0 ** -53
         assert np.array_equal(got, got.conj().T)
 
 
