@@ -318,7 +318,7 @@ typedef struct {
                              /* and x, y together on LDS z-slices               */
   int32_t damp_xy;           /* damped step: 1 = x and y transforms on LDS       */
                              /* z-slices (where they fit), 0 = line passes,     */
-                             /* -1 = the default (slices up to 32^3)            */
+                             /* -1 = the default (slices where they fit)        */
   int32_t overlap_split[2];  /* split-K factor of the I/H product per species    */
   int32_t square_split[2];   /* split-K factor of the subspace products          */
   int32_t from_cache;        /* 1: every shape came from the cache file          */

@@ -119,9 +119,30 @@ template <int N, int LP = 0> struct LineCfg {
   static_assert(THREADS <= 1024, "workgroup too large");
 };
 
+// Orders a line's LDS writes before its threads' reads: a workgroup barrier, or,
+// where the threads of every line belong to one wave (WL), only the order of
+// that wave's own LDS operations.
+template <bool WL> __device__ inline void line_barrier() {
+  if (WL) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
 // FFT of S spinor components along one line, S in {1, 2}.
 // Y is the line's LDS exchange buffer of YSIZE complex values.
-template <typename T, int N, int S> struct LineFFT {
+//
+// Each direction holds one barrier, between the writes of its first stage and
+// the reads of its second.  None is needed around it: the second stage of
+// forward reads the row (s, j) that the first of inverse, in the same thread,
+// writes, and the second of inverse reads the column j that the first of
+// forward writes, so transforms with the same (line, j) -> thread map may
+// follow each other.  A caller that uses Y otherwise, or with another map,
+// separates the uses itself.  WL: the lines are wave-local (line_barrier).
+template <typename T, int N, int S, bool WL = false> struct LineFFT {
   static constexpr int R1 = Fact<N>::R1, R2 = Fact<N>::R2;
   static constexpr int YROW = R2 + 1;                 // padded row
   static constexpr int YSIZE = S * R1 * YROW + 1;     // odd stride between lines
@@ -138,7 +159,7 @@ template <typename T, int N, int S> struct LineFFT {
           Y[(s * R1 + k1) * YROW + j] = k1 ? va[s][k1] * twN[j * k1] : va[s][k1];
       }
     }
-    __syncthreads();
+    line_barrier<WL>();
     if (j < R1) {
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -147,7 +168,6 @@ template <typename T, int N, int S> struct LineFFT {
         DFT<T, R2, false>::run(vb[s]);
       }
     }
-    __syncthreads();
   }
 
   // vb[s][k2] at frequencies j + R1*k2  ->  va[s][j1] at positions j + R2*j1
@@ -162,7 +182,7 @@ template <typename T, int N, int S> struct LineFFT {
           Y[(s * R1 + j) * YROW + j2] = j2 ? vb[s][j2] * conj(twN[j2 * j]) : vb[s][j2];
       }
     }
-    __syncthreads();
+    line_barrier<WL>();
     if (j < R2) {
 #pragma unroll
       for (int s = 0; s < S; ++s) {
@@ -171,7 +191,6 @@ template <typename T, int N, int S> struct LineFFT {
         DFT<T, R1, true>::run(va[s]);
       }
     }
-    __syncthreads();
   }
 
   // In-place spectral derivative i*(k + kshift) along the line, Nyquist kept
@@ -194,6 +213,9 @@ template <typename T, int N, int S> struct LineFFT {
     inverse(vb, va, Y, j, twN);
   }
 };
+
+// Whether the threads of an x line (consecutive, RT of them) share a wave.
+template <int N> constexpr bool x_wave_local() { return 64 % LineCfg<N>::RT == 0; }
 
 // Distance in LDS between the exchange buffers of consecutive lines of a
 // workgroup (complex values).  Along y and z consecutive lanes hold

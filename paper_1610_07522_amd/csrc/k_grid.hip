@@ -88,6 +88,16 @@ template <typename T> __device__ inline float cabs_max(cpx<T> z) {
   return fmaxf(fabsf(float(z.re)), fabsf(float(z.im)));
 }
 
+// A pointer the compiler takes as new: loads through it are not merged with
+// earlier ones (whose values would stay in registers across the transforms).
+// The complex64 kernels read psi anew (from the L2) where the local terms need
+// it: 24 registers fewer at 48^3, a wave more per SIMD.  In complex128 the line
+// passes are no faster with it (48^3, 100 states: 592 us with, 570 without).
+template <typename P> __device__ inline P* reread(P* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // ------------------------------------------------------------------ h * psi
 // One pass adds the DIR part of h:
 //   - D(B D psi) + (i/2) [A D psi + D(A psi)]  =  D g + (i/2) A D psi,
@@ -101,7 +111,7 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
          unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N, LP>;
-  using F = LineFFT<T, N, 2>;
+  using F = LineFFT<T, N, 2, DIR == 0 && x_wave_local<N>()>;
   constexpr int YS = line_stride<T, N, 2, DIR>();
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   __shared__ cpx<T> tw[N];
@@ -119,15 +129,13 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   cpx<T>* Y = Ybuf + line * YS;
   const T kun = T(g.kunit * (1.0 / N)), ksn = T(g.tw[DIR] * (1.0 / N));
 
-  cpx<T> v[2][R1], d[2][R1];
+  cpx<T> d[2][R1];
   if (j < R2) {
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
-      v[0][j1] = p[r];
-      v[1][j1] = p[N3 + r];
-      d[0][j1] = v[0][j1];
-      d[1][j1] = v[1][j1];
+      d[0][j1] = p[r];
+      d[1][j1] = p[N3 + r];
     }
   }
   load_twiddles<T, N>(tw);
@@ -136,14 +144,16 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   // g (into d) and the accumulated local terms (into acc)
   cpx<T> acc[2][R1];
   if (j < R2) {
+    const cpx<T>* q = sizeof(T) == 4 ? reread(p) : p;
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
-      h_local<T, N, DIR>(mf, r, v[0][j1], v[1][j1], d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
+      const cpx<T> vu = q[r], vd = q[N3 + r];
+      h_local<T, N, DIR>(mf, r, vu, vd, d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
       if (FIRST) {
         const T U = fld_U<T>(mf, r);
-        acc[0][j1] = acc[0][j1] + U * v[0][j1];
-        acc[1][j1] = acc[1][j1] + U * v[1][j1];
+        acc[0][j1] = acc[0][j1] + U * vu;
+        acc[1][j1] = acc[1][j1] + U * vd;
       }
     }
   }
@@ -160,11 +170,22 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
         cpx<T> t = acc[s][j1] + d[s][j1];
         if (!FIRST) t = t + hp[s * N3 + r];
         hp[s * N3 + r] = t;
-        if (LAST && eps_part != nullptr)
-          dot += double(v[s][j1].re) * double(t.re) + double(v[s][j1].im) * double(t.im);
-        if (LAST && nrm_part != nullptr)
-          nrm += double(v[s][j1].re) * double(v[s][j1].re) + double(v[s][j1].im) * double(v[s][j1].im);
-        if (LAST) am = fmaxf(am, cabs_max(t));
+        if (LAST) {
+          acc[s][j1] = t;
+          am = fmaxf(am, cabs_max(t));
+        }
+      }
+    }
+    if (LAST && (eps_part != nullptr || nrm_part != nullptr)) {
+      const cpx<T>* q = sizeof(T) == 4 ? reread(p) : p;
+#pragma unroll
+      for (int j1 = 0; j1 < R1; ++j1) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const cpx<T> v = q[s * N3 + base + (j + R2 * j1) * stride], t = acc[s][j1];
+          dot += double(v.re) * double(t.re) + double(v.im) * double(t.im);
+          nrm += double(v.re) * double(v.re) + double(v.im) * double(v.im);
+        }
       }
     }
   }
@@ -250,12 +271,10 @@ void state_dots(const void* a, const void* b, int n, int nstate, double dV, doub
 }
 
 // ------------------------------------------------------------------ xy planes
-// One workgroup holds a z-slice of one state (both spin components, N x N
-// points, rows padded to N + 1) in LDS and runs the x lines (rows) and the y
-// lines (columns) of a pass on it, so that x and y cost one read and one
-// write of the state instead of two each.  Threads: N lines x RT per line.
-// Used where slice and exchange buffers fit 80 KB of LDS (two workgroups per
-// CU): every grid in complex64 up to 48^3, complex128 up to 32^3.
+// One workgroup takes a z-slice of one state (both spin components, N x N
+// points) through the x lines (rows) and the y lines (columns) of a pass, so
+// that x and y cost one read and one write of the state instead of two each.
+// Threads: N lines x RT per line.  Slices in LDS have rows padded to N + 1.
 template <int N> struct PlaneCfg {
   static constexpr int R1 = Fact<N>::R1, R2 = Fact<N>::R2;
   static constexpr int RT = R1 > R2 ? R1 : R2;
@@ -264,31 +283,33 @@ template <int N> struct PlaneCfg {
   static constexpr int SPIN = N * PITCH;   // one spin component of the slice
 };
 
-template <typename T, int N> constexpr int plane_lds(int xs) {
-  const int ys = LineFFT<T, N, 2>::YSIZE;
-  return (2 * PlaneCfg<N>::SPIN + N * (xs > ys ? xs : ys) + N) * int(sizeof(cpx<T>));
-}
-// Stride of the h slice kernel's x-line buffers: the bank-spreading x stride
-// where the slice still fits 80 KB, else the y lines' stride.
-template <typename T, int N> constexpr int plane_xstride() {
-  return plane_lds<T, N>(line_stride<T, N, 2, 0>()) <= 80 * 1024 ? line_stride<T, N, 2, 0>()
-                                                                 : LineFFT<T, N, 2>::YSIZE;
+// LDS of the h slice kernel: one exchange buffer per line, for the x and the y
+// lines in turn (and for a slice in between).
+template <typename T, int N> constexpr int plane_buf() {
+  const int x = line_stride<T, N, 2, 0>(), y = line_stride<T, N, 2, 1>();
+  return N * (x > y ? x : y);
 }
 template <typename T, int N> constexpr bool plane_fits() {
-  return PlaneCfg<N>::THREADS <= 1024 && plane_lds<T, N>(plane_xstride<T, N>()) <= 80 * 1024;
+  return PlaneCfg<N>::THREADS <= 1024 && (plane_buf<T, N>() + N) * int(sizeof(cpx<T>)) <= 80 * 1024;
+}
+// Waves per SIMD the h slice kernel is compiled for.
+template <typename T, int N> constexpr int plane_waves() {
+  return sizeof(T) == 4 && N == 48 ? 5 : 1;
 }
 // The damped step's slice kernels exchange in place in the slice (no line
-// buffers): half the LDS of the h slices.
+// buffers).  Default wherever they fit: x and y cost one read and one write
+// instead of two.  Measured against the line passes (us): complex64 8^3 x 60
+// 20.8 / 25.3, 16^3 x 100 28.8 / 29.5, 24^3 x 200 78 / 102, 32^3 x 200 138 / 203,
+// 48^3 x 400 1038 / 1578, 64^3 x 150 929 / 1355; complex128 16^3 x 60 28.1 / 29.6,
+// 24^3 x 100 74 / 90, 32^3 x 160 237 / 321, 48^3 x 100 645 / 780.
 template <typename T, int N> constexpr bool damp_slices_fit() {
   return PlaneCfg<N>::THREADS <= 1024 && (2 * PlaneCfg<N>::SPIN + N) * sizeof(cpx<T>) <= 80 * 1024;
 }
-// Default use: measured on MI355X, the slices win up to 32^3 (damped step
-// 16% faster, h psi even or faster); at 48^3 their 80 KB of LDS leaves two
-// workgroups per CU and the line passes are faster.  The tuner decides per box.
-template <typename T, int N> constexpr bool plane_default() { return plane_fits<T, N>() && N <= 32; }
-template <typename T, int N> constexpr bool damp_slice_default() {
-  return damp_slices_fit<T, N>() && N <= 32;
-}
+// The slices are the default wherever they fit.  Measured against the line
+// passes (us, with <h>): complex64 8^3 x 60 12.2 / 14.2, 16^3 x 100 19.7 / 25.9,
+// 24^3 x 200 73 / 88, 32^3 x 200 147 / 173, 48^3 x 400 1125 / 1236, 64^3 x 150
+// 970 / 1050; complex128 16^3 x 60 21.9 / 27.0, 24^3 x 100 76 / 82, 32^3 x 160
+// 241 / 278.  The tuner decides per box.
 
 // Deterministic workgroup sum of one double per thread (any blockDim), using
 // buf[blockDim.x] of LDS; the result is returned to thread 0.
@@ -305,130 +326,139 @@ __device__ inline double tree_sum(double v, double* buf) {
   return buf[0];
 }
 
-// The DIR part of h on one line held by this thread (R1 points at grid
-// offsets r[j1]): D g + (i/2) A D psi with g = -B D psi + (i/2) A psi.
-template <typename T, int N, int DIR>
-__device__ inline void h_dir_line(const cpx<T> (&v)[2][Fact<N>::R1], cpx<T> (&out)[2][Fact<N>::R1],
-                                  const int (&r)[Fact<N>::R1], cpx<T>* Y, int j,
-                                  const cpx<T>* tw, T kun, T ksn, const MeanFieldPtrs& mf) {
-  using F = LineFFT<T, N, 2>;
-  constexpr int R1 = Fact<N>::R1, R2 = Fact<N>::R2;
-  cpx<T> d[2][R1];
-#pragma unroll
-  for (int j1 = 0; j1 < R1; ++j1) {
-    d[0][j1] = v[0][j1];
-    d[1][j1] = v[1][j1];
-  }
-  F::deriv(d, Y, j, tw, kun, ksn);
-  if (j < R2) {
-#pragma unroll
-    for (int j1 = 0; j1 < R1; ++j1)
-      h_local<T, N, DIR>(mf, r[j1], v[0][j1], v[1][j1], d[0][j1], d[1][j1], out[0][j1], out[1][j1]);
-  }
-  F::deriv(d, Y, j, tw, kun, ksn);
-  if (j < R2) {
-#pragma unroll
-    for (int j1 = 0; j1 < R1; ++j1) {
-      out[0][j1] = out[0][j1] + d[0][j1];
-      out[1][j1] = out[1][j1] + d[1][j1];
-    }
-  }
-}
-
 // x and y parts of h psi on slice z = blockIdx.x of state blockIdx.y, added to
-// what hpsi holds (the z part and U psi); partial sums of <psi|h psi>.
+// what hpsi holds (the z part and U psi); partial sums of <psi|h psi> and
+// <psi|psi>.  HBM traffic: psi and h psi read, h psi written (with the z pass
+// five state transfers, against eight by line passes).  Registers decide how
+// many workgroups a CU holds, so nothing is kept that can be had again: psi is
+// read anew (from the L2) where the local terms need it, and the x part goes
+// to the y lines' threads through the exchange buffer, which is all the LDS
+// there is.  At 48^3 complex64 it is compiled for five
+// waves per SIMD (three workgroups per CU): 400 states take 739 us for these
+// two directions (2.9 TB/s; vector issue busy three quarters of the cycles),
+// where the kernel that kept psi in LDS and registers, two workgroups per CU,
+// took 1250 us and the two line passes 900 us.
 template <typename T, int N>
-__global__ void __launch_bounds__(PlaneCfg<N>::THREADS)
+__global__ void __launch_bounds__(PlaneCfg<N>::THREADS, (plane_waves<T, N>()))
 k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtrs mf, GridArgs g,
           double* __restrict__ eps_part, double* __restrict__ nrm_part,
           unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = PlaneCfg<N>;
-  using F = LineFFT<T, N, 2>;
+  using FX = LineFFT<T, N, 2, x_wave_local<N>()>;
+  using FY = LineFFT<T, N, 2>;
   constexpr int R1 = C::R1, R2 = C::R2, RT = C::RT, PITCH = C::PITCH, SP = C::SPIN;
   constexpr int N2 = N * N, N3 = N * N2;
+  constexpr int XS = line_stride<T, N, 2, 0>(), YS = line_stride<T, N, 2, 1>();
+  static_assert(plane_buf<T, N>() >= 2 * SP, "a slice fits the exchange buffers");
   __shared__ cpx<T> tw[N];
-  __shared__ cpx<T> P[2 * SP];
-  constexpr int XS = plane_xstride<T, N>(), YS = F::YSIZE;   // x- and y-line buffers
-  __shared__ cpx<T> Ybuf[N * (XS > YS ? XS : YS)];
+  __shared__ cpx<T> E[plane_buf<T, N>()];
   const int zoff = blockIdx.x * N2;
   const size_t soff = size_t(blockIdx.y) * 2 * N3;
   const cpx<T>* p = psi + soff;
   cpx<T>* hp = hpsi + soff;
-  constexpr int NIT = (2 * N2 + C::THREADS - 1) / C::THREADS;   // unrolled: loads go out together
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int i = threadIdx.x + it * C::THREADS;
-    if (i < 2 * N2) {
-      const int s = i / N2, e = i - s * N2;
-      P[s * SP + (e / N) * PITCH + e % N] = p[s * N3 + zoff + e];
-    }
-  }
-  load_twiddles<T, N>(tw);   // ends with a barrier
   const T kun = T(g.kunit * (1.0 / N));
-  // x lines: row ly, role jx (role fastest: consecutive threads, consecutive x)
-  const int jx = threadIdx.x % RT, ly = threadIdx.x / RT;
-  cpx<T> vx[2][R1], ax[2][R1];
-  int rx[R1];
-#pragma unroll
-  for (int j1 = 0; j1 < R1; ++j1) {
-    const int x = jx + R2 * j1;
-    rx[j1] = zoff + ly * N + x;
+  cpx<T> acc[2][R1], d[2][R1];
+  {  // x lines: row ly, role jx (role fastest: consecutive threads, consecutive x)
+    const int jx = threadIdx.x % RT, ly = threadIdx.x / RT;
+    const int r0 = zoff + ly * N + jx;
     if (jx < R2) {
-      vx[0][j1] = P[ly * PITCH + x];
-      vx[1][j1] = P[SP + ly * PITCH + x];
+#pragma unroll
+      for (int j1 = 0; j1 < R1; ++j1) {
+        d[0][j1] = p[r0 + R2 * j1];
+        d[1][j1] = p[N3 + r0 + R2 * j1];
+      }
+    }
+    load_twiddles<T, N>(tw);
+    FX::deriv(d, E + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)));
+    if (jx < R2) {
+      const cpx<T>* q = reread(p);
+#pragma unroll
+      for (int j1 = 0; j1 < R1; ++j1) {
+        const int r = r0 + R2 * j1;
+        h_local<T, N, 0>(mf, r, q[r], q[N3 + r], d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
+      }
+    }
+    FX::deriv(d, E + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)));
+    __syncthreads();   // every x line is done with its buffer
+    if (jx < R2) {
+#pragma unroll
+      for (int j1 = 0; j1 < R1; ++j1) {
+        const int e = ly * PITCH + jx + R2 * j1;
+        E[e] = acc[0][j1] + d[0][j1];
+        E[SP + e] = acc[1][j1] + d[1][j1];
+      }
     }
   }
-  h_dir_line<T, N, 0>(vx, ax, rx, Ybuf + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)), mf);
   // y lines: column lx (line fastest: consecutive threads, consecutive x)
   const int lx = threadIdx.x % N, jy = threadIdx.x / N;
-  cpx<T> vy[2][R1], ay[2][R1];
-  int ry[R1];
-#pragma unroll
-  for (int j1 = 0; j1 < R1; ++j1) {
-    const int y = jy + R2 * j1;
-    ry[j1] = zoff + y * N + lx;
-    if (jy < R2) {
-      vy[0][j1] = P[y * PITCH + lx];
-      vy[1][j1] = P[SP + y * PITCH + lx];
-    }
-  }
-  __syncthreads();
-  if (jx < R2) {
+  const int r0 = zoff + jy * N + lx;
+  if (jy < R2) {
+    const cpx<T>* q = reread(p);
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
-      P[ly * PITCH + jx + R2 * j1] = ax[0][j1];
-      P[SP + ly * PITCH + jx + R2 * j1] = ax[1][j1];
+      d[0][j1] = q[r0 + R2 * j1 * N];
+      d[1][j1] = q[N3 + r0 + R2 * j1 * N];
     }
   }
   __syncthreads();
-  h_dir_line<T, N, 1>(vy, ay, ry, Ybuf + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)), mf);
+  if (jy < R2) {
+#pragma unroll
+    for (int j1 = 0; j1 < R1; ++j1) {
+      const int e = (jy + R2 * j1) * PITCH + lx;
+      acc[0][j1] = E[e];
+      acc[1][j1] = E[SP + e];
+    }
+  }
+  __syncthreads();
+  FY::deriv(d, E + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)));
+  if (jy < R2) {
+    const cpx<T>* q = reread(p);
+#pragma unroll
+    for (int j1 = 0; j1 < R1; ++j1) {
+      const int r = r0 + R2 * j1 * N;
+      cpx<T> au, ad;
+      h_local<T, N, 1>(mf, r, q[r], q[N3 + r], d[0][j1], d[1][j1], au, ad);
+      acc[0][j1] = acc[0][j1] + au;
+      acc[1][j1] = acc[1][j1] + ad;
+    }
+  }
+  FY::deriv(d, E + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)));
   double dot = 0.0, nrm = 0.0;
   float am = 0.0f;
   if (jy < R2) {
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
-      const int y = jy + R2 * j1;
+      const int r = r0 + R2 * j1 * N;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        const cpx<T> t = ay[s][j1] + P[s * SP + y * PITCH + lx] + hp[s * N3 + ry[j1]];
-        hp[s * N3 + ry[j1]] = t;
-        if (eps_part != nullptr)
-          dot += double(vy[s][j1].re) * double(t.re) + double(vy[s][j1].im) * double(t.im);
-        if (nrm_part != nullptr)
-          nrm += double(vy[s][j1].re) * double(vy[s][j1].re) + double(vy[s][j1].im) * double(vy[s][j1].im);
+        const cpx<T> t = acc[s][j1] + d[s][j1] + hp[s * N3 + r];
+        hp[s * N3 + r] = t;
+        acc[s][j1] = t;
         am = fmaxf(am, cabs_max(t));
       }
     }
+    if (eps_part != nullptr || nrm_part != nullptr) {
+      const cpx<T>* q = reread(p);
+#pragma unroll
+      for (int j1 = 0; j1 < R1; ++j1) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const cpx<T> v = q[s * N3 + r0 + R2 * j1 * N], t = acc[s][j1];
+          dot += double(v.re) * double(t.re) + double(v.im) * double(t.im);
+          nrm += double(v.re) * double(v.re) + double(v.im) * double(v.im);
+        }
+      }
+    }
   }
-  if (eps_part != nullptr) {
-    __syncthreads();   // P is free again: reuse it for the reduction
-    const double sum = tree_sum(dot, reinterpret_cast<double*>(P));
+  if (eps_part != nullptr) {   // E again for the reductions
+    __syncthreads();
+    const double sum = tree_sum(dot, reinterpret_cast<double*>(E));
     if (threadIdx.x == 0) eps_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
   if (nrm_part != nullptr) {
     __syncthreads();
-    const double sum = tree_sum(nrm, reinterpret_cast<double*>(P));
+    const double sum = tree_sum(nrm, reinterpret_cast<double*>(E));
     if (threadIdx.x == 0) nrm_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
   if (amax != nullptr) block_amax(am, amax);
@@ -602,7 +632,7 @@ k_damp_fwd_x(const cpx<T>* __restrict__ psi, const cpx<T>* __restrict__ hpsi,
              double* __restrict__ r2_part, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N>;
-  using F = LineFFT<T, N, 2>;
+  using F = LineFFT<T, N, 2, x_wave_local<N>()>;
   constexpr int YS = line_stride<T, N, 2, 0>();
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   __shared__ cpx<T> tw[N];
@@ -800,7 +830,7 @@ k_damp_inv_x(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ buf,
              unsigned int* __restrict__ amax, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N>;
-  using F = LineFFT<T, N, 2>;
+  using F = LineFFT<T, N, 2, x_wave_local<N>()>;
   constexpr int YS = line_stride<T, N, 2, 0>();
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   __shared__ cpx<T> tw[N];
@@ -847,7 +877,7 @@ __global__ void __launch_bounds__(LineCfg<N>::THREADS)
 k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restrict__ part, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N>;
-  using F = LineFFT<T, N, 2>;
+  using F = LineFFT<T, N, 2, DIR == 0 && x_wave_local<N>()>;
   constexpr int YS = line_stride<T, N, 2, DIR>();
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   constexpr int NS = DIR == 0 ? 8 : 4;
@@ -1048,7 +1078,7 @@ static int launch_apply_h(const void* psi, void* hpsi, int nstate, MeanFieldPtrs
   constexpr int H = (D / 2 > 0 && lines_ok<N>(D / 2, sizeof(cpx<T>))) ? D / 2 : D;
   constexpr int W = lines_ok<N>(2 * D, sizeof(cpx<T>)) ? 2 * D : D;
   constexpr bool PL = plane_fits<T, N>();
-  if (lines == 0) lines = plane_default<T, N>() ? H_PLANE : D;
+  if (lines == 0) lines = plane_fits<T, N>() ? H_PLANE : D;
   if (lines == H_PLANE) {
     if constexpr (PL) {
       launch_h_plane<T, N>(psi, hpsi, nstate, mf, g, pt, st);
@@ -1079,7 +1109,7 @@ template <typename T, int N> static int lines_list(int* out) {
 }
 
 template <typename T, int N> static int lines_default() {
-  return plane_default<T, N>() ? H_PLANE : LineCfg<N>::LPW;
+  return plane_fits<T, N>() ? H_PLANE : LineCfg<N>::LPW;
 }
 
 int grid_ntiles(int n) {
@@ -1135,7 +1165,7 @@ static void launch_damp(const void* psi, const void* hpsi, const double* eps, vo
   auto p = reinterpret_cast<const cpx<T>*>(psi);
   auto h = reinterpret_cast<const cpx<T>*>(hpsi);
   auto o = reinterpret_cast<cpx<T>*>(phi);
-  const bool pl = damp_slices_fit<T, N>() && (xy < 0 ? damp_slice_default<T, N>() : xy != 0);
+  const bool pl = damp_slices_fit<T, N>() && xy != 0;
   if (stage != 2) {
     if (pl) {
       if constexpr (damp_slices_fit<T, N>())
@@ -1172,9 +1202,9 @@ void damped_step(int n, int prec, const void* psi, const void* hpsi, const doubl
   if (stage == 2) return;
   int nt = 0;
   if (prec == 0)
-    SKY_DISPATCH_N(n, nt = (damp_slices_fit<double, NN>() && (xy < 0 ? damp_slice_default<double, NN>() : xy != 0)) ? NN : ntiles<NN>())
+    SKY_DISPATCH_N(n, nt = (damp_slices_fit<double, NN>() && xy != 0) ? NN : ntiles<NN>())
   else
-    SKY_DISPATCH_N(n, nt = (damp_slices_fit<float, NN>() && (xy < 0 ? damp_slice_default<float, NN>() : xy != 0)) ? NN : ntiles<NN>())
+    SKY_DISPATCH_N(n, nt = (damp_slices_fit<float, NN>() && xy != 0) ? NN : ntiles<NN>())
   if (r2) sum_partials(r2_part, nullptr, nt, nstate, r2, nullptr, st);
 }
 
