@@ -136,18 +136,6 @@ k_overlap_reduce(const double2* __restrict__ part, int npair, int split, int m, 
   }
 }
 
-__global__ void k_hermitian_fill(double2* __restrict__ C, int m, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int row = blockIdx.y * 16 + threadIdx.y, col = blockIdx.x * 16 + threadIdx.x;
-  if (row >= m || col >= m) return;
-  if (col > row) {
-    double2 v = C[size_t(col) * m + row];
-    C[size_t(row) * m + col] = make_double2(v.x, -v.y);
-  } else if (col == row) {
-    C[size_t(row) * m + col].y = 0.0;
-  }
-}
-
 // ----------------------------------------------------------- combine
 // Y[b][v] = sum_a U[a][b] X[a][v]: M = b (rows of Y), N = v, K = a.
 __global__ void __launch_bounds__(GT)
@@ -199,13 +187,14 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 // ----------------------------------------------------------- square products
 // C = op(A) op(B), op 0 = N, 1 = conjugate transpose; all m x m row-major.
 // With lower, a product known to be Hermitian: only tiles on or below the
-// diagonal are computed, and the caller mirrors the strictly upper part.
+// diagonal are computed; without a split (MIRROR) the strictly upper part is
+// written as the mirror image here, else by k_sum_splits_herm.
 // Grid (column tiles, row tiles, split): workgroup z sums the contraction
 // chunks [nk z / split, nk (z+1) / split) and writes C + z m^2 (split > 1:
 // partials, reduced in order by k_sum_splits).  Each operand is loaded along
 // its contiguous index (op N of B and op H of A read rows of 64 columns), one
 // chunk ahead into registers.
-template <int OPA, int OPB>
+template <int OPA, int OPB, bool MIRROR>
 __global__ void __launch_bounds__(GT)
 k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
               double2* __restrict__ C, int m, int split, int lower, const int* __restrict__ sky_gate) {
@@ -272,7 +261,13 @@ k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
   double2* out = C + size_t(sp) * m * m;
   mfma::foreach(acc, wm, wn, lane, [&](int row, int col, double re, double im) {
     const int r = r0 + row, c = c0 + col;
-    if (r < m && c < m) out[size_t(r) * m + c] = make_double2(re, im);
+    if (r >= m || c >= m) return;
+    if (!MIRROR) {
+      out[size_t(r) * m + c] = make_double2(re, im);
+    } else if (r >= c) {
+      out[size_t(r) * m + c] = make_double2(re, r == c ? 0.0 : im);
+      if (r > c) out[size_t(c) * m + r] = make_double2(re, -im);
+    }
   });
 }
 
@@ -289,6 +284,38 @@ __global__ void k_sum_splits(const double2* __restrict__ part, int split, size_t
     acc.y += v.y;
   }
   C[e] = acc;
+}
+
+// The same for a Hermitian product of which only the lower tiles were computed:
+// 16 x 16 blocks on or below the diagonal, mirrored through LDS (grid over the
+// blocks of the matrix).
+__global__ void __launch_bounds__(256)
+k_sum_splits_herm(const double2* __restrict__ part, int split, int m, double2* __restrict__ C,
+                  const int* __restrict__ sky_gate) {
+  if (sky_gate != nullptr && *sky_gate == 0) return;
+  if (blockIdx.x > blockIdx.y) return;
+  __shared__ double2 T[16][17];
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  const int row0 = blockIdx.y * 16, col0 = blockIdx.x * 16, row = row0 + r, col = col0 + c;
+  const size_t n = size_t(m) * m;
+  if (row < m && col <= row) {
+    const size_t e = size_t(row) * m + col;
+    double2 acc = part[e];
+    for (int s = 1; s < split; ++s) {
+      const double2 v = part[size_t(s) * n + e];
+      acc.x += v.x;
+      acc.y += v.y;
+    }
+    if (row == col) acc.y = 0.0;
+    C[e] = acc;
+    T[r][c] = acc;
+  }
+  __syncthreads();
+  const int mr = col0 + r, mc = row0 + c;
+  if (mc < m && mr < mc) {
+    const double2 v = T[c][r];
+    C[size_t(mr) * m + mc] = make_double2(v.x, -v.y);
+  }
 }
 
 // Contraction splits of the square products: enough workgroups for ~4 per
@@ -361,12 +388,6 @@ void overlap_reduce(const void* part, int npair, int split, int m, double scale,
                      g_launch_gate);
 }
 
-void hermitian_fill(void* C, int m, hipStream_t st) {
-  if (m <= 0) return;
-  dim3 grid((m + 15) / 16, (m + 15) / 16), block(16, 16);
-  hipLaunchKernelGGL(k_hermitian_fill, grid, block, 0, st, (double2*)C, m, g_launch_gate);
-}
-
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st) {
   if (m <= 0) return;
   dim3 grid(unsigned(k / TM), (m + TM - 1) / TM);
@@ -399,16 +420,23 @@ void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m,
   auto a = (const double2*)A;
   auto b = (const double2*)B;
   auto c = (double2*)(split > 1 ? part : C);
-  if (opA == 0 && opB == 0) hipLaunchKernelGGL((k_gemm_square<0, 0>), grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
-  else if (opA == 0 && opB == 1) hipLaunchKernelGGL((k_gemm_square<0, 1>), grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
-  else if (opA == 1 && opB == 0) hipLaunchKernelGGL((k_gemm_square<1, 0>), grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
-  else hipLaunchKernelGGL((k_gemm_square<1, 1>), grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
-  if (split > 1) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
+  };
+  const bool mirror = herm && split == 1;
+  if (opA == 0 && opB == 0) mirror ? launch(k_gemm_square<0, 0, true>) : launch(k_gemm_square<0, 0, false>);
+  else if (opA == 0) mirror ? launch(k_gemm_square<0, 1, true>) : launch(k_gemm_square<0, 1, false>);
+  else if (opB == 0) mirror ? launch(k_gemm_square<1, 0, true>) : launch(k_gemm_square<1, 0, false>);
+  else mirror ? launch(k_gemm_square<1, 1, true>) : launch(k_gemm_square<1, 1, false>);
+  if (split > 1 && herm) {
+    const unsigned nb = unsigned((m + 15) / 16);
+    hipLaunchKernelGGL(k_sum_splits_herm, dim3(nb, nb), dim3(256), 0, st, (const double2*)part, split,
+                       m, (double2*)C, g_launch_gate);
+  } else if (split > 1) {
     const size_t n = size_t(m) * m;
     hipLaunchKernelGGL(k_sum_splits, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st,
                        (const double2*)part, split, n, (double2*)C, g_launch_gate);
   }
-  if (herm) hermitian_fill(C, m, st);
 }
 
 }  // namespace sky

@@ -247,16 +247,20 @@ k_minus_identity(const double2* __restrict__ A, double2* __restrict__ D, int m,
   if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// out[0] = sum of part[0 .. nb): lane t of one wave adds t, t + 64, ... in
+// out[0] (and host[0], host-visible memory, if given) = sum of part[0 .. nb): lane t of one wave adds t, t + 64, ... in
 // order, then a fixed butterfly (a one-thread loop over 256 partials is a
 // serial chain of loads: 18 us; SUMPARTS_US).
-__global__ void k_sum_parts(const double* __restrict__ part, int nb, double* __restrict__ out, const int* __restrict__ sky_gate) {
+__global__ void k_sum_parts(const double* __restrict__ part, int nb, double* __restrict__ out,
+                            double* __restrict__ host, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   double s = 0.0;
   for (int b = threadIdx.x; b < nb; b += 64) s += part[b];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (threadIdx.x == 0) out[0] = s;
+  if (threadIdx.x == 0) {
+    out[0] = s;
+    if (host != nullptr) host[0] = s;
+  }
 }
 
 // P = a D + c 1
@@ -518,7 +522,7 @@ __global__ void k_offnorm_final(const double* __restrict__ part, int nb, double*
     d += __shfl_down(d, k, 64);
   }
   if (threadIdx.x == 0) {
-    out[0] = o;
+    out[0] = o;   // host-visible memory
     out[1] = d;
   }
 }
@@ -648,7 +652,7 @@ size_t jacobi_scratch_bytes(int m) {
 }
 
 int jacobi_eigh(void* Av, int m, double* w, void* Zv, void* work, double tol, int max_sweeps,
-                hipStream_t st) {
+                hipStream_t st, double* host) {
   if (m <= 0) return 0;
   int nb;
   const int mp = jacobi_dims(m, nb);
@@ -674,17 +678,15 @@ int jacobi_eigh(void* Av, int m, double* w, void* Zv, void* work, double tol, in
   hipLaunchKernelGGL(k_jacobi_init, dim3(unsigned((mm + 255) / 256)), dim3(256), 0, st,
                      (const double2*)Av, m, Ap, V, mp, g_launch_gate);
   const int nrb = 256;
-  double host_norm[2];
   int sweeps = 0;
   bool done = false;
   for (; sweeps <= max_sweeps; ++sweeps) {
     hipLaunchKernelGGL(k_offnorm, dim3(nrb), dim3(256), 0, st, (const double2*)Ap, mp, norms, g_launch_gate);
     hipLaunchKernelGGL(k_offnorm_final, dim3(1), dim3(64), 0, st, (const double*)norms, nrb,
-                       norms + 2 * nrb, g_launch_gate);
-    hipMemcpyAsync(host_norm, norms + 2 * nrb, 2 * sizeof(double), hipMemcpyDeviceToHost, st);
-    hipStreamSynchronize(st);
-    if (!std::isfinite(host_norm[0]) || !std::isfinite(host_norm[1])) return -2;
-    if (host_norm[0] <= tol * tol * host_norm[1] || host_norm[0] < 1e-300) { done = true; break; }
+                       host, g_launch_gate);
+    if (hipStreamSynchronize(st) != hipSuccess) return -2;
+    if (!std::isfinite(host[0]) || !std::isfinite(host[1])) return -2;
+    if (host[0] <= tol * tol * host[1] || host[0] < 1e-300) { done = true; break; }
     if (sweeps == max_sweeps) break;   // the norm after the last sweep was checked
     for (int r = 0; r < nb - 1; ++r) {
       const int2* pr = pairs + size_t(r) * np;
@@ -708,17 +710,15 @@ void eig_sort(const void* D, const void* V, int m, int ld, double* w, void* Z, h
 }
 
 int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double max_dev,
-                   double* scratch, void* part, hipStream_t st, int sq_split, double eps) {
+                   double* scratch, void* part, hipStream_t st, double* host, int sq_split, double eps) {
   if (m <= 0) return 0;
   auto D = (double2*)Dv;
   const size_t mm = size_t(m) * m;
   const int nb = int(std::min<size_t>(256, (mm + 255) / 256));
   hipLaunchKernelGGL(k_minus_identity, dim3(nb), dim3(256), 0, st, (const double2*)Iv, D, m, scratch, g_launch_gate);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, (const double*)scratch, nb, scratch + nb, g_launch_gate);
-  double fro2 = 0.0;
-  hipMemcpyAsync(&fro2, scratch + nb, sizeof(double), hipMemcpyDeviceToHost, st);
-  hipStreamSynchronize(st);
-  const double f = sqrt(fro2);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, (const double*)scratch, nb, scratch + nb, host, g_launch_gate);
+  if (hipStreamSynchronize(st) != hipSuccess) return -1;
+  const double f = sqrt(host[0]);
   if (!std::isfinite(f)) return -1;
   if (!(f <= max_dev)) return 0;
   // (1 + D)^-1/2 = sum_k c_k D^k, c_k = c_{k-1} (1 - 2k) / (2k); ||D||_2 <= f, so the
@@ -827,7 +827,7 @@ void loewdin_series_dev(const void* Iv, void* Cv, void* Dv, void* Tv, int m, dou
   {
     GateScope g(active);
     hipLaunchKernelGGL(k_minus_identity, dim3(nb), dim3(256), 0, st, (const double2*)Iv, D, m, scratch, g_launch_gate);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, (const double*)scratch, nb, scratch + nb, g_launch_gate);
+    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, (const double*)scratch, nb, scratch + nb, (double*)nullptr, g_launch_gate);
   }
   // the most terms any accepted norm (f <= max_dev) can need, plus one:
   // Horner steps beyond those are never taken and are not captured

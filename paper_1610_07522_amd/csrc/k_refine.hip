@@ -121,42 +121,56 @@ k_ref_reach(const double2* __restrict__ S, const double2* __restrict__ R, const 
 // cluster list, -1 for singletons).  The list holds (start, size) of every
 // cluster of two to KMAX positions; info[0] = list length, info[1] = widest
 // cluster found.
-// One workgroup of 1024 threads, chunked scans; pm (m ints) holds the
-// prefix maximum.
-__global__ void __launch_bounds__(1024)
+// One workgroup of up to 1024 threads, a chunk of positions each; pm (m ints)
+// holds the prefix maximum.  The chunk maxima are scanned by shuffles (a
+// one-thread scan over 1024 chunks took 27 to 33 us, now CLUSTERS_US).
+constexpr int CL_THREADS = 1024;
+
+// Inclusive maximum over the threads up to this one (buf: one int per wave);
+// *before: over the threads before this one (-1 for the first).
+__device__ inline int scan_max(int v, int* buf, int* before) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(v, o, 64);
+    if (lane >= o) v = max(v, t);
+  }
+  if (lane == 63) buf[wv] = v;
+  __syncthreads();
+  int head = -1;
+  for (int w = 0; w < wv; ++w) head = max(head, buf[w]);
+  __syncthreads();
+  const int prev = __shfl_up(v, 1, 64);
+  *before = lane ? max(prev, head) : head;
+  return max(v, head);
+}
+
+__global__ void __launch_bounds__(CL_THREADS)
 k_ref_clusters(const int* __restrict__ reach, int m, int* __restrict__ pm, int* __restrict__ cstart,
                int* __restrict__ csize, int* __restrict__ cslot, int2* __restrict__ clist,
                int* __restrict__ info, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ int tmax[1024], tcut[1024];
+  __shared__ int buf[CL_THREADS / 64];
   __shared__ int ncl, widest;
   const int t = threadIdx.x, T = blockDim.x;
   const int chunk = (m + T - 1) / T;
   const int a0 = min(m, t * chunk), a1 = min(m, a0 + chunk);
   if (t == 0) { ncl = 0; widest = 1; }
-  // pass 1: chunk prefix max of reach
+  // pass 1: prefix max of reach before each chunk
   int mx = -1;
   for (int a = a0; a < a1; ++a) mx = max(mx, reach[a]);
-  tmax[t] = mx;
-  __syncthreads();
-  if (t == 0)
-    for (int u = 1; u < T; ++u) tmax[u] = max(tmax[u], tmax[u - 1]);
-  __syncthreads();
+  int run;
+  scan_max(mx, buf, &run);
   // pass 2: cuts; last cut before each chunk
-  int run = t ? tmax[t - 1] : -1;
   int lastcut = -1;
   for (int a = a0; a < a1; ++a) {
     run = max(run, reach[a]);
     if (run == a) lastcut = a;
     pm[a] = run;
   }
-  tcut[t] = lastcut;
-  __syncthreads();
-  if (t == 0)
-    for (int u = 1; u < T; ++u) tcut[u] = max(tcut[u], tcut[u - 1]);
-  __syncthreads();
+  int prevcut;
+  scan_max(lastcut, buf, &prevcut);
   // pass 3: start of each position's cluster = last cut before it + 1
-  int prevcut = t ? tcut[t - 1] : -1;
   for (int a = a0; a < a1; ++a) {
     const bool cut = pm[a] == a;
     const int st = prevcut + 1;
@@ -205,14 +219,14 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
   const int k = cs.y;
   if (k > KMAX) return;   // reported through info[1]; the caller falls back
   const int np = (k + 1) & ~1, nh = np / 2;
-  __shared__ double2 M[KMAX][KMAX + 1];
+  __shared__ double2 MP[2][KMAX][KMAX + 1];   // the matrix and its next value, in turn
   __shared__ double2 J[KMAX][KMAX + 1];
-  __shared__ double2 P[KMAX][KMAX + 1];
-  __shared__ Rot rot[KMAX / 2];
-  __shared__ int2 pair[KMAX / 2];   // index pairs of the round
+  double2 (*M)[KMAX + 1] = MP[0];
+  double2 (*P)[KMAX + 1] = MP[1];
+  __shared__ Rot rot[4][KMAX / 2];    // rotations and index pairs of the round, a copy per wave
+  __shared__ int2 pair[4][KMAX / 2];
   __shared__ int idx[KMAX];
   __shared__ double red[4][2];
-  __shared__ int done;
   const int tid = threadIdx.x;
   if (tid < k) idx[tid] = order[cs.x + tid];
   __syncthreads();
@@ -268,48 +282,52 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
     }
     if ((tid & 63) == 0) { red[tid >> 6][0] = off; red[tid >> 6][1] = dia; }
     __syncthreads();
-    if (tid == 0) {
-      const double o = red[0][0] + red[1][0] + red[2][0] + red[3][0];
-      const double d = red[0][1] + red[1][1] + red[2][1] + red[3][1];
-      done = (o <= tol * tol * d) || (o < 1e-300);
-    }
-    __syncthreads();
-    if (done) break;
+    const double o = red[0][0] + red[1][0] + red[2][0] + red[3][0];
+    const double d = red[0][1] + red[1][1] + red[2][1] + red[3][1];
+    if ((o <= tol * tol * d) || (o < 1e-300)) break;   // the same in every thread
     for (int r = 0; r < np - 1; ++r) {
-      if (tid < nh) {
+      // one barrier per round: every wave makes the round's rotations for
+      // itself, and the rotated matrix goes to the other buffer
+      const int wv = tid >> 6, lane = tid & 63;
+      if (lane < nh) {
         int p, q;
-        rr_pair(np, r, tid, p, q);
+        rr_pair(np, r, lane, p, q);
         if (p > q) { const int t = p; p = q; q = t; }
-        pair[tid] = make_int2(p, q);
-        rot[tid] = make_rot(M[p][p].x, M[q][q].x, M[p][q]);
+        pair[wv][lane] = make_int2(p, q);
+        rot[wv][lane] = make_rot_rsq(M[p][p].x, M[q][q].x, M[p][q]);
       }
-      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       // M <- G^H M G on the 2x2 blocks (rotation u rows, rotation v columns)
       for (int e = tid; e < nh * nh; e += blockDim.x) {
         const int u = e / nh, v = e % nh;
-        const int pu = pair[u].x, qu = pair[u].y, pv = pair[v].x, qv = pair[v].y;
-        const Rot gu = rot[u], gv = rot[v];
+        const int pu = pair[wv][u].x, qu = pair[wv][u].y, pv = pair[wv][v].x, qv = pair[wv][v].y;
+        const Rot gu = rot[wv][u], gv = rot[wv][v];
         const double2 epu = make_double2(gu.er, gu.ei), epv = make_double2(gv.er, gv.ei);
         const double2 x00 = M[pu][pv], x01 = M[pu][qv], x10 = M[qu][pv], x11 = M[qu][qv];
         const double2 y00 = csub(cscale(gv.c, cmul(x00, epv)), cscale(gv.s, x01));
         const double2 y01 = cadd(cscale(gv.s, cmul(x00, epv)), cscale(gv.c, x01));
         const double2 y10 = csub(cscale(gv.c, cmul(x10, epv)), cscale(gv.s, x11));
         const double2 y11 = cadd(cscale(gv.s, cmul(x10, epv)), cscale(gv.c, x11));
-        M[pu][pv] = csub(cscale(gu.c, cmulc(y00, epu)), cscale(gu.s, y10));
-        M[pu][qv] = csub(cscale(gu.c, cmulc(y01, epu)), cscale(gu.s, y11));
-        M[qu][pv] = cadd(cscale(gu.s, cmulc(y00, epu)), cscale(gu.c, y10));
-        M[qu][qv] = cadd(cscale(gu.s, cmulc(y01, epu)), cscale(gu.c, y11));
+        P[pu][pv] = csub(cscale(gu.c, cmulc(y00, epu)), cscale(gu.s, y10));
+        P[pu][qv] = csub(cscale(gu.c, cmulc(y01, epu)), cscale(gu.s, y11));
+        P[qu][pv] = cadd(cscale(gu.s, cmulc(y00, epu)), cscale(gu.c, y10));
+        P[qu][qv] = cadd(cscale(gu.s, cmulc(y01, epu)), cscale(gu.c, y11));
       }
       // J <- J G
       for (int e = tid; e < np * nh; e += blockDim.x) {
         const int i = e / nh, v = e % nh;
-        const int pv = pair[v].x, qv = pair[v].y;
-        const Rot gv = rot[v];
+        const int pv = pair[wv][v].x, qv = pair[wv][v].y;
+        const Rot gv = rot[wv][v];
         const double2 epv = make_double2(gv.er, gv.ei);
         const double2 x0 = J[i][pv], x1 = J[i][qv];
         J[i][pv] = csub(cscale(gv.c, cmul(x0, epv)), cscale(gv.s, x1));
         J[i][qv] = cadd(cscale(gv.s, cmul(x0, epv)), cscale(gv.c, x1));
       }
+      double2 (*t)[KMAX + 1] = M;
+      M = P;
+      P = t;
       __syncthreads();
     }
   }
@@ -343,17 +361,32 @@ struct Clusters {
   }
 };
 
-// lam2[a] = Re S2_aa / (1 - Re R2_aa) in the cluster-rotated sorted basis.
-__global__ void k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m,
-                              Clusters cl, double* __restrict__ lam2, const int* __restrict__ sky_gate) {
+// lam2[a] = Re S2_aa / (1 - Re R2_aa) in the cluster-rotated sorted basis.  One
+// wave per a: lane l takes the products l, l + 64, ... of the k x k sum, then a
+// fixed butterfly (one thread per a was bound by the widest cluster's k^2
+// serial loads: 28 us over the uneven boxes and 46 at 1600 states, now 6 and 5).
+__global__ void __launch_bounds__(256)
+k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
+              double* __restrict__ lam2, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+  const int a = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (a >= m) return;
-  const int s0 = cl.cstart[a], k = cl.csize[a];
+  const int s0 = cl.cstart[a], k = cl.csize[a], ta = a - s0;
   const double2* Wa = cl.w(a);
-  const double s2 = sandwich(S, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x;
-  const double r2 = R ? sandwich(R, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x : 0.0;
-  lam2[a] = s2 / (1.0 - r2);
+  double s2 = 0.0, r2 = 0.0;
+  for (int e = lane; e < k * k; e += 64) {
+    const int s = e / k, u = e % k;
+    const size_t at = size_t(cl.order[s0 + s]) * m + cl.order[s0 + u];
+    const double2 w = Wa ? cconjmul(Wa[s * KMAX + ta], Wa[u * KMAX + ta]) : make_double2(1.0, 0.0);
+    s2 += cmul(S[at], w).x;
+    if (R) r2 += cmul(R[at], w).x;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    s2 += __shfl_xor(s2, o);
+    r2 += __shfl_xor(r2, o);
+  }
+  if (lane == 0) lam2[a] = s2 / (1.0 - r2);
 }
 
 // E in the cluster-rotated sorted basis (m x m, row a, column b), and
@@ -627,7 +660,11 @@ __global__ void k_ref_tau(const double* __restrict__ norms, int m, double noise,
 
 // Sums of the check's block partials over 64 lanes (lane t takes blocks
 // t, t + 64, ... in order, then a fixed butterfly), NaN-propagating max.
-__global__ void k_ref_check_final(const double* __restrict__ part, int nb, double* __restrict__ out, const int* __restrict__ sky_gate) {
+// With host (host-visible memory): the norms and the widest cluster of the
+// step, for the host's stop test.
+__global__ void k_ref_check_final(const double* __restrict__ part, int nb, double* __restrict__ out,
+                                  const int* __restrict__ info, double* __restrict__ host,
+                                  const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   const int t = threadIdx.x;
   if (t >= 64) return;
@@ -649,8 +686,17 @@ __global__ void k_ref_check_final(const double* __restrict__ part, int nb, doubl
     out[0] = o;
     out[1] = d;
     out[2] = r;
+    if (host != nullptr) {
+      host[0] = o;
+      host[1] = d;
+      host[2] = r;
+      host[3] = double(info[1]);
+    }
   }
 }
+
+// Threads of k_ref_clusters: one position each up to 1024, whole waves.
+unsigned cluster_threads(int m) { return unsigned(std::min(CL_THREADS, (m + 63) / 64 * 64)); }
 
 struct RefineWork {
   double2 *mat[7], *W, *gpart;
@@ -698,7 +744,7 @@ size_t refine_scratch_bytes(int m) {
 }
 
 int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                int maxit, hipStream_t st, int sq_split) {
+                int maxit, hipStream_t st, double* host, int sq_split) {
   if (m <= 0) return 0;
   const double tol = tg.tol, noise = tg.noise, orth = tg.orth;
   RefineWork r = carve(work, m);
@@ -728,13 +774,10 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
       hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                          r.part, g_launch_gate);
       hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
-                         int(ncheck), r.norms, g_launch_gate);
-      double h[3];
-      int hi[2];
-      hipMemcpyAsync(h, r.norms, sizeof(h), hipMemcpyDeviceToHost, st);
-      hipMemcpyAsync(hi, r.info, sizeof(hi), hipMemcpyDeviceToHost, st);
-      hipStreamSynchronize(st);
-      if (!(h[0] == h[0]) || !(h[1] == h[1]) || !(h[2] == h[2]) || hi[1] > KMAX) return -1;
+                         int(ncheck), r.norms, (const int*)r.info, host, g_launch_gate);
+      if (hipStreamSynchronize(st) != hipSuccess) return -1;
+      const double* h = host;
+      if (!(h[0] == h[0]) || !(h[1] == h[1]) || !(h[2] == h[2]) || h[3] > KMAX) return -1;
       if ((h[0] <= tol * tol * h[1] || h[0] < 1e-300) && h[2] <= orth) {
         eig_sort(S, X, m, m, w, Z, st);
         return it;
@@ -748,11 +791,12 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
     hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, (const double*)r.lam, m, r.rank, r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
                        (const int*)r.rank, m, THETA, (const double*)tau, r.reach, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(1024), 0, st, (const int*)r.reach, m, r.pm,
+    hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W, tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2, g_launch_gate);
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+                       g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, r.emax, st);
     // E^2/2 only while |E| > e2skip, decided on the device (as in the
     // device-decided refinement, so that the two take the same arithmetic)
@@ -837,7 +881,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
         hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                            r.part, g_launch_gate);
         hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
-                           int(ncheck), r.norms, g_launch_gate);
+                           int(ncheck), r.norms, (const int*)r.info, (double*)nullptr, g_launch_gate);
       }
       hipLaunchKernelGGL(k_ref_decide, dim3(1), dim3(64), 0, st, (const double*)r.norms,
                          (const int*)r.info, tol, orth, it, maxit, flags, set);
@@ -858,12 +902,13 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
                        r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
                        (const int*)r.rank, m, THETA, (const double*)tau, r.reach, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(1024), 0, st, (const int*)r.reach, m, r.pm,
+    hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W,
                        tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2, g_launch_gate);
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+                       g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, r.emax, st);
     int* e2 = r.info + 3;
     hipLaunchKernelGGL(k_ref_e2_flag, dim3(1), dim3(64), 0, st, (const unsigned long long*)r.emax,

@@ -262,6 +262,10 @@ struct sky_ctx {
   GridArgs g;          // untwisted grid arguments (fields, tuning)
   bool hpsi_lagged = false;   // one_h: h psi holds (h phi) U of the last update
   Skyrme sk;
+  // pinned status words the solvers' kernels write (HOST_STATUS doubles): a read
+  // of a norm is then a wait for the stream, without a copy kernel and a staged
+  // transfer.  Allocated at the first solve, freed with the context.
+  double* host = nullptr;
   int last_sweeps;     // eigensolver iterations of the last iteration
   int fallbacks;       // refinement -> Jacobi fallbacks in the current call
   int unconverged;     // Jacobi solves of the current call stopped at the sweep limit
@@ -446,8 +450,15 @@ void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
 // U = Z C (paper_solve).
 int paper_solve(sky_ctx* c, int s, double* ritz);
 
+int need_host(sky_ctx* c) {
+  if (c->host) return SKY_OK;
+  return hip_check(hipHostMalloc(reinterpret_cast<void**>(&c->host), sizeof(double) * HOST_STATUS,
+                                 hipHostMallocDefault),
+                   "status memory");
+}
+
 int jacobi_checked(sky_ctx* c, void* A, int m, double* w, void* Z) {
-  const int its = jacobi_eigh(A, m, w, Z, c->at(c->lay.jac_work), JACOBI_TOL, JACOBI_SWEEPS, c->st);
+  const int its = jacobi_eigh(A, m, w, Z, c->at(c->lay.jac_work), JACOBI_TOL, JACOBI_SWEEPS, c->st, c->host);
   if (its == -2) return fail(SKY_ERR_NAN, "non-finite subspace matrix");
   if (its < 0) {
     ++c->unconverged;
@@ -457,6 +468,8 @@ int jacobi_checked(sky_ctx* c, void* A, int m, double* w, void* Z) {
 }
 
 int subspace_solve(sky_ctx* c, int s, double* ritz) {
+  int rch = need_host(c);
+  if (rch) return rch;
   if (c->d.update == SKY_UPDATE_PAPER) return paper_solve(c, s, ritz);
   const int q = s & 1;
   const int m = c->nq[q];
@@ -475,7 +488,7 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
   void* sq = c->at(c->lay.sq_part);
   const int sqs = c->tune.sq[q];
   const int terms = loewdin_series(I, Linv, Cw, T, m, LOEWDIN_SERIES_MAX,
-                                   c->at<double>(c->lay.nrm), sq, st, sqs,
+                                   c->at<double>(c->lay.nrm), sq, st, c->host, sqs,
                                    c->prec ? MIXED_SERIES_EPS : SERIES_EPS);
   if (terms < 0) return fail(SKY_ERR_NAN, "non-finite overlap matrix");
   if (terms > 0) {   // C = I^-1/2 (Hermitian) in Linv
@@ -493,7 +506,7 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
   }
   double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
   int its = refine_eigh(Hp, m, w, Z, c->at(c->lay.ref_work), c->prec ? REFINE_MIXED : REFINE_FP64,
-                        REFINE_ITERS, st, sqs);
+                        REFINE_ITERS, st, c->host, sqs);
   if (its < 0) {   // a wide cluster or no convergence: blocked Jacobi from H'
     ++c->fallbacks;
     its = jacobi_checked(c, Hp, m, w, Z);
@@ -613,7 +626,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
   hipMemsetAsync(info, 0, sizeof(int), st);
   // 3c: C = I^-1/2, by the series near the identity, else by the eigenvectors of I
   const int terms = loewdin_series(I, C, Cw, T, m, LOEWDIN_SERIES_MAX,
-                                   c->at<double>(c->lay.nrm), sq, st, sqs);
+                                   c->at<double>(c->lay.nrm), sq, st, c->host, sqs);
   if (terms < 0) return fail(SKY_ERR_NAN, "non-finite overlap matrix");
   if (terms == 0) {
     double* wi = c->at<double>(c->lay.wtmp);
@@ -631,7 +644,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
   double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
   const RefineTargets tg{JACOBI_TOL, c->prec ? MIXED_HP_NOISE : 0x1p-49, REFINE_FP64.orth,
                          REFINE_FP64.e2skip};
-  int its = refine_eigh(H, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, sqs);
+  int its = refine_eigh(H, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host, sqs);
   if (its < 0) {
     ++c->fallbacks;
     hipMemcpyAsync(X, H, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
@@ -738,6 +751,8 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   const int q = s & 1;
   const int m = c->nq[q];
   if (m == 0) return SKY_OK;
+  int rch = need_host(c);
+  if (rch) return rch;
   hipStream_t st = c->st;
   void* I = c->at(c->lay.matI);
   void* X = c->at(c->lay.matZ);
@@ -1639,6 +1654,7 @@ void sky_destroy(sky_ctx* c) {
   for (auto& m : c->marks) { hipEventDestroy(m.a); hipEventDestroy(m.b); }
   for (auto e : c->pool) hipEventDestroy(e);
   graphs_clear(c);
+  if (c->host) hipHostFree(c->host);
   delete c;
 }
 

@@ -214,9 +214,6 @@ void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
 void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,
                     const unsigned int* mxX, void* Y, int m, long k, hipStream_t st,
                     int waves = 8);
-// Fill the upper triangle of Hermitian C from the lower one (and make the
-// diagonal real), in place.
-void hermitian_fill(void* C, int m, hipStream_t st);
 // Y[b][v] = sum_a U[a][b] X[a][v]   (psi = phi U), X: m x k, U: m x m (ld m)
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st);
 // C = op(A) op(B), square m x m; opA/opB: 0 = N, 1 = conjugate transpose.
@@ -240,7 +237,10 @@ void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m,
 // max |Z^H Z - 1| below orth.  noise: the relative precision of A's entries
 // (x its rms eigenvalue = the coupling floor below which entries are noise:
 // no clusters, no rotation, counted as converged); 8 ulps for A from FP64
-// products.  Synchronises the stream once per step.
+// products.  Synchronises the stream once per step; host: HOST_STATUS doubles
+// of pinned host memory that the kernels write their results for the host to
+// (one caller at a time).
+constexpr int HOST_STATUS = 8;
 size_t refine_scratch_bytes(int m);
 // Stop and step targets of the refinement.
 struct RefineTargets {
@@ -250,7 +250,7 @@ struct RefineTargets {
   double e2skip;   // an update forms its E^2/2 term while max |E| > e2skip
 };
 int refine_eigh(const void* A, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                int maxit, hipStream_t st, int sq_split = 0);
+                int maxit, hipStream_t st, double* host, int sq_split = 0);
 // The same refinement with its decisions on the device (launches only): up
 // to maxit steps, each gated by flags[F_REF_RUN]; the check after step it
 // sorts the eigenpairs out when converged (flags[F_REF_OK + it]); a step
@@ -274,8 +274,9 @@ void cholesky_inverse(void* A, void* Linv, int m, void* work, int* info, hipStre
 // after max_sweeps sweeps (w, Z then hold the last sweep's result), -2 when
 // the matrix holds a non-finite value.
 size_t jacobi_scratch_bytes(int m);
+// host as refine_eigh's.
 int jacobi_eigh(void* A, int m, double* w, void* Z, void* work, double tol, int max_sweeps,
-                hipStream_t st);
+                hipStream_t st, double* host);
 // Gauge of the paper-literal update: info[3c..3c+2] = (start, size, packed
 // offset) of the eigenvalue cluster of column c.  gauge_gather packs each
 // cluster's diagonal block of Z (row-major, m x m); gauge_apply writes
@@ -289,9 +290,10 @@ void gauge_apply(const void* Z, int m, const int* info, const void* Q, void* out
 // Returns p, 0 (nothing written to C) when ||D||_F > max_dev, or -1 when
 // ||D||_F is not a finite number.  D and T
 // are m x m work matrices, scratch >= 257 doubles, part the square-product
-// scratch (gemm_square); synchronises the stream.
+// scratch (gemm_square), host as refine_eigh's; synchronises the stream.
 int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_dev,
-                   double* scratch, void* part, hipStream_t st, int sq_split = 0, double eps = 0x1p-56);
+                   double* scratch, void* part, hipStream_t st, double* host, int sq_split = 0,
+                   double eps = 0x1p-56);
 // The series with the decision on the device: the term count from the norm
 // of D = I - 1 (as loewdin_series), Horner steps gated by flags[F_SERIES + k].
 // If the series does not apply (norm above max_dev or not finite), flags

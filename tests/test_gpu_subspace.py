@@ -69,3 +69,34 @@ def test_jacobi_eigenpairs(m):
     psi = to_host(out).reshape(m, -1)
     ref = ((z * lam ** -0.5) @ z.conj().T).T @ f
     assert np.abs(psi - ref).max() <= tol
+
+
+# cluster sizes of a degenerate spectrum: none, pairs, shells, the widest cluster the
+# refinement takes (48) and a wider one (Jacobi fallback)
+@pytest.mark.parametrize("sizes", [[1] * 5, [2] * 8, [2, 12, 24], [1, 48, 3], [50, 2], [1] * 130,
+                                   [2] * 40 + [24, 17, 24]])
+def test_rayleigh_ritz_of_degenerate_levels(sizes):
+    """Ritz values, U^H I U = 1 and U^H H U = diag for phi a small step off
+    eigenstates of an operator with degenerate levels."""
+    n, m = 8, sum(sizes)
+    rng = np.random.default_rng(300 + m)
+    q = np.linalg.qr(rng.standard_normal((1024, m)) + 1j * rng.standard_normal((1024, m)))[0].T
+    lam = np.repeat(-60.0 + 3.0 * np.arange(len(sizes)), sizes)
+    phi = q + 1e-4 * (rng.standard_normal(q.shape) + 1j * rng.standard_normal(q.shape))
+    hphi = ((phi @ q.conj().T) * lam) @ q
+    shape = (m, 2, n, n, n)
+    box = _box(n, m)
+    out, ritz = to_dev(np.zeros(shape, complex)), to_dev(np.zeros(m))
+    box.orthonormalize(0, to_dev(phi.reshape(shape)), to_dev(hphi.reshape(shape)), out, ritz)
+    I, H = phi.conj() @ phi.T, phi.conj() @ hphi.T
+    low = np.linalg.inv(np.linalg.cholesky(I))
+    ref = np.linalg.eigvalsh(low @ H @ low.conj().T)
+    scale = np.abs(lam).max()
+    assert np.abs(to_host(ritz) - ref).max() <= 1e-12 * scale * np.sqrt(m)
+    u = to_host(box.view("umat"))
+    assert np.abs(u.conj().T @ I @ u - np.eye(m)).max() <= 1e-12
+    # the solvers stop at an off-diagonal Frobenius norm of 1e-12 of the norm
+    d = u.conj().T @ H @ u
+    assert np.linalg.norm(d - np.diag(np.diag(d))) <= 4e-12 * np.linalg.norm(lam)
+    psi = to_host(out).reshape(m, -1)
+    assert np.abs(psi - u.T @ phi).max() <= 1e-12
