@@ -871,10 +871,11 @@ k_damp_inv_x(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ buf,
 //   y: tau_y, j_y, J_x(y), J_z(y)                              (slots 8..11)
 //   z: tau_z, j_z, J_x(z), J_y(z)                              (slots 12..15)
 // with J_k = sum_lm eps_klm Im(psi^dag sigma_m d_l psi).  Partial sums per
-// state chunk go to part[chunk][slot][point] and are reduced in fixed order.
+// state chunk (blockIdx.y; the first species' chunks, then the second's) go to
+// part[chunk][slot][point] and are reduced in fixed order.
 template <typename T, int N, int DIR>
 __global__ void __launch_bounds__(LineCfg<N>::THREADS)
-k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restrict__ part, const int* __restrict__ sky_gate) {
+k_dens_pass(DensArgs grp, GridArgs g, double* __restrict__ part, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   using C = LineCfg<N>;
   using F = LineFFT<T, N, 2, DIR == 0 && x_wave_local<N>()>;
@@ -902,11 +903,14 @@ k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restric
   // chunks of the flat (group, state) index: every group's states in order;
   // the next state's line is loaded into registers while this one is
   // transformed
-  const int s0 = blockIdx.y * chunk;
-  const int s1 = min(nstate * grp.ngroup, s0 + chunk);
+  const bool second = int(blockIdx.y) >= grp.sp[0].nchunk;
+  const DensSpecies& sp = grp.sp[second ? 1 : 0];
+  const int nstate = sp.nstate;
+  const int s0 = (int(blockIdx.y) - (second ? grp.sp[0].nchunk : 0)) * grp.chunk;
+  const int s1 = min(nstate * grp.ngroup, s0 + grp.chunk);
   auto load_line = [&](int fs, cpx<T> (&dst)[2][R1]) {
     const int t = fs / nstate, st = fs - t * nstate;
-    const cpx<T>* p = reinterpret_cast<const cpx<T>*>(grp.psi[t]) + size_t(st) * 2 * N3;
+    const cpx<T>* p = reinterpret_cast<const cpx<T>*>(sp.psi[t]) + size_t(st) * 2 * N3;
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       const int r = base + (j + R2 * j1) * stride;
@@ -971,21 +975,24 @@ k_dens_pass(DensGroups grp, int nstate, int chunk, GridArgs g, double* __restric
   }
 }
 
-// rho, tau, J[3], s[3], j[3] (11 fields) from the chunk partials.
-__global__ void k_dens_reduce(const double* __restrict__ part, int nchunk, int n3,
-                              double* __restrict__ dens, double scale, const int* __restrict__ sky_gate) {
+// rho, tau, J[3], s[3], j[3] (11 fields) of species blockIdx.y from its chunk
+// partials (zero without chunks).
+__global__ void k_dens_reduce(const double* __restrict__ part, DensArgs grp, int n3, double scale,
+                              const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n3) return;
+  const DensSpecies& sp = grp.sp[blockIdx.y];
+  const int c0 = blockIdx.y ? grp.sp[0].nchunk : 0;
   double q[16];
   for (int k = 0; k < 16; ++k) q[k] = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
+  for (int c = c0; c < c0 + sp.nchunk; ++c) {
     const double* p = part + size_t(c) * 16 * n3 + r;
     for (int k = 0; k < 16; ++k) q[k] += p[size_t(k) * n3];
   }
   if (scale != 1.0)
     for (int k = 0; k < 16; ++k) q[k] *= scale;
-  double* o = dens;
+  double* o = sp.dens;
   o[0 * n3 + r] = q[0];                       // rho
   o[1 * n3 + r] = q[4] + q[8] + q[12];        // tau
   o[2 * n3 + r] = q[10] + q[14];              // J_x
@@ -1208,38 +1215,74 @@ void damped_step(int n, int prec, const void* psi, const void* hpsi, const doubl
   if (r2) sum_partials(r2_part, nullptr, nt, nstate, r2, nullptr, st);
 }
 
-template <typename T, int N>
-static void launch_dens(const DensGroups& grp, int nstate, int chunk, int nchunk, GridArgs g,
-                        double* part, hipStream_t st) {
-  dim3 grid(ntiles<N>(), nchunk), block(LineCfg<N>::THREADS);
-  hipLaunchKernelGGL((k_dens_pass<T, N, 0>), grid, block, 0, st, grp, nstate, chunk, g, part, g_launch_gate);
-  hipLaunchKernelGGL((k_dens_pass<T, N, 1>), grid, block, 0, st, grp, nstate, chunk, g, part, g_launch_gate);
-  hipLaunchKernelGGL((k_dens_pass<T, N, 2>), grid, block, 0, st, grp, nstate, chunk, g, part, g_launch_gate);
+// Workgroups of a density pass that the card holds at once.
+template <typename T, int N> static int dens_capacity() {
+  static const int cap = [] {
+    int per_cu = 0, dev = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_dens_pass<T, N, 1>,
+                                                     LineCfg<N>::THREADS, 0) != hipSuccess)
+      per_cu = 2;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      cus = 256;
+    return std::max(1, per_cu) * std::max(1, cus);
+  }();
+  return cap;
 }
 
-int densities(int n, int prec, const void* const* psi, const GridArgs* g, int ngroup,
-              int nstate, int nchunk_max, double* part, double* dens, hipStream_t st) {
-  const int n3 = n * n * n;
-  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nchunk_max < 1) return 0;
-  if (nstate <= 0 || ngroup == 0) {
-    zero(dens, size_t(11) * n3, st);
-    return 1;
+// Chunks of states: as many as fill the card once.  More only add partial
+// sums (16 doubles per point and chunk, written and read: as much as six
+// complex64 states' reads) and a last round of workgroups that is mostly
+// empty.  640 + 160 complex64 states at 32^3: 32 chunks per species and launches
+// of its own took 386 us for the passes and 62 for the sums, now 301 (4.2 TB/s
+// per pass) and 25; 1600 + 400 at 48^3 3.1 and 0.16 ms, now 2.6 and 0.02.
+template <typename T, int N>
+static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g, double* part,
+                        hipStream_t st) {
+  const int want = std::min(nchunk_max, std::max(nspecies, dens_capacity<T, N>() / ntiles<N>()));
+  int total = 0;
+  for (int q = 0; q < nspecies; ++q) total += grp.ngroup * grp.sp[q].nstate;
+  // the smallest chunk whose count over both species does not exceed `want`
+  auto chunks = [&](int c) {
+    int k = 0;
+    for (int q = 0; q < nspecies; ++q) k += (grp.ngroup * grp.sp[q].nstate + c - 1) / c;
+    return k;
+  };
+  int chunk = std::max(1, (total + want - 1) / want);
+  while (chunks(chunk) > want) ++chunk;
+  grp.chunk = chunk;
+  for (int q = 0; q < nspecies; ++q)
+    grp.sp[q].nchunk = (grp.ngroup * grp.sp[q].nstate + chunk - 1) / chunk;
+  const int nchunk = chunks(chunk);
+  if (nchunk > 0) {
+    dim3 grid(ntiles<N>(), nchunk), block(LineCfg<N>::THREADS);
+    hipLaunchKernelGGL((k_dens_pass<T, N, 0>), grid, block, 0, st, grp, g, part, g_launch_gate);
+    hipLaunchKernelGGL((k_dens_pass<T, N, 1>), grid, block, 0, st, grp, g, part, g_launch_gate);
+    hipLaunchKernelGGL((k_dens_pass<T, N, 2>), grid, block, 0, st, grp, g, part, g_launch_gate);
   }
-  // one launch per pass over all groups (twists): the flat (group, state)
-  // index is cut into at most nchunk_max chunks of consecutive states
-  DensGroups grp{};
+  constexpr int n3 = N * N * N;
+  hipLaunchKernelGGL(k_dens_reduce, dim3((n3 + 255) / 256, nspecies), dim3(256), 0, st,
+                     (const double*)part, grp, n3, 1.0 / std::max(1, grp.ngroup), g_launch_gate);
+}
+
+int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
+              const int* nstate, double* const* dens, const GridArgs* g, int ngroup,
+              int nchunk_max, double* part, hipStream_t st) {
+  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nspecies < 1 || nspecies > 2 || nchunk_max < nspecies)
+    return 0;
+  // one launch per pass over all species and groups (twists): each species'
+  // flat (group, state) index is cut into chunks of consecutive states
+  DensArgs grp{};
   grp.ngroup = ngroup;
-  for (int t = 0; t < ngroup; ++t) {
-    grp.psi[t] = psi[t];
+  for (int t = 0; t < ngroup; ++t)
     for (int a = 0; a < 3; ++a) grp.kshift[t][a] = g[t].tw[a];
+  for (int q = 0; q < nspecies; ++q) {
+    for (int t = 0; t < ngroup; ++t) grp.sp[q].psi[t] = psi[q][t];
+    grp.sp[q].nstate = std::max(0, nstate[q]);
+    grp.sp[q].dens = dens[q];
   }
-  const int total = ngroup * nstate;
-  const int chunk = (total + nchunk_max - 1) / nchunk_max;
-  const int nchunk = (total + chunk - 1) / chunk;
-  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nstate, chunk, nchunk, g[0], part, st))
-  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nstate, chunk, nchunk, g[0], part, st))
-  hipLaunchKernelGGL(k_dens_reduce, dim3((n3 + 255) / 256), dim3(256), 0, st,
-                     (const double*)part, nchunk, n3, dens, 1.0 / ngroup, g_launch_gate);
+  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nspecies, nchunk_max, g[0], part, st))
+  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nspecies, nchunk_max, g[0], part, st))
   return 1;
 }
 

@@ -262,6 +262,7 @@ struct sky_ctx {
   GridArgs g;          // untwisted grid arguments (fields, tuning)
   bool hpsi_lagged = false;   // one_h: h psi holds (h phi) U of the last update
   Skyrme sk;
+  FieldTaps taps;      // line operators of the field derivatives and the Coulomb DFT
   // pinned status words the solvers' kernels write (HOST_STATUS doubles): a read
   // of a norm is then a wait for the stream, without a copy kernel and a staged
   // transfer.  Allocated at the first solve, freed with the context.
@@ -797,28 +798,27 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
 // averaged over the twists, then mean field, Coulomb and energy.
 void fields(sky_ctx* c) {
   hipStream_t st = c->st;
-  const void* ps[SKY_MAX_TWIST];
-  GridArgs gs[SKY_MAX_TWIST];
-  for (int q = 0; q < 2; ++q) {
+  const void* ps[2][DENS_MAX_GROUPS] = {};
+  GridArgs gs[DENS_MAX_GROUPS];
+  double* dens[2] = {c->at<double>(c->lay.dens[0]), c->at<double>(c->lay.dens[1])};
+  for (int t = 0; t < c->ntw; ++t) {
+    gs[t] = c->gset(2 * t);   // the twist; the same for both species
+    for (int q = 0; q < 2; ++q) ps[q][t] = c->psi(2 * t + q);
+  }
+  // both species in one launch per pass; one after the other only to be timed
+  const int per = c->timing ? 1 : 2;
+  for (int q = 0; q < 2; q += per) {
     const int td = t_begin(c, SKY_PHASE_DENSITIES, q);
-    for (int t = 0; t < c->ntw; ++t) {
-      ps[t] = c->psi(2 * t + q);
-      gs[t] = c->gset(2 * t + q);
-    }
-    (void)sky::densities(c->n, c->prec, ps, gs, c->ntw, c->nocc[q], DENS_CHUNKS,
-                   c->at<double>(c->lay.dens_part), c->at<double>(c->lay.dens[q]), st);
+    (void)sky::densities(c->n, c->prec, per, ps + q, c->nocc + q, dens + q, gs, c->ntw, DENS_CHUNKS,
+                         c->at<double>(c->lay.dens_part), st);
     t_end(c, td);
   }
   const int tmf = t_begin(c, SKY_PHASE_MEANFIELD, 0);
-  mean_field(c->n, c->g, c->sk, c->at<double>(c->lay.dens[0]), c->at<double>(c->lay.dens[1]),
-             c->at<double>(c->lay.der[0]), c->at<double>(c->lay.der[1]),
-             c->at<double>(c->lay.mf[0]), c->at<double>(c->lay.mf[1]),
-             c->at<double>(c->lay.vc), c->at(c->lay.fscratch), c->at<double>(c->lay.epart),
-             c->at<double>(c->lay.energy), st);
-  // FP32 copies of U, B, W for the complex64 kernels (5 n^3 doubles as
-  // complex pairs: n^3 is even)
-  for (int q = 0; q < 2; ++q)
-    convert_states(c->at(c->lay.mf[q]), 0, c->at(c->lay.mf32[q]), 1, size_t(5) * c->n3 / 2, st);
+  mean_field(c->n, c->g, c->sk, c->taps, dens[0], dens[1], c->at<double>(c->lay.der[0]),
+             c->at<double>(c->lay.der[1]), c->at<double>(c->lay.mf[0]),
+             c->at<double>(c->lay.mf[1]), c->at<float>(c->lay.mf32[0]),
+             c->at<float>(c->lay.mf32[1]), c->at<double>(c->lay.vc), c->at(c->lay.fscratch),
+             c->at<double>(c->lay.epart), c->at<double>(c->lay.energy), st);
   t_end(c, tmf);
 }
 // |k| at the corner of the Brillouin zone
@@ -1317,6 +1317,7 @@ int sky_create(const sky_box_desc* d, void* workspace, size_t bytes, void* strea
   c->g.dV = d->dx * d->dx * d->dx;
   c->g.kunit = 2.0 * M_PI / (d->n * d->dx);
   c->g.tw[0] = c->g.tw[1] = c->g.tw[2] = 0.0;
+  c->taps = field_taps(d->n, c->g.kunit);
   const double t0 = d->t0, t1 = d->t1, t2 = d->t2, t3 = d->t3;
   const double x0 = d->x0, x1 = d->x1, x2 = d->x2, x3 = d->x3;
   // b-coefficients of the Skyrme functional (standard t/x -> b mapping)

@@ -112,20 +112,27 @@ void precond_dir(int prec, const void* bpsi, void* bphi, size_t n, hipStream_t s
 size_t precond_gram_bytes(int ns);
 void precond_targets(int prec, const void* bpsi, const void* bh, const void* bd, const void* bhd,
                      const double* beps, int ns, long V, double* part, float* S, hipStream_t st);
-// dens = 11 fields [rho, tau, Jx, Jy, Jz, sx, sy, sz, jx, jy, jz][n^3],
-// summed over the first nstate states of each of ngroup state arrays psi[t]
-// (each with its own grid arguments g[t], i.e. its twist; spacing from g[0])
-// and divided by ngroup (the twist average); part holds nchunk_max * 16 * n^3
-// doubles.  Returns 0 (nothing launched) for ngroup outside [0,
-// DENS_MAX_GROUPS] or nchunk_max < 1.
+// dens[q] = 11 fields [rho, tau, Jx, Jy, Jz, sx, sy, sz, jx, jy, jz][n^3] of each
+// of nspecies species, summed over the first nstate[q] states of each of ngroup
+// state arrays psi[q][t] (each with its own grid arguments g[t], i.e. its
+// twist; spacing from g[0]) and divided by ngroup (the twist average); part
+// holds nchunk_max * 16 * n^3 doubles.  Returns 0 (nothing launched) for ngroup
+// outside [0, DENS_MAX_GROUPS], nspecies outside 1..2 or nchunk_max < nspecies.
 constexpr int DENS_MAX_GROUPS = 32;
-struct DensGroups {
+struct DensSpecies {
   const void* psi[DENS_MAX_GROUPS];
-  double kshift[DENS_MAX_GROUPS][3];   // GridArgs::tw of each group
-  int ngroup;
+  int nstate;        // occupied states of each group
+  int nchunk;        // chunks of this species' flat (group, state) index
+  double* dens;
 };
-int densities(int n, int prec, const void* const* psi, const GridArgs* g, int ngroup,
-               int nstate, int nchunk_max, double* part, double* dens, hipStream_t st);
+struct DensArgs {
+  DensSpecies sp[2];
+  double kshift[DENS_MAX_GROUPS][3];   // GridArgs::tw of each group
+  int ngroup, chunk;                   // states per chunk
+};
+int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
+              const int* nstate, double* const* dens, const GridArgs* g, int ngroup,
+              int nchunk_max, double* part, hipStream_t st);
 // n complex values between precisions (0 = complex128, 1 = complex64).
 void convert_states(const void* src, int src_prec, void* dst, int dst_prec, size_t n,
                     hipStream_t st);
@@ -141,14 +148,21 @@ struct Skyrme {
   double b0, b0p, b1, b1p, b2, b2p, b3, b3p, b4, b4p, alpha;
   double hb2m_n, hb2m_p, e2;
 };
+// Taps of the line operators (first and second derivative of a real field) and
+// the DFT twiddles e^{-2 pi i d / n} of an n-point axis, handed to the kernels by
+// value.
+struct FieldTaps {
+  double c0[64], c1[64], twr[64], twi[64];
+};
+FieldTaps field_taps(int n, double kunit);
 // dens[q] as produced by densities(); derived[q] = 5 fields [lap rho, d rho (3), div J];
-// mf[q] = 5 fields [U, B, Wx, Wy, Wz]; vc = Coulomb potential;
-// scratch >= 2 n^3 complex + 4 n doubles (mean_field_scratch_bytes).
+// mf[q] = 5 fields [U, B, Wx, Wy, Wz], mf32[q] the same in FP32; vc = Coulomb
+// potential; scratch >= 2 n^3 complex (mean_field_scratch_bytes).
 // epart: per-block energy partials, energy[8] = {kin, rho, rho3, tau, lap, so, coul, total}.
-void mean_field(int n, GridArgs g, const Skyrme& sk, const double* dens_n,
+void mean_field(int n, GridArgs g, const Skyrme& sk, const FieldTaps& tab, const double* dens_n,
                 const double* dens_p, double* derived_n, double* derived_p, double* mf_n,
-                double* mf_p, double* vc, void* scratch, double* epart, double* energy,
-                hipStream_t st);
+                double* mf_p, float* mf32_n, float* mf32_p, double* vc, void* scratch,
+                double* epart, double* energy, hipStream_t st);
 int energy_nblocks(int n);
 size_t mean_field_scratch_bytes(int n);
 
