@@ -196,9 +196,10 @@ template <typename T, int N, int S, bool WL = false> struct LineFFT {
   // In-place spectral derivative i*(k + kshift) along the line, Nyquist kept
   // (k = -N/2); kshift is the Bloch shift of twisted boundary conditions.  kun
   // and ksn are the wave-number unit and kshift divided by N (the inverse's
-  // scale).  R2 is even, so whether a frequency wraps depends on k2 alone.
+  // scale); a caller that scales the result itself passes 1 and kshift / unit.
+  // R2 is even, so whether a frequency wraps depends on k2 alone.
   __device__ static inline void deriv(cpx<T> (&va)[S][R1], cpx<T>* Y, int j,
-                                      const cpx<T>* twN, T kun, T ksn = T(0)) {
+                                      const cpx<T>* twN, T kun, T ksn) {
     cpx<T> vb[S][R2];
     forward(va, vb, Y, j, twN);
     if (j < R1) {

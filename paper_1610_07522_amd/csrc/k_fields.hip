@@ -282,16 +282,21 @@ void launch_coulomb(const double* rho_p, double* vc, double2* a, double2* b, con
 // -kunit^2 (n^2 + 2) / 12 at d = 0: the differentiation matrices of periodic
 // spectral collocation (Trefethen, Spectral Methods in MATLAB, ch. 3).
 FieldTaps field_taps(int n, double kunit) {
+  // extended precision, and the two halves of an axis exact mirror images: the
+  // taps' rounding errors then cancel in the derivative of a constant
+  const long double pi = 3.14159265358979323846264338327950288L;
   FieldTaps t{};
   for (int d = 0; d < n; ++d) {
-    const double s = std::sin(M_PI * d / n), c = std::cos(M_PI * d / n);
-    const double sign = d % 2 ? -1.0 : 1.0;
-    t.c0[d] = d ? 0.5 * kunit * sign * c / s : 0.0;
-    t.c1[d] = d ? -0.5 * kunit * kunit * sign / (s * s) : -kunit * kunit * (double(n) * n + 2.0) / 12.0;
-    t.twr[d] = std::cos(2.0 * M_PI * d / n);
-    t.twi[d] = -std::sin(2.0 * M_PI * d / n);
+    const int e = d <= n / 2 ? d : n - d;   // distance along the shorter way
+    const long double s = sinl(pi * e / n), c = cosl(pi * e / n), sign = e % 2 ? -1.0L : 1.0L;
+    const double c0 = e && 2 * e != n ? double(0.5L * kunit * sign * c / s) : 0.0;
+    t.c0[d] = d == e ? c0 : -c0;
+    t.c1[d] = e ? double(-0.5L * kunit * kunit * sign / (s * s))
+                : double(-(long double)kunit * kunit * (n * n + 2.0L) / 12.0L);
+    t.twr[d] = double(cosl(2.0L * pi * e / n));
+    const double si = 2 * e != n ? double(sinl(2.0L * pi * e / n)) : 0.0;
+    t.twi[d] = d == e ? -si : si;
   }
-  if (n % 2 == 0) t.c0[n / 2] = 0.0;
   return t;
 }
 

@@ -357,7 +357,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
   const size_t soff = size_t(blockIdx.y) * 2 * N3;
   const cpx<T>* p = psi + soff;
   cpx<T>* hp = hpsi + soff;
-  const T kun = T(g.kunit * (1.0 / N));
+  const T kun = T(g.kunit * (1.0 / N)), kx = T(g.tw[0] * (1.0 / N)), ky = T(g.tw[1] * (1.0 / N));
   cpx<T> acc[2][R1], d[2][R1];
   {  // x lines: row ly, role jx (role fastest: consecutive threads, consecutive x)
     const int jx = threadIdx.x % RT, ly = threadIdx.x / RT;
@@ -370,7 +370,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
       }
     }
     load_twiddles<T, N>(tw);
-    FX::deriv(d, E + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)));
+    FX::deriv(d, E + ly * XS, jx, tw, kun, kx);
     if (jx < R2) {
       const cpx<T>* q = reread(p);
 #pragma unroll
@@ -379,7 +379,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
         h_local<T, N, 0>(mf, r, q[r], q[N3 + r], d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
       }
     }
-    FX::deriv(d, E + ly * XS, jx, tw, kun, T(g.tw[0] * (1.0 / N)));
+    FX::deriv(d, E + ly * XS, jx, tw, kun, kx);
     __syncthreads();   // every x line is done with its buffer
     if (jx < R2) {
 #pragma unroll
@@ -411,7 +411,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
     }
   }
   __syncthreads();
-  FY::deriv(d, E + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)));
+  FY::deriv(d, E + lx * YS, jy, tw, kun, ky);
   if (jy < R2) {
     const cpx<T>* q = reread(p);
 #pragma unroll
@@ -423,7 +423,7 @@ k_h_plane(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPt
       acc[1][j1] = acc[1][j1] + ad;
     }
   }
-  FY::deriv(d, E + lx * YS, jy, tw, kun, T(g.tw[1] * (1.0 / N)));
+  FY::deriv(d, E + lx * YS, jy, tw, kun, ky);
   double dot = 0.0, nrm = 0.0;
   float am = 0.0f;
   if (jy < R2) {
@@ -892,7 +892,6 @@ k_dens_pass(DensArgs grp, GridArgs g, double* __restrict__ part, const int* __re
   int base, stride, a, b;
   line_geom<N, DIR>(L, base, stride, a, b);
   cpx<T>* Y = Ybuf + line * YS;
-  const T kun = T(g.kunit * (1.0 / N));
 
   double acc[NS][R1];
 #pragma unroll
@@ -921,7 +920,9 @@ k_dens_pass(DensArgs grp, GridArgs g, double* __restrict__ part, const int* __re
   cpx<T> vn[2][R1];
   if (s0 < s1 && j < R2) load_line(s0, vn);
   for (int fs = s0; fs < s1; ++fs) {
-    const T ksn = T(grp.kshift[fs / nstate][DIR] * (1.0 / N));
+    // derivatives in units of kunit / N: integer multipliers, exact in FP32; the
+    // sums are scaled in FP64
+    const T ksn = T(grp.kshift[fs / nstate][DIR]);
     cpx<T> v[2][R1], d[2][R1];
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
@@ -929,7 +930,7 @@ k_dens_pass(DensArgs grp, GridArgs g, double* __restrict__ part, const int* __re
       v[1][j1] = d[1][j1] = vn[1][j1];
     }
     if (fs + 1 < s1 && j < R2) load_line(fs + 1, vn);
-    F::deriv(d, Y, j, tw, kun, ksn);
+    F::deriv(d, Y, j, tw, T(1), ksn);
     if (j < R2) {
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1) {
@@ -966,11 +967,17 @@ k_dens_pass(DensArgs grp, GridArgs g, double* __restrict__ part, const int* __re
   }
   if (j < R2) {
     double* out = part + size_t(blockIdx.y) * 16 * N3;
+    const double u = g.kunit * (1.0 / N);
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
 #pragma unroll
-      for (int q = 0; q < NS; ++q) out[size_t(SLOT0 + q) * N3 + r] = acc[q][j1];
+      for (int q = 0; q < NS; ++q) {
+        // rho and s carry no derivative, tau two, j and J one
+        constexpr int TAU = DIR == 0 ? 4 : 0;
+        const double sc = q < TAU ? 1.0 : q == TAU ? u * u : u;
+        out[size_t(SLOT0 + q) * N3 + r] = sc * acc[q][j1];
+      }
     }
   }
 }
@@ -1275,7 +1282,7 @@ int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_G
   DensArgs grp{};
   grp.ngroup = ngroup;
   for (int t = 0; t < ngroup; ++t)
-    for (int a = 0; a < 3; ++a) grp.kshift[t][a] = g[t].tw[a];
+    for (int a = 0; a < 3; ++a) grp.kshift[t][a] = g[t].tw[a] / g[0].kunit;
   for (int q = 0; q < nspecies; ++q) {
     for (int t = 0; t < ngroup; ++t) grp.sp[q].psi[t] = psi[q][t];
     grp.sp[q].nstate = std::max(0, nstate[q]);
