@@ -42,252 +42,334 @@ __device__ inline float bf16_round(float x) {
   return __uint_as_float(u & 0xFFFF0000u);
 }
 
+// Packed BF16 copies of the two 128 x 128 weights behind the rounded parameters
+// (16-byte aligned): W2, W3 row-major for the forward layers, then both
+// transposed for the backward ones, so that every B operand of a matrix
+// instruction is one 16-byte load.
+constexpr int OPACK = (NPAR + 3) / 4 * 4;          // in floats from the parameters
+constexpr int WSZ = PH * PH;
+__device__ inline unsigned short bf16_hi(float x) { return (unsigned short)(__float_as_uint(x) >> 16); }
+__device__ inline const unsigned short* packed(const float* Pb, int layer, bool transposed) {
+  return reinterpret_cast<const unsigned short*>(Pb + OPACK) + (transposed ? 2 * WSZ : 0) + layer * WSZ;
+}
+
 __global__ void k_round_params(const float* __restrict__ p, float* __restrict__ q, int n, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) q[i] = bf16_round(p[i]);
+  if (i >= n) return;
+  const float v = bf16_round(p[i]);
+  q[i] = v;
+  const int layer = (i >= OW2 && i < OB2) ? 0 : (i >= OW3 && i < OB3) ? 1 : -1;
+  if (layer < 0) return;
+  unsigned short* w = reinterpret_cast<unsigned short*>(q + OPACK) + layer * WSZ;
+  const int o = i - (layer ? OW3 : OW2);
+  w[o] = bf16_hi(v);
+  w[2 * WSZ + (o % PH) * PH + o / PH] = bf16_hi(v);
 }
 
 // ---- forward pass on the BF16 matrix cores (v_mfma_f32_16x16x32_bf16)
-// One wave carries 16 samples through the MLP.  The two 128 x 128 layers are
-// MFMA products: the weights are BF16 values already (the parameters are
-// rounded by k_round_params), and each FP32 activation is split exactly into
-// three BF16 terms h = t0 + t1 + t2 (8 significant bits each, rounded to
-// nearest at each step), so that every product t_i w is exact in FP32 and
-// the layer is FP32 activations x BF16 weights with FP32 accumulation, as
-// the scalar form, up to the order of the sums.  MFMA operands: lane l
-// supplies 8 consecutive contraction elements starting at 8 (l / 16) of row
-// (A: sample) or column (B: neuron) l % 16; register e of lane l returns
-// sample 4 (l / 16) + e, neuron l % 16.  The first (4 inputs) and last
-// (1 output) layers are scalar.
+// A workgroup carries 16 samples through the MLP, each of its four waves a
+// quarter of the neurons.  The two 128 x 128 layers are MFMA products: the
+// weights are BF16 values already (the parameters are rounded by
+// k_round_params), and each FP32 activation is split exactly into three BF16
+// terms h = t0 + t1 + t2 (8 significant bits each, rounded to nearest at each
+// step), so that every product t_i w is exact in FP32 and the layer is FP32
+// activations x BF16 weights with FP32 accumulation, as the scalar form, up
+// to the order of the sums.  MFMA operands: lane l supplies 8 consecutive
+// contraction elements starting at 8 (l / 16) of row (A: sample) or column (B:
+// neuron) l % 16; register e of lane l returns sample 4 (l / 16) + e, neuron
+// l % 16.  The first (4 inputs) and last (1 output) layers are scalar.
+//
+// A few thousand rows are a few hundred short chains of layers: what counts is
+// their latency and that they reach every CU.  Hence 16 rows per workgroup (64
+// left three quarters of the CUs idle at 4099 rows), both layers' weights
+// loaded before the first is needed, and activations split once, by the wave
+// that makes them, into BF16 planes in LDS.  4099 rows: forward 34 -> 11.5,
+// backward with the loss 45 -> 12.9.
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
-constexpr int FR = 16;         // samples per wave
+constexpr int FR = 16;         // samples per workgroup
 constexpr int FWV = 4;         // waves per workgroup
-constexpr int FLP = PH + 4;    // LDS row pitch of the activations (floats)
+constexpr int NJ = PH / 16 / FWV;   // 16-neuron blocks per wave
+constexpr int KS = PH / 32;    // matrix instructions per block and split term
+constexpr int PLP = PH + 8;    // LDS row pitch of the BF16 planes
 
-__device__ inline unsigned short bf16_hi(float x) { return (unsigned short)(__float_as_uint(x) >> 16); }
-
-// 128 -> 128 layer of one wave: out = relu(bias + in W^T), in and out in LDS
-// ([FR][FLP]); W row-major [PH][PH] (BF16 values).
-__device__ inline void mlp_layer_mfma(const float* in, float* out, const float* __restrict__ W,
-                                      const float* __restrict__ bias, int lane) {
-  const int r = lane & 15, kg = (lane >> 4) * 8;
-  us8 a[PH / 32][3];
-#pragma unroll
-  for (int ks = 0; ks < PH / 32; ++ks)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const float x = in[r * FLP + ks * 32 + kg + t];
-      const float x0 = bf16_round(x), x1 = bf16_round(x - x0), x2 = bf16_round(x - x0 - x1);
-      a[ks][0][t] = bf16_hi(x0);
-      a[ks][1][t] = bf16_hi(x1);
-      a[ks][2][t] = bf16_hi(x2);
-    }
-#pragma unroll
-  for (int j = 0; j < PH / 16; ++j) {
-    const int n = j * 16 + r;
-    f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < PH / 32; ++ks) {
-      const float4* wp = reinterpret_cast<const float4*>(W + n * PH + ks * 32 + kg);
-      const float4 w0 = wp[0], w1 = wp[1];
-      const us8 wb = {bf16_hi(w0.x), bf16_hi(w0.y), bf16_hi(w0.z), bf16_hi(w0.w),
-                      bf16_hi(w1.x), bf16_hi(w1.y), bf16_hi(w1.z), bf16_hi(w1.w)};
-      const bf8 b = __builtin_bit_cast(bf8, wb);
-#pragma unroll
-      for (int t = 0; t < 3; ++t)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a[ks][t]), b, acc, 0, 0, 0);
-    }
-    const float bn = bias[n];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[(4 * (lane >> 4) + e) * FLP + n] = fmaxf(acc[e] + bn, 0.0f);
-  }
+// x = v[0][t] + v[1][t] + v[2][t] as three BF16 bit patterns (exact for
+// normal FP32 x: 8 significant bits per term, rounded to nearest at each step).
+__device__ inline void split3(float x, unsigned short& a, unsigned short& b, unsigned short& c) {
+  const float x0 = bf16_round(x), x1 = bf16_round(x - x0), x2 = bf16_round(x - x0 - x1);
+  a = bf16_hi(x0);
+  b = bf16_hi(x1);
+  c = bf16_hi(x2);
 }
 
-// Forward pass of FR samples per wave, FWV waves per workgroup.  H1..H3 (may
-// be null) keep the activations for the backward pass; O the outputs.
+// Split planes of a workgroup's 16 x 128 activations.
+struct alignas(16) Planes {
+  unsigned short v[3][FR][PLP];
+  __device__ void put(int s, int n, float x) { split3(x, v[0][s][n], v[1][s][n], v[2][s][n]); }
+};
+
+struct Weights {
+  us8 w[NJ][KS];
+};
+
+// The wave's B operands of one layer, neurons (or inputs) 32 wv .. 32 wv + 31.
+__device__ inline Weights load_weights(const unsigned short* __restrict__ W, int wv, int lane) {
+  Weights r;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      r.w[j][ks] = *reinterpret_cast<const us8*>(W + ((wv * NJ + j) * 16 + (lane & 15)) * PH + ks * 32 +
+                                                 (lane >> 4) * 8);
+  return r;
+}
+
+__device__ inline void layer_mfma(const Planes& in, const Weights& w, f4v (&acc)[NJ], int lane) {
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) acc[j] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const us8 a = *reinterpret_cast<const us8*>(&in.v[t][lane & 15][ks * 32 + (lane >> 4) * 8]);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a),
+                                                         __builtin_bit_cast(bf8, w.w[j][ks]), acc[j], 0, 0, 0);
+    }
+}
+
+// H1..H3 (all or none) keep the activations for the backward pass; O the outputs.
 __global__ void __launch_bounds__(64 * FWV)
 k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ X, int ldx, int B,
           float* __restrict__ H1, float* __restrict__ H2, float* __restrict__ H3,
           float* __restrict__ O, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ float hs[FWV][2][FR * FLP];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int b0 = (blockIdx.x * FWV + wv) * FR;
-  float* ha = hs[wv][0];
-  float* hb = hs[wv][1];
-  // layer 1: lane -> neurons lane, lane + 64
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int n = lane + 64 * q;
+  __shared__ Planes pa, pb;
+  __shared__ float red[FWV][FR];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int b0 = blockIdx.x * FR;
+  const Weights w2 = load_weights(packed(P, 0, false), wv, lane);
+  const Weights w3 = load_weights(packed(P, 1, false), wv, lane);
+  {  // layer 1: thread -> neuron, half of the samples
+    const int n = tid % PH, s0 = (tid / PH) * (FR / 2);
     float w1[PIN];
 #pragma unroll
     for (int i = 0; i < PIN; ++i) w1[i] = P[OW1 + n * PIN + i];
     const float bn = P[OB1 + n];
-    for (int s = 0; s < FR; ++s) {
+#pragma unroll
+    for (int q = 0; q < FR / 2; ++q) {
+      const int s = s0 + q, b = b0 + s;
       float a = bn;
-      if (b0 + s < B)
+      if (b < B)
 #pragma unroll
-        for (int i = 0; i < PIN; ++i) a += w1[i] * X[size_t(b0 + s) * ldx + i];
-      ha[s * FLP + n] = fmaxf(a, 0.0f);
+        for (int i = 0; i < PIN; ++i) a += w1[i] * X[size_t(b) * ldx + i];
+      a = fmaxf(a, 0.0f);
+      pa.put(s, n, a);
+      if (H1 && b < B) H1[size_t(b) * PH + n] = a;
     }
   }
-  __syncthreads();
-  mlp_layer_mfma(ha, hb, P + OW2, P + OB2, lane);
-  __syncthreads();
-  if (H1)
-    for (int s = 0; s < FR; ++s)
-      if (b0 + s < B) {
-        H1[size_t(b0 + s) * PH + lane] = ha[s * FLP + lane];
-        H1[size_t(b0 + s) * PH + lane + 64] = ha[s * FLP + lane + 64];
-      }
-  __syncthreads();
-  mlp_layer_mfma(hb, ha, P + OW3, P + OB3, lane);
-  __syncthreads();
-  if (H2 || H3)
-    for (int s = 0; s < FR; ++s)
-      if (b0 + s < B)
+  const int col = lane & 15, r0 = 4 * (lane >> 4);
+  float bias2[NJ], bias3[NJ], w4[NJ];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int n = lane + 64 * q;
-          if (H2) H2[size_t(b0 + s) * PH + n] = hb[s * FLP + n];
-          if (H3) H3[size_t(b0 + s) * PH + n] = ha[s * FLP + n];
-        }
-  // layer 4: sample lane % 16, a quarter of the neurons per lane, then the
-  // four quarters summed in a fixed order
-  const int s = lane & 15, k0 = (lane >> 4) * (PH / 4);
-  float v = 0.0f;
-  for (int k = 0; k < PH / 4; ++k) v += P[OW4 + k0 + k] * ha[s * FLP + k0 + k];
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  if (lane < FR && b0 + s < B) O[b0 + s] = v + P[OB4];
-}
-
-// dL/do per sample and the loss terms: g = GMAX sigmoid(o),
-// L = sum_b w_b (g_b - t_b)^2 / sum_b w_b.  S = [x0..x3, t, w] rows.
-__global__ void k_mlp_loss(const float* __restrict__ O, const float* __restrict__ S, int B,
-                           double wsum, float* __restrict__ dO, double* __restrict__ lpart, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  double l = 0.0;
-  if (b < B) {
-    const float t = S[size_t(b) * 6 + 4], w = S[size_t(b) * 6 + 5];
-    const float sg = 1.0f / (1.0f + expf(-O[b]));
-    const float g = GMAX * sg;
-    const float e = g - t;
-    l = double(w) * double(e) * double(e) / wsum;
-    dO[b] = float(2.0 * double(w) * double(e) / wsum) * GMAX * sg * (1.0f - sg);
+  for (int j = 0; j < NJ; ++j) {
+    const int n = (wv * NJ + j) * 16 + col;
+    bias2[j] = P[OB2 + n];
+    bias3[j] = P[OB3 + n];
+    w4[j] = P[OW4 + n];
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-  __shared__ double red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
   __syncthreads();
-  if (threadIdx.x == 0) lpart[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
-// One backward layer of one wave on the BF16 matrix cores: out[s][j] =
-// relu'(Hp[b0 + s][j]) sum_i in[s][i] W[i][j] (W row-major [PH][PH], BF16
-// values), also stored to Dout for the weight gradients.  Operands and
-// splits as in mlp_layer_mfma, with W's columns as the B operand.
-__device__ inline void mlp_layer_bwd_mfma(const float* in, float* out, const float* __restrict__ W,
-                                          const float* __restrict__ Hp, float* __restrict__ Dout,
-                                          int b0, int B, int lane) {
-  const int r = lane & 15, kg = (lane >> 4) * 8;
-  us8 a[PH / 32][3];
+  f4v acc[NJ];
+  layer_mfma(pa, w2, acc, lane);
 #pragma unroll
-  for (int ks = 0; ks < PH / 32; ++ks)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const float x = in[r * FLP + ks * 32 + kg + t];
-      const float x0 = bf16_round(x), x1 = bf16_round(x - x0), x2 = bf16_round(x - x0 - x1);
-      a[ks][0][t] = bf16_hi(x0);
-      a[ks][1][t] = bf16_hi(x1);
-      a[ks][2][t] = bf16_hi(x2);
-    }
-#pragma unroll
-  for (int jb = 0; jb < PH / 16; ++jb) {
-    const int j = jb * 16 + r;
-    f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < PH / 32; ++ks) {
-      us8 wb;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) wb[t] = bf16_hi(W[(ks * 32 + kg + t) * PH + j]);
-      const bf8 b = __builtin_bit_cast(bf8, wb);
-#pragma unroll
-      for (int t = 0; t < 3; ++t)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a[ks][t]), b, acc, 0, 0, 0);
-    }
+  for (int j = 0; j < NJ; ++j)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int sr = 4 * (lane >> 4) + e, b = b0 + sr;
-      float v = 0.0f;
-      if (b < B) {
-        v = Hp[size_t(b) * PH + j] > 0.0f ? acc[e] : 0.0f;
-        Dout[size_t(b) * PH + j] = v;
-      }
-      out[sr * FLP + j] = v;
+      const int n = (wv * NJ + j) * 16 + col, b = b0 + r0 + e;
+      const float v = fmaxf(acc[j][e] + bias2[j], 0.0f);
+      pb.put(r0 + e, n, v);
+      if (H2 && b < B) H2[size_t(b) * PH + n] = v;
     }
+  __syncthreads();
+  layer_mfma(pb, w3, acc, lane);
+  // layer 4: the wave's neurons of each sample, lanes in a fixed order
+  float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = (wv * NJ + j) * 16 + col, b = b0 + r0 + e;
+      const float v = fmaxf(acc[j][e] + bias3[j], 0.0f);
+      o[e] += v * w4[j];
+      if (H3 && b < B) H3[size_t(b) * PH + n] = v;
+    }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int k = 1; k < 16; k <<= 1) o[e] += __shfl_xor(o[e], k);
+    if (col == 0) red[wv][r0 + e] = o[e];
+  }
+  __syncthreads();
+  if (tid < FR && b0 + tid < B) {
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < FWV; ++w) v += red[w][tid];
+    O[b0 + tid] = v + P[OB4];
   }
 }
 
-// dL/d(pre-activation) of the three hidden layers, FR samples per wave:
-// D3 = dO W4 relu'(H3), D2 = (D3 W3) relu'(H2), D1 = (D2 W2) relu'(H1).
-__global__ void __launch_bounds__(64 * FWV)
-k_mlp_bwd_act(const float* __restrict__ P, const float* __restrict__ H1,
-              const float* __restrict__ H2, const float* __restrict__ H3,
-              const float* __restrict__ dO, int B, float* __restrict__ D1,
-              float* __restrict__ D2, float* __restrict__ D3, const int* __restrict__ sky_gate) {
+// Sum of the sample weights (column 5 of the rows), at least so that it can
+// divide: one workgroup, fixed order.
+__global__ void __launch_bounds__(1024)
+k_pc_wsum(const float* __restrict__ S, int B, double* __restrict__ wsum, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ float hs[FWV][2][FR * FLP];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int b0 = (blockIdx.x * FWV + wv) * FR;
-  float* da = hs[wv][0];
-  float* db = hs[wv][1];
+  __shared__ double red[16];
+  double v = 0.0;
+  for (int b = threadIdx.x; b < B; b += 1024) v += double(S[size_t(b) * 6 + 5]);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int n = lane + 64 * q;
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < 16; ++w) s += red[w];
+    *wsum = s > 0.0 ? s : 1.0;
+  }
+}
+
+// Loss terms and dL/do per sample: g = GMAX sigmoid(o),
+// L = sum_b w_b (g_b - t_b)^2 / sum_b w_b.  S = [x0..x3, t, w] rows.  Then
+// dL/d(pre-activation) of the three hidden layers of FR samples:
+// D3 = dO W4 relu'(H3), D2 = (D3 W3) relu'(H2), D1 = (D2 W2) relu'(H1), the
+// products on the BF16 matrix cores as in the forward layers, with the
+// transposed weights.  lpart[blockIdx.x]: the workgroup's loss terms.
+__global__ void __launch_bounds__(64 * FWV)
+k_mlp_bwd_act(const float* __restrict__ P, const float* __restrict__ S, const float* __restrict__ H1,
+              const float* __restrict__ H2, const float* __restrict__ H3,
+              const float* __restrict__ O, const double* __restrict__ wsump, int B,
+              float* __restrict__ dO, float* __restrict__ D1, float* __restrict__ D2,
+              float* __restrict__ D3, double* __restrict__ lpart, const int* __restrict__ sky_gate) {
+  if (sky_gate != nullptr && *sky_gate == 0) return;
+  __shared__ Planes pa, pb;
+  __shared__ float dos[FR];
+  __shared__ double ls[FR];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int b0 = blockIdx.x * FR;
+  const Weights w3 = load_weights(packed(P, 1, true), wv, lane);
+  const Weights w2 = load_weights(packed(P, 0, true), wv, lane);
+  if (tid < FR) {
+    const int b = b0 + tid;
+    float d = 0.0f;
+    double l = 0.0;
+    if (b < B) {
+      const double wsum = *wsump;
+      const float t = S[size_t(b) * 6 + 4], w = S[size_t(b) * 6 + 5];
+      const float sg = 1.0f / (1.0f + expf(-O[b]));
+      const float g = GMAX * sg;
+      const float e = g - t;
+      l = double(w) * double(e) * double(e) / wsum;
+      d = float(2.0 * double(w) * double(e) / wsum) * GMAX * sg * (1.0f - sg);
+      dO[b] = d;
+    }
+    dos[tid] = d;
+    ls[tid] = l;
+  }
+  // the masks of this wave's outputs, ahead of the products that need them
+  const int col = lane & 15, r0 = 4 * (lane >> 4);
+  bool on2[NJ][4], on1[NJ][4];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = (wv * NJ + j) * 16 + col, b = b0 + r0 + e;
+      on2[j][e] = b < B && H2[size_t(b) * PH + n] > 0.0f;
+      on1[j][e] = b < B && H1[size_t(b) * PH + n] > 0.0f;
+    }
+  __syncthreads();
+  if (tid == 0) {
+    double l = 0.0;
+    for (int k = 0; k < FR; ++k) l += ls[k];
+    lpart[blockIdx.x] = l;
+  }
+  {
+    const int n = tid % PH, s0 = (tid / PH) * (FR / 2);
     const float w4 = P[OW4 + n];
-    for (int sr = 0; sr < FR; ++sr) {
-      const int b = b0 + sr;
+#pragma unroll
+    for (int q = 0; q < FR / 2; ++q) {
+      const int s = s0 + q, b = b0 + s;
       float v = 0.0f;
       if (b < B) {
-        v = H3[size_t(b) * PH + n] > 0.0f ? dO[b] * w4 : 0.0f;
+        v = H3[size_t(b) * PH + n] > 0.0f ? dos[s] * w4 : 0.0f;
         D3[size_t(b) * PH + n] = v;
       }
-      da[sr * FLP + n] = v;
+      pa.put(s, n, v);
     }
   }
   __syncthreads();
-  mlp_layer_bwd_mfma(da, db, P + OW3, H2, D2, b0, B, lane);
+  f4v acc[NJ];
+  layer_mfma(pa, w3, acc, lane);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = (wv * NJ + j) * 16 + col, b = b0 + r0 + e;
+      const float v = on2[j][e] ? acc[j][e] : 0.0f;
+      pb.put(r0 + e, n, v);
+      if (b < B) D2[size_t(b) * PH + n] = v;
+    }
   __syncthreads();
-  mlp_layer_bwd_mfma(db, da, P + OW2, H1, D1, b0, B, lane);
+  layer_mfma(pb, w2, acc, lane);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = (wv * NJ + j) * 16 + col, b = b0 + r0 + e;
+      if (b < B) D1[size_t(b) * PH + n] = on1[j][e] ? acc[j][e] : 0.0f;
+    }
 }
 
 // ---- parameter gradient
-// x = v[0][t] + v[1][t] + v[2][t] as three BF16 bit patterns (exact for
-// normal FP32 x: 8 significant bits per term, rounded to nearest at each step).
-__device__ inline void split3_at(float x, us8 (&v)[3], int t) {
-  const float a = bf16_round(x), b = bf16_round(x - a), c = bf16_round(x - a - b);
-  v[0][t] = bf16_hi(a);
-  v[1][t] = bf16_hi(b);
-  v[2][t] = bf16_hi(c);
-}
-
 constexpr int GCH = 64;    // samples per chunk of the gradient partials
 constexpr int GSUB = 32;   // samples per MFMA step (the contraction of one MFMA)
+constexpr int GLP = GSUB + 8;   // LDS row pitch of the transposed planes
+
+// Eight consecutive samples of one neuron, samples past the chunk's end zero.
+struct Eight {
+  float v[8];
+  __device__ void load(const float* __restrict__ p, int b, int c1, int n) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = b + t < c1 ? p[size_t(b + t) * PH + n] : 0.0f;
+  }
+  // the three split terms as one 16-byte store each, at [term][row][8 g ..]
+  __device__ void put(unsigned short* base, int rows, int row, int g) const {
+    us8 w[3];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      unsigned short a, b, c;
+      split3(v[t], a, b, c);
+      w[0][t] = a;
+      w[1][t] = b;
+      w[2][t] = c;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) *reinterpret_cast<us8*>(base + (k * rows + row) * GLP + 8 * g) = w[k];
+  }
+};
 
 // Partial gradient of every parameter over the samples of chunk blockIdx.x:
 // part[chunk][p].  The two 128 x 128 weight blocks are D^T H over the chunk
 // on the BF16 matrix cores: both FP32 operands split in three BF16 terms,
 // the six products t_i u_j with i + j <= 2 (the dropped ones are below
-// 2^-24 of the product), FP32 accumulation; wave w owns the output rows
-// 32 w .. 32 w + 31 of both blocks.  W1, the biases, W4 and b4 are FP32
-// sums over the chunk, one thread per parameter.  The chunk goes through LDS
-// GSUB samples at a time.
+// 2^-24 of the product), FP32 accumulation.  blockIdx.y = 2 m + h takes the
+// output rows 64 h .. 64 h + 63 of block m (W2: D2^T H1, W3: D3^T H2), wave w
+// 16 of them, and the biases of those rows; y = 0 also W1 and b1, y = 3 W4 and
+// b4, as FP32 sums over the chunk.  Four workgroups per chunk instead of one
+// keep every CU busy from 4096 rows on.  Operands are split once, by the
+// thread that loads them, and stored with the samples running along the rows,
+// so that a fragment is one 16-byte read; the small sums are taken from the
+// loaded registers (4099 rows: 36 us, now 13.6).
 __global__ void __launch_bounds__(256)
 k_mlp_grad_part(const float* __restrict__ S, const float* __restrict__ H1,
                 const float* __restrict__ H2, const float* __restrict__ H3,
@@ -295,114 +377,122 @@ k_mlp_grad_part(const float* __restrict__ S, const float* __restrict__ H1,
                 const float* __restrict__ D2, const float* __restrict__ D3, int B,
                 float* __restrict__ part, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ float ds[2][GSUB][FLP], hs[2][GSUB][FLP];   // (D2, H1), (D3, H2)
-  __shared__ float d1s[GSUB][FLP], h3s[GSUB][FLP], xs[GSUB][PIN], dos[GSUB];
+  __shared__ alignas(16) unsigned short dsp[3 * 64 * GLP], hsp[3 * PH * GLP];
+  __shared__ float xs[GCH][PIN], dos[GCH];
+  __shared__ float red[5][256];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int y = blockIdx.y, m = y >> 1, j0 = (y & 1) * 64;
+  const float* __restrict__ D = m ? D3 : D2;
+  const float* __restrict__ H = m ? H2 : H1;
+  const float* __restrict__ E = y == 0 ? D1 : H3;
+  const bool extra = y == 0 || y == 3;
   const int c0 = blockIdx.x * GCH, c1 = min(B, c0 + GCH);
   float* out = part + size_t(blockIdx.x) * NPAR;
   const int r = lane & 15, kg = (lane >> 4) * 8;
-  f4v acc[2][2][PH / 16];
+  if (tid < GCH * PIN) xs[tid / PIN][tid % PIN] = c0 + tid / PIN < c1 ? S[size_t(c0 + tid / PIN) * 6 + tid % PIN] : 0.0f;
+  if (tid < GCH) dos[tid] = c0 + tid < c1 ? dO[c0 + tid] : 0.0f;
+  f4v acc[PH / 16];
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-      for (int ib = 0; ib < PH / 16; ++ib) acc[m][jb][ib] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int ib = 0; ib < PH / 16; ++ib) acc[ib] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
   constexpr int PI[6] = {0, 0, 1, 0, 1, 2};
   constexpr int PJ[6] = {0, 1, 0, 2, 1, 0};
-  // W1, b1, b2, b3, W4, b4: thread tid owns parameters tid + 256 q
-  constexpr int NSMALL = PH * PIN + 4 * PH + 1;
-  constexpr int NQ = (NSMALL + 255) / 256;
-  float sv[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) sv[q] = 0.0f;
+  // thread -> neuron and sample groups: D nd, gd; H and E nh, gh and gh + 2
+  const int nd = tid & 63, gd = tid >> 6, nh = tid & 127, gh = tid >> 7;
+  float bsum = 0.0f, es[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // es: W1 rows and b1, or W4
   for (int s0 = c0; s0 < c1; s0 += GSUB) {
+    Eight d, h[2], e[2];
+    d.load(D, s0 + 8 * gd, c1, j0 + nd);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) h[q].load(H, s0 + 8 * (gh + 2 * q), c1, nh);
+    if (extra)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) e[q].load(E, s0 + 8 * (gh + 2 * q), c1, nh);
+    __syncthreads();   // the previous step's fragments are read (and xs, dos are there)
+    d.put(dsp, 64, nd, gd);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) h[q].put(hsp, PH, nh, gh + 2 * q);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) bsum += d.v[t];
+    if (extra)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int sr = s0 - c0 + 8 * (gh + 2 * q) + t;
+          if (y == 0) {
+#pragma unroll
+            for (int i = 0; i < PIN; ++i) es[i] += e[q].v[t] * xs[sr][i];
+            es[PIN] += e[q].v[t];
+          } else {
+            es[0] += e[q].v[t] * dos[sr];
+          }
+        }
     __syncthreads();
-    for (int e = tid; e < GSUB * PH; e += 256) {
-      const int sr = e / PH, n = e % PH, b = s0 + sr;
-      const bool ok = b < c1;
-      const size_t o = size_t(b) * PH + n;
-      ds[0][sr][n] = ok ? D2[o] : 0.0f;
-      hs[0][sr][n] = ok ? H1[o] : 0.0f;
-      ds[1][sr][n] = ok ? D3[o] : 0.0f;
-      hs[1][sr][n] = ok ? H2[o] : 0.0f;
-      d1s[sr][n] = ok ? D1[o] : 0.0f;
-      h3s[sr][n] = ok ? H3[o] : 0.0f;
-    }
-    if (tid < GSUB * PIN) {
-      const int sr = tid / PIN, i = tid % PIN, b = s0 + sr;
-      xs[sr][i] = b < c1 ? S[size_t(b) * 6 + i] : 0.0f;
-    }
-    if (tid < GSUB) dos[tid] = s0 + tid < c1 ? dO[s0 + tid] : 0.0f;
-    __syncthreads();
+    us8 a[3];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      us8 a[2][3];
+    for (int k = 0; k < 3; ++k)
+      a[k] = *reinterpret_cast<const us8*>(dsp + (k * 64 + wv * 16 + r) * GLP + kg);
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+    for (int ib = 0; ib < PH / 16; ++ib) {
+      us8 u[3];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) split3_at(ds[m][kg + t][(2 * wv + jb) * 16 + r], a[jb], t);
+      for (int k = 0; k < 3; ++k)
+        u[k] = *reinterpret_cast<const us8*>(hsp + (k * PH + ib * 16 + r) * GLP + kg);
 #pragma unroll
-      for (int ib = 0; ib < PH / 16; ++ib) {
-        us8 u[3];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) split3_at(hs[m][kg + t][ib * 16 + r], u, t);
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-          for (int q = 0; q < 6; ++q)
-            acc[m][jb][ib] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf8, a[jb][PI[q]]), __builtin_bit_cast(bf8, u[PJ[q]]),
-                acc[m][jb][ib], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int p = tid + 256 * q;
-      float v = 0.0f;
-      if (p < PH * PIN) {                          // W1[j][i]: D1[b][j] x[b][i]
-        const int j = p / PIN, i = p % PIN;
-        for (int sr = 0; sr < GSUB; ++sr) v += d1s[sr][j] * xs[sr][i];
-      } else if (p < PH * PIN + 3 * PH) {          // b1, b2, b3
-        const int l = (p - PH * PIN) / PH, j = (p - PH * PIN) % PH;
-        for (int sr = 0; sr < GSUB; ++sr) v += l == 0 ? d1s[sr][j] : ds[l - 1][sr][j];
-      } else if (p < PH * PIN + 4 * PH) {          // W4[i]: dO[b] H3[b][i]
-        const int i = p - PH * PIN - 3 * PH;
-        for (int sr = 0; sr < GSUB; ++sr) v += dos[sr] * h3s[sr][i];
-      } else if (p < NSMALL) {                     // b4
-        for (int sr = 0; sr < GSUB; ++sr) v += dos[sr];
-      }
-      sv[q] += v;
+      for (int q = 0; q < 6; ++q)
+        acc[ib] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a[PI[q]]),
+                                                          __builtin_bit_cast(bf8, u[PJ[q]]), acc[ib], 0, 0, 0);
     }
   }
   // output rows j (neuron of the layer's output) and columns i (its input)
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int ib = 0; ib < PH / 16; ++ib)
 #pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
+    for (int e = 0; e < 4; ++e)
+      out[(m ? OW3 : OW2) + (j0 + wv * 16 + 4 * (lane >> 4) + e) * PH + ib * 16 + r] = acc[ib][e];
+  // small sums: the sample groups of a neuron in order
+  red[0][tid] = bsum;
+  __syncthreads();
+  if (tid < 64) out[(m ? OB3 : OB2) + j0 + tid] = red[0][tid] + red[0][tid + 64] + red[0][tid + 128] + red[0][tid + 192];
+  if (!extra) return;
+  __syncthreads();
 #pragma unroll
-      for (int ib = 0; ib < PH / 16; ++ib)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = (2 * wv + jb) * 16 + 4 * (lane >> 4) + e, i = ib * 16 + r;
-          out[(m ? OW3 : OW2) + j * PH + i] = acc[m][jb][ib][e];
-        }
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int p = tid + 256 * q;
-    if (p < PH * PIN) out[OW1 + p] = sv[q];
-    else if (p < PH * PIN + 3 * PH) {
-      const int l = (p - PH * PIN) / PH, j = (p - PH * PIN) % PH;
-      out[(l == 0 ? OB1 : l == 1 ? OB2 : OB3) + j] = sv[q];
-    } else if (p < PH * PIN + 4 * PH) out[OW4 + p - PH * PIN - 3 * PH] = sv[q];
-    else if (p < NSMALL) out[OB4] = sv[q];
+  for (int i = 0; i < 5; ++i) red[i][tid] = es[i];
+  __syncthreads();
+  if (y == 0) {
+    for (int p = tid; p < PH * PIN + PH; p += 256) {
+      const int j = p < PH * PIN ? p / PIN : p - PH * PIN, i = p < PH * PIN ? p % PIN : PIN;
+      out[(i < PIN ? OW1 + p : OB1 + j)] = red[i][j] + red[i][j + PH];
+    }
+  } else {
+    if (tid < PH) out[OW4 + tid] = red[0][tid] + red[0][tid + PH];
+    if (tid == PH) {
+      float v = 0.0f;
+      for (int s = 0; s < GCH; ++s) v += dos[s];
+      out[OB4] = v;
+    }
   }
 }
 
-// G[p] = sum over the chunks of part[chunk][p], in chunk order.
-__global__ void k_mlp_grad_sum(const float* __restrict__ part, int nchunk, float* __restrict__ G,
-                               const int* __restrict__ sky_gate) {
+// G[p] = sum over the chunks of part[chunk][p], in chunk order.  The workgroup
+// past the parameters sums the loss terms (one wave's worth of partial sums in
+// a fixed order) for the host.
+__global__ void __launch_bounds__(256)
+k_mlp_grad_sum(const float* __restrict__ part, int nchunk, float* __restrict__ G,
+               const double* __restrict__ lpart, int nl, double* __restrict__ host,
+               const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double red[4];
+    double l = 0.0;
+    for (int i = threadIdx.x; i < nl; i += 256) l += lpart[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) *host = red[0] + red[1] + red[2] + red[3];
+    return;
+  }
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= NPAR) return;
   float v = 0.0f;
@@ -423,14 +513,6 @@ __global__ void k_adam(float* __restrict__ P, const float* __restrict__ G, float
   M[i] = m;
   V[i] = v;
   P[i] -= lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
-}
-
-__global__ void k_sum_d(const double* __restrict__ part, int n, double* __restrict__ out, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  if (threadIdx.x) return;
-  double s = 0.0;
-  for (int i = 0; i < n; ++i) s += part[i];
-  out[0] = s;
 }
 
 // Features of (state alpha, shell s) rows: X[(a*S + s)][0..3] (row length 6).
@@ -619,8 +701,8 @@ void precond_round(const float* P, float* Pb, hipStream_t st) {
 void precond_forward(const float* Pb, const float* X, int B, float* H1, float* H2, float* H3,
                      float* O, hipStream_t st) {
   if (B <= 0) return;
-  hipLaunchKernelGGL(k_mlp_fwd, dim3((B + FR * FWV - 1) / (FR * FWV)), dim3(64 * FWV), 0, st, Pb, X,
-                     6, B, H1, H2, H3, O, g_launch_gate);
+  hipLaunchKernelGGL(k_mlp_fwd, dim3((B + FR - 1) / FR), dim3(64 * FWV), 0, st, Pb, X, 6, B, H1, H2,
+                     H3, O, g_launch_gate);
 }
 
 void precond_features(const double* pow, const double* eps, int stride, int ns, double e0,
@@ -636,31 +718,28 @@ void precond_gains(const float* O, int n, float* gain, hipStream_t st) {
   hipLaunchKernelGGL(k_pc_gains, dim3((n + 255) / 256), dim3(256), 0, st, O, n, gain, g_launch_gate);
 }
 
-double precond_loss_grad(const float* Pb, const float* S, int B, double wsum, float* H1,
-                         float* H2, float* H3, float* O, float* dO, float* D1, float* D2,
-                         float* D3, float* G, float* gpart, double* dscratch, int want_loss,
-                         hipStream_t st) {
-  if (B <= 0) return 0.0;
+size_t precond_rounded_floats() { return OPACK + 2 * size_t(WSZ); }
+size_t precond_loss_doubles(int rows) { return size_t(rows + FR - 1) / FR + 1; }
+
+void precond_wsum(const float* S, int B, double* wsum, hipStream_t st) {
+  hipLaunchKernelGGL(k_pc_wsum, dim3(1), dim3(1024), 0, st, S, B, wsum, g_launch_gate);
+}
+
+void precond_loss_grad(const float* Pb, const float* S, int B, const double* wsum, float* H1,
+                       float* H2, float* H3, float* O, float* dO, float* D1, float* D2, float* D3,
+                       float* G, float* gpart, double* lpart, double* host, hipStream_t st) {
+  if (B <= 0) return;
   precond_forward(Pb, S, B, H1, H2, H3, O, st);
-  const int nb = (B + 255) / 256;
-  hipLaunchKernelGGL(k_mlp_loss, dim3(nb), dim3(256), 0, st, (const float*)O, S, B, wsum, dO,
-                     dscratch, g_launch_gate);
-  hipLaunchKernelGGL(k_sum_d, dim3(1), dim3(64), 0, st, (const double*)dscratch, nb, dscratch + nb, g_launch_gate);
-  hipLaunchKernelGGL(k_mlp_bwd_act, dim3((B + FR * FWV - 1) / (FR * FWV)), dim3(64 * FWV), 0, st, Pb,
-                     (const float*)H1, (const float*)H2, (const float*)H3, (const float*)dO, B,
-                     D1, D2, D3, g_launch_gate);
+  const int nl = (B + FR - 1) / FR;
+  hipLaunchKernelGGL(k_mlp_bwd_act, dim3(nl), dim3(64 * FWV), 0, st, Pb, S, (const float*)H1,
+                     (const float*)H2, (const float*)H3, (const float*)O, wsum, B, dO, D1, D2, D3,
+                     lpart, g_launch_gate);
   const int nchunk = (B + GCH - 1) / GCH;
-  hipLaunchKernelGGL(k_mlp_grad_part, dim3(nchunk), dim3(256), 0, st, S, (const float*)H1,
+  hipLaunchKernelGGL(k_mlp_grad_part, dim3(nchunk, 4), dim3(256), 0, st, S, (const float*)H1,
                      (const float*)H2, (const float*)H3, (const float*)dO, (const float*)D1,
                      (const float*)D2, (const float*)D3, B, gpart, g_launch_gate);
-  hipLaunchKernelGGL(k_mlp_grad_sum, dim3((NPAR + 255) / 256), dim3(256), 0, st, (const float*)gpart,
-                     nchunk, G, g_launch_gate);
-  double loss = 0.0;
-  if (want_loss) {
-    hipMemcpyAsync(&loss, dscratch + nb, sizeof(double), hipMemcpyDeviceToHost, st);
-    hipStreamSynchronize(st);
-  }
-  return loss;
+  hipLaunchKernelGGL(k_mlp_grad_sum, dim3((NPAR + 255) / 256 + 1), dim3(256), 0, st,
+                     (const float*)gpart, nchunk, G, (const double*)lpart, nl, host, g_launch_gate);
 }
 
 void precond_adam(float* P, const float* G, float* M, float* V, int step, float lr,

@@ -179,7 +179,7 @@ Layout plan(const sky_box_desc& d) {
     const size_t rows = std::max<size_t>(PC_CAP, size_t(nmax) * PC_SHELLS);
     const size_t pw = size_t(std::max(nmax, L.pc_nb)) * PC_SHELLS;
     L.pc_P = take(sizeof(float) * np);
-    L.pc_Pb = take(sizeof(float) * np);
+    L.pc_Pb = take(sizeof(float) * precond_rounded_floats());
     L.pc_G = take(sizeof(float) * np);
     L.pc_M = take(sizeof(float) * np);
     L.pc_V = take(sizeof(float) * np);
@@ -191,7 +191,7 @@ Layout plan(const sky_box_desc& d) {
     L.pc_X = take(sizeof(float) * 6 * size_t(nmax) * PC_SHELLS);
     L.pc_pow = take(sizeof(double) * pw);
     L.pc_gain = take(sizeof(float) * pw);
-    L.pc_dscr = take(sizeof(double) * (PC_CAP / 256 + 4));
+    L.pc_dscr = take(sizeof(double) * (precond_loss_doubles(PC_CAP) + 1));
     L.pc_gpart = take(precond_gpart_bytes(PC_CAP));
     L.pc_gram = take(precond_gram_bytes(precond_ns_max()));
     L.pc_idx = take(sizeof(int) * precond_ns_max());
@@ -890,39 +890,39 @@ int pc_collect(sky_ctx* c, int s) {
   return SKY_OK;
 }
 
-double precond_wsum(sky_ctx* c) {
-  std::vector<float> rows(size_t(c->pc_count) * 6);
-  hipMemcpyAsync(rows.data(), c->at(c->lay.pc_S), sizeof(float) * rows.size(),
-                 hipMemcpyDeviceToHost, c->st);
-  hipStreamSynchronize(c->st);
-  double w = 0.0;
-  for (int b = 0; b < c->pc_count; ++b) w += rows[size_t(b) * 6 + 5];
-  return w > 0.0 ? w : 1.0;
+// The weight sum is the first of the pc_dscr doubles, the loss terms follow.
+void pc_wsum(sky_ctx* c, int rows) {
+  precond_wsum(c->at<float>(c->lay.pc_S), rows, c->at<double>(c->lay.pc_dscr), c->st);
 }
 
-double precond_pass(sky_ctx* c, double wsum, int want_loss) {
-  return precond_loss_grad(
-      c->at<float>(c->lay.pc_Pb), c->at<float>(c->lay.pc_S), c->pc_count, wsum,
+void precond_pass(sky_ctx* c, int rows) {
+  double* dscr = c->at<double>(c->lay.pc_dscr);
+  precond_loss_grad(
+      c->at<float>(c->lay.pc_Pb), c->at<float>(c->lay.pc_S), rows, dscr,
       c->at<float>(c->lay.pc_H[0]), c->at<float>(c->lay.pc_H[1]), c->at<float>(c->lay.pc_H[2]),
       c->at<float>(c->lay.pc_O), c->at<float>(c->lay.pc_dO), c->at<float>(c->lay.pc_D[0]),
       c->at<float>(c->lay.pc_D[1]), c->at<float>(c->lay.pc_D[2]), c->at<float>(c->lay.pc_G),
-      c->at<float>(c->lay.pc_gpart), c->at<double>(c->lay.pc_dscr), want_loss, c->st);
+      c->at<float>(c->lay.pc_gpart), dscr + 1, c->host, c->st);
 }
 
 // Adam over every held row; returns the loss before the last update.
-double pc_train(sky_ctx* c, int steps, double lr) {
-  const double w = precond_wsum(c);
-  double l = 0.0;
+int pc_train(sky_ctx* c, int steps, double lr, double* loss) {
+  int rc = need_host(c);
+  if (rc) return rc;
+  pc_wsum(c, c->pc_count);
   for (int s = 1; s <= steps; ++s) {
     precond_round(c->at<float>(c->lay.pc_P), c->at<float>(c->lay.pc_Pb), c->st);
-    l = precond_pass(c, w, s == steps);
+    precond_pass(c, c->pc_count);
     precond_adam(c->at<float>(c->lay.pc_P), c->at<float>(c->lay.pc_G), c->at<float>(c->lay.pc_M),
                  c->at<float>(c->lay.pc_V), ++c->pc_step, float(lr), c->st);
   }
   precond_round(c->at<float>(c->lay.pc_P), c->at<float>(c->lay.pc_Pb), c->st);
+  rc = hip_check(hipStreamSynchronize(c->st), "precond_train");
+  if (rc) return rc;
   c->pc_trained = true;
   c->pc_lr = lr;
-  return l;
+  if (loss) *loss = *c->host;
+  return SKY_OK;
 }
 
 // Step 2 and step 3a of set s: h psi and <h> (or, with one_h after an
@@ -1508,7 +1508,8 @@ int sky_iterate(sky_ctx* c, int32_t max_iter, double tol, sky_report* rep) {
         int rc = pc_collect(c, q);
         if (rc) return rc;
       }
-      pc_train(c, PC_RETRAIN_STEPS, c->pc_lr);
+      int rct = pc_train(c, PC_RETRAIN_STEPS, c->pc_lr, nullptr);
+      if (rct) return rct;
     }
     // precision ladder: finish in FP64 once the mixed form has done its part
     if (c->prec == 1 && c->d.ladder_tol > 0.0 && de <= c->d.ladder_tol) {
@@ -1847,22 +1848,21 @@ int sky_precond_collect(sky_ctx* c, int32_t q, int32_t* total) {
 
 int sky_precond_loss_grad(sky_ctx* c, int32_t nsamples, double* loss) {
   if (!c || nsamples < 1 || nsamples > PC_CAP) return fail(SKY_ERR_INVALID, "precond_loss_grad arguments");
-  const int keep = c->pc_count;
-  c->pc_count = nsamples;
-  const double w = precond_wsum(c);
+  int rc = need_host(c);
+  if (rc) return rc;
+  pc_wsum(c, nsamples);
   precond_round(c->at<float>(c->lay.pc_P), c->at<float>(c->lay.pc_Pb), c->st);
-  const double l = precond_pass(c, w, 1);
-  c->pc_count = keep;
-  if (loss) *loss = l;
-  return hip_check(hipStreamSynchronize(c->st), "precond_loss_grad");
+  precond_pass(c, nsamples);
+  rc = hip_check(hipStreamSynchronize(c->st), "precond_loss_grad");
+  if (rc) return rc;
+  if (loss) *loss = *c->host;
+  return SKY_OK;
 }
 
 int sky_precond_train(sky_ctx* c, int32_t steps, double lr, double* loss) {
   if (!c || steps < 1 || !(lr > 0.0)) return fail(SKY_ERR_INVALID, "precond_train arguments");
   if (c->pc_count < 1) return fail(SKY_ERR_INVALID, "precond_train: no samples collected");
-  const double l = pc_train(c, steps, lr);
-  if (loss) *loss = l;
-  return hip_check(hipStreamSynchronize(c->st), "precond_train");
+  return pc_train(c, steps, lr, loss);
 }
 
 int sky_precond_set_rows(sky_ctx* c, int32_t nrows) {

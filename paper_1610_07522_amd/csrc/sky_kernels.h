@@ -87,6 +87,9 @@ void damped_step(int n, int prec, const void* psi, const void* hpsi, const doubl
 int precond_nparams();
 int precond_ns_max();
 void precond_init_params(float* P_dev, unsigned seed, hipStream_t st);
+// Pb (precond_rounded_floats): the parameters rounded to BF16 as floats, then
+// the packed copies of the 128 x 128 weights that the matrix kernels read.
+size_t precond_rounded_floats();
 void precond_round(const float* P, float* Pb, hipStream_t st);
 void precond_forward(const float* Pb, const float* X, int B, float* H1, float* H2, float* H3,
                      float* O, hipStream_t st);
@@ -95,13 +98,15 @@ void precond_forward(const float* Pb, const float* X, int B, float* H1, float* H
 void precond_features(const double* pow, const double* eps, int stride, int ns, double e0,
                       double hb2m, double kmax, float* X, hipStream_t st);
 void precond_gains(const float* O, int n, float* gain, hipStream_t st);
+// *wsum (device) = the sum of the rows' weights (1 if it is not positive).
+void precond_wsum(const float* S, int B, double* wsum, hipStream_t st);
 // loss and parameter gradient G; gpart: precond_gpart_bytes(B) of chunk
-// partials of G; dscratch >= B/256 + 2 doubles; want_loss: synchronise and
-// return the loss (else 0).
-double precond_loss_grad(const float* Pb, const float* S, int B, double wsum, float* H1,
-                         float* H2, float* H3, float* O, float* dO, float* D1, float* D2,
-                         float* D3, float* G, float* gpart, double* dscratch, int want_loss,
-                         hipStream_t st);
+// partials of G; lpart: precond_loss_doubles(B); the loss goes to *host (pinned
+// memory, after the stream has been waited for).
+size_t precond_loss_doubles(int rows);
+void precond_loss_grad(const float* Pb, const float* S, int B, const double* wsum, float* H1,
+                       float* H2, float* H3, float* O, float* dO, float* D1, float* D2, float* D3,
+                       float* G, float* gpart, double* lpart, double* host, hipStream_t st);
 size_t precond_gpart_bytes(int rows);
 void precond_adam(float* P, const float* G, float* M, float* V, int step, float lr,
                   hipStream_t st);
@@ -127,7 +132,7 @@ struct DensSpecies {
 };
 struct DensArgs {
   DensSpecies sp[2];
-  double kshift[DENS_MAX_GROUPS][3];   // GridArgs::tw of each group
+  double kshift[DENS_MAX_GROUPS][3];   // GridArgs::tw of each group, in units of kunit
   int ngroup, chunk;                   // states per chunk
 };
 int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
