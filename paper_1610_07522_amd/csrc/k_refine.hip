@@ -12,7 +12,7 @@
 //   lam_i = Re S_ii / (1 - Re R_ii);
 //   sort by lam; cut the sorted order into contiguous clusters so that every
 //   pair (i, j) in different clusters is weakly coupled,
-//   |S_ij + lam R_ij| <= THETA |lam_j - lam_i| (both orientations);
+//   |S_ij + lam R_ij| <= REF_THETA |lam_j - lam_i| (both orientations);
 //   diagonalise each cluster block of (1 + R/2) S (1 + R/2) exactly (cyclic
 //   Jacobi in one workgroup, unitary W_c; B = blockdiag(W_c) in sorted order);
 //   in the rotated basis (S2 = B^H S B, R2 = B^H R B, lam2 from its diagonal)
@@ -41,8 +41,6 @@ namespace {
 using namespace jrot;
 
 constexpr int KMAX = 48;            // widest cluster diagonalised in one workgroup (LDS: 3 x 48 x 49 x 16 B)
-constexpr double THETA = 0.03;      // weak-coupling ratio |coupling| / |gap|
-constexpr double E_CLAMP = 0.25;    // bound on one update coefficient
 constexpr int CHECK_BLOCKS = 256;
 
 // lam[i] = Re S_ii / (1 - Re R_ii)  (R may be null: R = 0); clears *emax.
@@ -123,7 +121,7 @@ k_ref_reach(const double2* __restrict__ S, const double2* __restrict__ R, const 
 // cluster found.
 // One workgroup of up to 1024 threads, a chunk of positions each; pm (m ints)
 // holds the prefix maximum.  The chunk maxima are scanned by shuffles (a
-// one-thread scan over 1024 chunks took 27 to 33 us, now CLUSTERS_US).
+// one-thread scan over 1024 chunks took 27 to 33 us, now 3 to 8).
 constexpr int CL_THREADS = 1024;
 
 // Inclusive maximum over the threads up to this one (buf: one int per wave);
@@ -395,7 +393,7 @@ k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int 
 // floor tau of the products is converged: it gets the orthonormality term
 // only.  (Its first-order coefficient would be rounding noise over a gap
 // that can itself be at rounding level, e.g. an exact Kramers pair, and would
-// rotate the pair at random by up to THETA on every step.)
+// rotate the pair at random by up to REF_THETA on every step.)
 __global__ void __launch_bounds__(256)
 k_ref_update(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
              const double* __restrict__ lam2, const double* __restrict__ taup,
@@ -422,7 +420,7 @@ k_ref_update(const double2* __restrict__ S, const double2* __restrict__ R, int m
       } else if (den != 0.0) {
         e = cscale(1.0 / den, gb);
         const double em = hypot(e.x, e.y);
-        if (em > E_CLAMP) e = cscale(E_CLAMP / em, e);
+        if (em > REF_E_CLAMP) e = cscale(REF_E_CLAMP / em, e);
       }
     }
     E[size_t(a) * m + b] = e;
@@ -500,7 +498,7 @@ k_ref_update_rows(const double2* __restrict__ S, const double2* __restrict__ R, 
       } else if (den != 0.0) {
         e = cscale(1.0 / den, gb);
         const double em = hypot(e.x, e.y);
-        if (em > E_CLAMP) e = cscale(E_CLAMP / em, e);
+        if (em > REF_E_CLAMP) e = cscale(REF_E_CLAMP / em, e);
       }
     }
     E[size_t(a) * m + b] = e;
@@ -746,6 +744,11 @@ size_t refine_scratch_bytes(int m) {
 int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const RefineTargets& tg,
                 int maxit, hipStream_t st, double* host, int sq_split) {
   if (m <= 0) return 0;
+  if (m <= SMALL_M) {
+    subspace_small(nullptr, Av, nullptr, nullptr, Z, nullptr, m, w, 0.0, 0.0, tg, maxit, st, host);
+    if (hipStreamSynchronize(st) != hipSuccess) return -1;
+    return int(host[1]);
+  }
   const double tol = tg.tol, noise = tg.noise, orth = tg.orth;
   RefineWork r = carve(work, m);
   const double2* A = static_cast<const double2*>(Av);
@@ -790,7 +793,7 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
     hipLaunchKernelGGL(k_ref_lambda, dim3(gm), dim3(256), 0, st, Sp, Rp, m, r.lam, r.emax, g_launch_gate);
     hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, (const double*)r.lam, m, r.rank, r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
-                       (const int*)r.rank, m, THETA, (const double*)tau, r.reach, g_launch_gate);
+                       (const int*)r.rank, m, REF_THETA, (const double*)tau, r.reach, g_launch_gate);
     hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
@@ -901,7 +904,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
     hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, (const double*)r.lam, m, r.rank,
                        r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
-                       (const int*)r.rank, m, THETA, (const double*)tau, r.reach, g_launch_gate);
+                       (const int*)r.rank, m, REF_THETA, (const double*)tau, r.reach, g_launch_gate);
     hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,

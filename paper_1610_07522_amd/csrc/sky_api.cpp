@@ -484,18 +484,39 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
   void* U = c->at(c->lay.matU);
   int* info = c->at<int>(c->lay.info);
   const int ts = t_begin(c, SKY_PHASE_SUBSPACE, q);
-  hipMemsetAsync(info, 0, sizeof(int), st);
   void* Cw = c->at(c->lay.matC);
   void* sq = c->at(c->lay.sq_part);
   const int sqs = c->tune.sq[q];
-  const int terms = loewdin_series(I, Linv, Cw, T, m, LOEWDIN_SERIES_MAX,
-                                   c->at<double>(c->lay.nrm), sq, st, c->host, sqs,
-                                   c->prec ? MIXED_SERIES_EPS : SERIES_EPS);
+  double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
+  const RefineTargets& tg = c->prec ? REFINE_MIXED : REFINE_FP64;
+  const double series_eps = c->prec ? MIXED_SERIES_EPS : SERIES_EPS;
+  // few states: the whole solve in one workgroup; its outcome sends what it
+  // did not finish down the general path (from H', or from I and H)
+  const bool small = subspace_small(I, H, Linv, Hp, Z, U, m, w, LOEWDIN_SERIES_MAX, series_eps, tg,
+                                    REFINE_ITERS, st, c->host);
+  int terms, its = -1;
+  if (small) {
+    const int rc = hip_check(hipStreamSynchronize(st), "subspace solve");
+    if (rc) return rc;
+    terms = int(c->host[0]);
+    its = int(c->host[1]);
+    if (its >= 0) {
+      c->last_sweeps += its;
+      t_end(c, ts);
+      return SKY_OK;
+    }
+  } else {
+    terms = loewdin_series(I, Linv, Cw, T, m, LOEWDIN_SERIES_MAX, c->at<double>(c->lay.nrm), sq, st,
+                           c->host, sqs, series_eps);
+  }
   if (terms < 0) return fail(SKY_ERR_NAN, "non-finite overlap matrix");
   if (terms > 0) {   // C = I^-1/2 (Hermitian) in Linv
-    gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
-    gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
+    if (!small) {
+      gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
+      gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
+    }
   } else {           // Linv = L^-1, C = L^-H
+    hipMemsetAsync(info, 0, sizeof(int), st);
     hipMemcpyAsync(Cw, I, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
     cholesky_inverse(Cw, Linv, m, c->at(c->lay.chol_work), info, st, CHOL_PIVOT_MIN);
     gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
@@ -505,9 +526,8 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
     int rc = check_info(c, "cholesky");
     if (rc) return rc;
   }
-  double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
-  int its = refine_eigh(Hp, m, w, Z, c->at(c->lay.ref_work), c->prec ? REFINE_MIXED : REFINE_FP64,
-                        REFINE_ITERS, st, c->host, sqs);
+  if (!small || terms <= 0)
+    its = refine_eigh(Hp, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host, sqs);
   if (its < 0) {   // a wide cluster or no convergence: blocked Jacobi from H'
     ++c->fallbacks;
     its = jacobi_checked(c, Hp, m, w, Z);
@@ -540,6 +560,14 @@ void subspace_solve_dev(sky_ctx* c, int s) {
   void* U = c->at(c->lay.matU);
   void* sq = c->at(c->lay.sq_part);
   const int sqs = c->tune.sq[q];
+  const int maxit = c->d.dev_refine_steps > 0 ? c->d.dev_refine_steps : REFINE_ITERS_DEV;
+  {
+    GateScope g(fl + F_ACTIVE);
+    if (subspace_small(I, H, Linv, Hp, Z, U, m, c->at<double>(c->lay.ritz[s]), LOEWDIN_SERIES_MAX,
+                       c->prec ? MIXED_SERIES_EPS : SERIES_EPS, c->prec ? REFINE_MIXED : REFINE_FP64,
+                       maxit, st, nullptr, fl, s))
+      return;
+  }
   loewdin_series_dev(I, Linv, c->at(c->lay.matC), T, m, LOEWDIN_SERIES_MAX,
                      c->prec ? MIXED_SERIES_EPS : SERIES_EPS, c->at<double>(c->lay.nrm), sq, st, sqs,
                      fl, db, s);
@@ -549,8 +577,7 @@ void subspace_solve_dev(sky_ctx* c, int s) {
     gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
   }
   refine_eigh_dev(Hp, m, c->at<double>(c->lay.ritz[s]), Z, c->at(c->lay.ref_work),
-                  c->prec ? REFINE_MIXED : REFINE_FP64,
-                  c->d.dev_refine_steps > 0 ? c->d.dev_refine_steps : REFINE_ITERS_DEV, st, sqs, fl, s);
+                  c->prec ? REFINE_MIXED : REFINE_FP64, maxit, st, sqs, fl, s);
   GateScope g(fl + F_ACTIVE);
   gemm_square(Linv, 0, Z, 0, U, m, st, sq, 0, sqs);
 }

@@ -260,6 +260,8 @@ void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m,
 // of pinned host memory that the kernels write their results for the host to
 // (one caller at a time).
 constexpr int HOST_STATUS = 8;
+constexpr double REF_THETA = 0.03;     // weak-coupling ratio |coupling| / |gap|
+constexpr double REF_E_CLAMP = 0.25;   // bound on one update coefficient
 size_t refine_scratch_bytes(int m);
 // Stop and step targets of the refinement.
 struct RefineTargets {
@@ -279,6 +281,21 @@ int refine_eigh(const void* A, int m, double* w, void* Z, void* work, const Refi
 // F_NFLAGS - F_REF_OK - 1.
 void refine_eigh_dev(const void* A, int m, double* w, void* Z, void* work, const RefineTargets& tg,
                      int maxit, hipStream_t st, int sq_split, int* flags, int set);
+
+// ---- subspace solves of up to SMALL_M states in one workgroup (k_small.hip)
+// With I (the overlap): the series transform C = I^-1/2, H' = C H C, the
+// refinement of H' to (w, Z) and U = C Z, by the formulas of loewdin_series
+// (max_dev, eps) and refine_eigh (tg, maxit).  I null: the refinement of H
+// alone (C, Hp, U unused).  host (as refine_eigh's, or null): host[0] = terms
+// of the series (0 when ||I - 1||_F > max_dev, -1 when it is not finite; 1
+// without I), host[1] = refinement steps, or -1 when the refinement did not
+// converge or was not reached.  flags (or null): the outcome as
+// loewdin_series_dev and refine_eigh_dev leave it.  One launch; false (nothing
+// done) when m is not 1 .. SMALL_M.
+constexpr int SMALL_M = 32;
+bool subspace_small(const void* I, const void* H, void* C, void* Hp, void* Z, void* U, int m, double* w,
+                    double max_dev, double eps, const RefineTargets& tg, int maxit, hipStream_t st,
+                    double* host, int* flags = nullptr, int set = 0);
 
 // ---- dense FP64 linear algebra (k_linalg.hip)
 // Cholesky A = L L^H of Hermitian positive definite A (m x m, lower used),

@@ -76,6 +76,18 @@ def test_jacobi_eigenpairs(m):
 @pytest.mark.parametrize("sizes", [[1] * 5, [2] * 8, [2, 12, 24], [1, 48, 3], [50, 2], [1] * 130,
                                    [2] * 40 + [24, 17, 24]])
 def test_rayleigh_ritz_of_degenerate_levels(sizes):
+    _check_degenerate(sizes)
+
+
+# the one-workgroup solve (up to 32 states) at the edges of its two stored orders:
+# clusters of one wave (to 16) and of the workgroup, odd ones, and none; 33 is past it
+@pytest.mark.parametrize("sizes", [[1], [2], [3, 5, 7, 1], [16], [17], [1, 17, 13, 1], [16, 16], [31, 1],
+                                   [3] * 10 + [2], [1] * 32, [2] * 16 + [1]])
+def test_rayleigh_ritz_of_few_states(sizes):
+    _check_degenerate(sizes)
+
+
+def _check_degenerate(sizes):
     """Ritz values, U^H I U = 1 and U^H H U = diag for phi a small step off
     eigenstates of an operator with degenerate levels."""
     n, m = 8, sum(sizes)
