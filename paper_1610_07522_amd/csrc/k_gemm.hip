@@ -5,9 +5,12 @@
 // lower triangle only (Fig. 3).  Sec. 3.3.3: the orthonormalised, diagonal
 // states are built with one product psi = phi (C Z) (step 3e).
 //
-// Tiles, operand staging and the three-product complex scheme are in
-// mfma_f64.h.
+// Every wave owns an output sub-tile of 16 x 16 blocks and loads its operands
+// from L2 in the layout of the matrix instruction.  Staging 64 x 64 tiles in
+// LDS moved half the operand bytes, but the matrix cores waited at its two
+// barriers per chunk, and ragged orders left quarters of the tiles dead.
 #include <algorithm>
+#include <type_traits>
 
 #include "mfma_f64.h"
 #include "sky_kernels.h"
@@ -21,6 +24,8 @@ using mfma::KC;
 using mfma::KP;
 using mfma::TM;
 
+constexpr int NXCD = 8;   // workgroups are dealt to the XCDs in turn, each has its own L2
+
 // Lower-triangle tile pair number p -> (ta, tb), ta >= tb.
 __device__ inline void tri_pair(int p, int& ta, int& tb) {
   int a = int((sqrt(8.0 * p + 1.0) - 1.0) * 0.5);
@@ -30,56 +35,106 @@ __device__ inline void tri_pair(int p, int& ta, int& tb) {
   tb = p - a * (a + 1) / 2;
 }
 
+// A wave's sub-tile of NB x NB blocks of 16 x 16, its operands loaded from
+// L2 straight in the layout of the matrix instruction: lane (r, kq) holds row
+// (or column) 16 i + r at contraction index kq of each step of four.
+template <int NB>
+struct Sub {
+  mfma::d4 re[NB][NB], im[NB][NB];
+  __device__ inline Sub() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) re[i][j] = im[i][j] = mfma::d4{0, 0, 0, 0};
+  }
+  // += conj(a) b^T (CONJA) or a b^T over one step
+  template <bool CONJA>
+  __device__ inline void step(const double2 (&a)[NB], const double2 (&b)[NB]) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const double ai = CONJA ? -a[i].y : a[i].y;
+        re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, re[i][j], 0, 0, 0);
+        im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, im[i][j], 0, 0, 0);
+        re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, b[j].y, re[i][j], 0, 0, 0);
+        im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b[j].x, im[i][j], 0, 0, 0);
+      }
+  }
+};
+constexpr int KQ = KC / 4;   // steps per chunk
+
 // ----------------------------------------------------------- overlap (lower)
-// part[(z*npair + pair)*split + s][64*64] = sum over chunk s of conj(A) B^T.
+// part[(z*npair + pair)*split + s][64*64] = sum over chunk s of conj(A) B^T,
+// the blocks of the 64 x 64 tile pairs that hold elements of the lower triangle.
+// One wave per 16 NB x 16 NB sub-tile of the triangle, split s and product z;
+// the waves need neither LDS nor barriers.  The loads of a step are issued as
+// soon as the step before frees their registers, three steps (of 16 matrix
+// instructions) ahead.  Rows past m read the last row; their results are
+// never read.  Grid (ceil(nsub / 4), split, nz), dealt out so that the
+// sub-tiles and both products of one split run on one XCD and share its L2.
+// Bound by the matrix cores: 150 states at 24^3, both products, 187 us with
+// tiles in LDS, now 114 (60 TF over its sub-tiles); 8 states at 16^3 22.5 ->
+// 10.2 us.  Sub-tiles of one block up to 16 states.
+template <int NB>
 __global__ void __launch_bounds__(GT)
 k_overlap_lower(const double2* __restrict__ A, const double2* __restrict__ B0,
                 const double2* __restrict__ B1, int m, long k, int split, double2* __restrict__ part, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double2 sA[TM * KP];
-  __shared__ double2 sB[TM * KP];
-  const int npair = gridDim.x;
-  const int pair = blockIdx.x, s = blockIdx.y, z = blockIdx.z;
-  const double2* B = z ? B1 : B0;
-  int ta, tb;
-  tri_pair(pair, ta, tb);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  constexpr int SUB = 16 * NB, PER = TM / SUB;
+  int w4 = blockIdx.x, s = blockIdx.y, z = blockIdx.z;
+  if (split % NXCD == 0) {
+    const int ng = gridDim.x, id = w4 + ng * (s + split * z), per = ng * int(gridDim.z), idx = id / NXCD;
+    s = idx / per * NXCD + id % NXCD;
+    w4 = idx % per % ng;
+    z = idx % per / ng;
+  }
+  const int nt = (m + TM - 1) / TM, npair = nt * (nt + 1) / 2, ns = (m + SUB - 1) / SUB;
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+  const int u = __builtin_amdgcn_readfirstlane(w4 * (GT / 64) + (threadIdx.x >> 6));
+  if (u >= ns * (ns + 1) / 2) return;
+  int ua, ub;
+  tri_pair(u, ua, ub);
   const long nck = k / KC;
   const long c0 = nck * s / split, c1 = nck * (s + 1) / split;
-  // loader: thread -> (row, 4 consecutive complex); contraction index kk of a
-  // row is stored at mfma::kperm(kk), so that the 8 lanes of an LDS store
-  // cycle (2 rows x 4 threads) meet 8 different bank groups
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  const int ga = ta * TM + lrow, gb = tb * TM + lrow;
-  // chunk c + 1 is loaded into registers while chunk c is multiplied
-  double2 ra[4], rb[4];
-  auto load = [&](long c) {
-    const long k0 = c * KC + lk;
+  const double2* B = z ? B1 : B0;
+  const double2 *pa[NB], *pb[NB];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      ra[e] = ga < m ? A[size_t(ga) * k + k0 + e] : make_double2(0, 0);
-      rb[e] = gb < m ? B[size_t(gb) * k + k0 + e] : make_double2(0, 0);
+  for (int i = 0; i < NB; ++i) {
+    pa[i] = A + size_t(min(ua * SUB + 16 * i + r, m - 1)) * k + kq;
+    pb[i] = B + size_t(min(ub * SUB + 16 * i + r, m - 1)) * k + kq;
+  }
+  double2 a[KQ][NB], b[KQ][NB];
+  auto load = [&](long c, int q) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      a[q][i] = pa[i][c * KC + 4 * q];
+      b[q][i] = pb[i][c * KC + 4 * q];
     }
   };
-  Acc acc;
-  mfma::zero(acc);
-  if (c0 < c1) load(c0);
-  for (long c = c0; c < c1; ++c) {
+  Sub<NB> acc;
+  if (c0 < c1)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      sA[lrow * KP + mfma::kperm(lk + e)] = ra[e];
-      sB[lrow * KP + mfma::kperm(lk + e)] = rb[e];
+    for (int q = 0; q < KQ; ++q) load(c0, q);
+  for (long c = c0; c < c1; ++c) {
+    const long cn = min(c + 1, c1 - 1);
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      acc.template step<true>(a[q], b[q]);
+      load(cn, q);
     }
-    __syncthreads();
-    if (c + 1 < c1) load(c + 1);
-    mfma::tile<true, true>(acc, sA, sB, wm, wn, lane);
-    __syncthreads();
   }
-  double2* out = part + (size_t(z) * npair + pair) * split * TM * TM + size_t(s) * TM * TM;
-  mfma::foreach(acc, wm, wn, lane, [&](int row, int col, double re, double im) {
-    out[row * TM + col] = make_double2(re, im);
-  });
+  int ta = ua / PER, tb = ub / PER;
+  const int pair = ta * (ta + 1) / 2 + tb;
+  double2* out = part + ((size_t(z) * npair + pair) * split + s) * TM * TM +
+                 (ua % PER * SUB) * TM + ub % PER * SUB;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        out[(16 * i + 4 * e + kq) * TM + 16 * j + r] = make_double2(acc.re[i][j][e], acc.im[i][j][e]);
 }
 
 // C[a][b] = scale * sum_s part[..][s][..] in order of s on the lower
@@ -137,200 +192,144 @@ k_overlap_reduce(const double2* __restrict__ part, int npair, int split, int m, 
 }
 
 // ----------------------------------------------------------- combine
-// Y[b][v] = sum_a U[a][b] X[a][v]: M = b (rows of Y), N = v, K = a.
+// Y[b][v] = sum_a U[a][b] X[a][v]: M = b (rows of Y), N = v, K = a.  One wave per
+// sub-tile of 32 x 32, as k_overlap_lower; grid (k / 32 / 4, row tiles of 32),
+// dealt out so that the row tiles of one column tile run on one XCD and X
+// is read from HBM once.  150 states at 24^3: 133 us with tiles in LDS, now 112.
+constexpr int CT = 32;   // sub-tile side
 __global__ void __launch_bounds__(GT)
 k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2* __restrict__ Y,
           int m, long k, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double2 sA[TM * KP];   // [b][a]
-  __shared__ double2 sB[TM * KP];   // [v][a]
-  const long v0 = long(blockIdx.x) * TM;
-  const int b0 = blockIdx.y * TM;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  // loader: thread -> (a within chunk = tid/16, columns lc + 16 e): 16 lanes
-  // read 256 contiguous bytes, and the transposed LDS stores of 8 lanes land
-  // in 8 different bank groups (KP odd)
-  const int la = tid >> 4, lc = tid & 15;
-  // chunk a0 + KC is loaded into registers while chunk a0 is multiplied
-  double2 ru[4], rx[4];
-  auto load = [&](int a0) {
-    const int a = a0 + la;
+  int vt = blockIdx.x, bt = blockIdx.y;
+  if (gridDim.x % NXCD == 0) {
+    const int id = vt + int(gridDim.x) * bt, idx = id / NXCD;
+    bt = idx % int(gridDim.y);
+    vt = idx / int(gridDim.y) * NXCD + id % NXCD;
+  }
+  const int lane = threadIdx.x & 63, lc = lane & 15, kq = lane >> 4;
+  const long v0 = (long(vt) * (GT / 64) + (threadIdx.x >> 6)) * CT;
+  const int b0 = bt * CT;
+  double2 u[KQ][2], x[KQ][2];
+  auto load = [&](int a0, int q) {
+    const int a = a0 + 4 * q + kq;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < 2; ++e) {
       const int col = lc + 16 * e, b = b0 + col;
-      ru[e] = (a < m && b < m) ? U[size_t(a) * m + b] : make_double2(0, 0);
-      rx[e] = (a < m) ? X[size_t(a) * k + v0 + col] : make_double2(0, 0);
+      u[q][e] = a < m ? U[size_t(a) * m + min(b, m - 1)] : make_double2(0, 0);
+      x[q][e] = a < m ? X[size_t(a) * k + v0 + col] : make_double2(0, 0);
     }
   };
-  Acc acc;
-  mfma::zero(acc);
-  if (m > 0) load(0);
-  for (int a0 = 0; a0 < m; a0 += KC) {
+  Sub<2> acc;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int col = lc + 16 * e;
-      sA[col * KP + la] = ru[e];
-      sB[col * KP + la] = rx[e];
+  for (int q = 0; q < KQ; ++q) load(0, q);
+  for (int a0 = 0; a0 < m; a0 += KC)
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      acc.step<false>(u[q], x[q]);
+      load(a0 + KC, q);
     }
-    __syncthreads();
-    if (a0 + KC < m) load(a0 + KC);
-    mfma::tile<false>(acc, sA, sB, wm, wn, lane);
-    __syncthreads();
-  }
-  mfma::foreach(acc, wm, wn, lane, [&](int row, int col, double re, double im) {
-    const int b = b0 + row;
-    if (b < m) Y[size_t(b) * k + v0 + col] = make_double2(re, im);
-  });
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int b = b0 + 16 * i + 4 * e + kq;
+        if (b < m) Y[size_t(b) * k + v0 + 16 * j + lc] = make_double2(acc.re[i][j][e], acc.im[i][j][e]);
+      }
 }
 
 // ----------------------------------------------------------- square products
 // C = op(A) op(B), op 0 = N, 1 = conjugate transpose; all m x m row-major.
-// With lower, a product known to be Hermitian: only tiles on or below the
-// diagonal are computed; without a split (MIRROR) the strictly upper part is
-// written as the mirror image here, else by k_sum_splits_herm.
-// Grid (column tiles, row tiles, split): workgroup z sums the contraction
-// chunks [nk z / split, nk (z+1) / split) and writes C + z m^2 (split > 1:
-// partials, reduced in order by k_sum_splits).  Each operand is loaded along
-// its contiguous index (op N of B and op H of A read rows of 64 columns), one
-// chunk ahead into registers.
-template <int OPA, int OPB, bool MIRROR>
-__global__ void __launch_bounds__(GT)
+// MIRROR: a product known to be Hermitian; only sub-tiles on or below the
+// diagonal are computed, the upper triangle is their mirror image and the
+// diagonal real.  One sub-tile of NB x NB blocks per workgroup, the contraction
+// split over its waves (wave g takes the chunks g, g + QW, ..; partials summed
+// in wave order through LDS).  Operands are loaded from L2 as in
+// k_overlap_lower; the last row or column is repeated past m, and the
+// contraction is zero past it.  64 x 64 tiles staged in LDS, split over
+// workgroups and summed by a second launch, took 13 us at 150 states where this
+// takes 6, and as long at 1600.
+template <int NB, int QW, int OPA, int OPB, bool MIRROR>
+__global__ void __launch_bounds__(64 * QW)
 k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
-              double2* __restrict__ C, int m, int split, int lower, const int* __restrict__ sky_gate) {
+                  double2* __restrict__ C, int m, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double2 sA[TM * KP];   // [row][k] of op(A)
-  __shared__ double2 sB[TM * KP];   // [col][k] of op(B)
-  constexpr int NE = TM * KC / GT;  // elements per thread and operand
-  if (lower && blockIdx.x > blockIdx.y) return;   // Hermitian product: lower tiles only
-  const int r0 = blockIdx.y * TM, c0 = blockIdx.x * TM, sp = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  if (MIRROR && blockIdx.x > blockIdx.y) return;
+  constexpr int QT = 16 * NB, NTH = 64 * QW;
+  __shared__ double red[QW][QT][QT + 1];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kq = lane >> 4;
+  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = blockIdx.y * QT, c0 = blockIdx.x * QT;
   const int nk = (m + KC - 1) / KC;
-  const int kc0 = int((long(nk) * sp) / split), kc1 = int((long(nk) * (sp + 1)) / split);
-  // (t, kk) of element q: t = tile row / column, kk = contraction index
-  auto idxA = [&](int q, int& t, int& kk) {
-    const int e = tid + q * GT;
-    if (OPA == 0) { t = e / KC; kk = e % KC; } else { t = e % TM; kk = e / TM; }
-  };
-  auto idxB = [&](int q, int& t, int& kk) {
-    const int e = tid + q * GT;
-    if (OPB == 0) { t = e % TM; kk = e / TM; } else { t = e / KC; kk = e % KC; }
-  };
-  double2 ra[NE], rb[NE];
-  auto load = [&](int kc) {
-    const int k0 = kc * KC;
+  const double2 *pa[NB], *pb[NB];
+  const size_t sa = OPA == 0 ? 1 : m, sb = OPB == 0 ? m : 1;   // along the contraction
 #pragma unroll
-    for (int q = 0; q < NE; ++q) {
-      int t, kk;
-      idxA(q, t, kk);
-      const int r = r0 + t, kg = k0 + kk;
-      double2 v = make_double2(0, 0);
-      if (r < m && kg < m) {
-        if (OPA == 0) v = A[size_t(r) * m + kg];
-        else { v = A[size_t(kg) * m + r]; v.y = -v.y; }
-      }
-      ra[q] = v;
-      idxB(q, t, kk);
-      const int c = c0 + t, kb = k0 + kk;
-      v = make_double2(0, 0);
-      if (c < m && kb < m) {
-        if (OPB == 0) v = B[size_t(kb) * m + c];
-        else { v = B[size_t(c) * m + kb]; v.y = -v.y; }
-      }
-      rb[q] = v;
+  for (int i = 0; i < NB; ++i) {
+    pa[i] = A + size_t(min(r0 + 16 * i + r, m - 1)) * (OPA == 0 ? m : 1);
+    pb[i] = B + size_t(min(c0 + 16 * i + r, m - 1)) * (OPB == 0 ? 1 : m);
+  }
+  double2 a[KQ][NB], b[KQ][NB];
+  auto load = [&](int kc, int q) {
+    const int k = kc * KC + 4 * q + kq;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      a[q][i] = k < m ? pa[i][k * sa] : make_double2(0, 0);
+      b[q][i] = k < m ? pb[i][k * sb] : make_double2(0, 0);
+      if (OPB) b[q][i].y = -b[q][i].y;
     }
   };
-  Acc acc;
-  mfma::zero(acc);
-  if (kc0 < kc1) load(kc0);
-  for (int kc = kc0; kc < kc1; ++kc) {
+  Sub<NB> acc;
 #pragma unroll
-    for (int q = 0; q < NE; ++q) {
-      int t, kk;
-      idxA(q, t, kk);
-      sA[t * KP + kk] = ra[q];
-      idxB(q, t, kk);
-      sB[t * KP + kk] = rb[q];
+  for (int q = 0; q < KQ; ++q) load(g, q);
+  for (int kc = g; kc < nk; kc += QW)
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      acc.template step<OPA != 0>(a[q], b[q]);
+      load(kc + QW, q);
     }
+  // real parts, then imaginary parts, through LDS; element e of the thread is
+  // (e / QT, e % QT) of the sub-tile
+  constexpr int NV = QT * QT / NTH > 0 ? QT * QT / NTH : 1;
+  double2 v[NV], w[NV];   // the element, and its mirror image's source
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    if (part) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          red[g][16 * i + 4 * e + kq][16 * j + r] = part ? acc.im[i][j][e] : acc.re[i][j][e];
     __syncthreads();
-    if (kc + 1 < kc1) load(kc + 1);
-    mfma::tile<false>(acc, sA, sB, wm, wn, lane);
-    __syncthreads();
-  }
-  double2* out = C + size_t(sp) * m * m;
-  mfma::foreach(acc, wm, wn, lane, [&](int row, int col, double re, double im) {
-    const int r = r0 + row, c = c0 + col;
-    if (r >= m || c >= m) return;
-    if (!MIRROR) {
-      out[size_t(r) * m + c] = make_double2(re, im);
-    } else if (r >= c) {
-      out[size_t(r) * m + c] = make_double2(re, r == c ? 0.0 : im);
-      if (r > c) out[size_t(c) * m + r] = make_double2(re, -im);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int e = tid + q * NTH, i = e / QT, j = e % QT;
+      if (e >= QT * QT) break;
+      double x = red[0][i][j], y = red[0][j][i];
+#pragma unroll
+      for (int h = 1; h < QW; ++h) {
+        x += red[h][i][j];
+        y += red[h][j][i];
+      }
+      if (part) v[q].y = x; else v[q].x = x;
+      if (part) w[q].y = y; else w[q].x = y;
     }
-  });
-}
-
-// C[e] = sum_s part[s][e], in order.
-__global__ void k_sum_splits(const double2* __restrict__ part, int split, size_t n,
-                             double2* __restrict__ C, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const size_t e = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  double2 acc = part[e];
-  for (int s = 1; s < split; ++s) {
-    const double2 v = part[size_t(s) * n + e];
-    acc.x += v.x;
-    acc.y += v.y;
   }
-  C[e] = acc;
-}
-
-// The same for a Hermitian product of which only the lower tiles were computed:
-// 16 x 16 blocks on or below the diagonal, mirrored through LDS (grid over the
-// blocks of the matrix).
-__global__ void __launch_bounds__(256)
-k_sum_splits_herm(const double2* __restrict__ part, int split, int m, double2* __restrict__ C,
-                  const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  if (blockIdx.x > blockIdx.y) return;
-  __shared__ double2 T[16][17];
-  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
-  const int row0 = blockIdx.y * 16, col0 = blockIdx.x * 16, row = row0 + r, col = col0 + c;
-  const size_t n = size_t(m) * m;
-  if (row < m && col <= row) {
-    const size_t e = size_t(row) * m + col;
-    double2 acc = part[e];
-    for (int s = 1; s < split; ++s) {
-      const double2 v = part[size_t(s) * n + e];
-      acc.x += v.x;
-      acc.y += v.y;
-    }
-    if (row == col) acc.y = 0.0;
-    C[e] = acc;
-    T[r][c] = acc;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int e = tid + q * NTH, i = e / QT, j = e % QT;
+    if (e >= QT * QT) break;
+    const bool diag = MIRROR && r0 == c0;
+    double2 x = v[q];
+    if (diag && i < j) x = make_double2(w[q].x, -w[q].y);
+    if (diag && i == j) x.y = 0.0;
+    if (r0 + i < m && c0 + j < m) C[size_t(r0 + i) * m + c0 + j] = x;
+    if (MIRROR && !diag && c0 + i < m && r0 + j < m)
+      C[size_t(c0 + i) * m + r0 + j] = make_double2(w[q].x, -w[q].y);
   }
-  __syncthreads();
-  const int mr = col0 + r, mc = row0 + c;
-  if (mc < m && mr < mc) {
-    const double2 v = T[c][r];
-    C[size_t(mr) * m + mc] = make_double2(v.x, -v.y);
-  }
-}
-
-// Contraction splits of the square products: enough workgroups for ~4 per
-// CU (tile counts such as 625 = 25^2 otherwise leave a long last round);
-// herm: only the nt (nt + 1) / 2 lower tiles are live.
-int square_split(int m, int herm) {
-  if (m <= 0) return 1;   // empty species: nothing to split
-  const int nt = (m + TM - 1) / TM;
-  const int nk = (m + KC - 1) / KC;
-  const int tiles = herm ? nt * (nt + 1) / 2 : nt * nt;
-  int split = (1024 + tiles - 1) / tiles;
-  if (split > 8) split = 8;
-  if (split > nk / 2) split = nk / 2;
-  if (split < 1) split = 1;
-  return split;
 }
 
 int overlap_split(int m, long k) {
@@ -374,9 +373,14 @@ void overlap_lower(const void* A, const void* B0, const void* B1, int m, long k,
   const int split = split_req > 0 ? split_req : overlap_split(m, k);
   const int nz = B1 ? 2 : 1;
   if (ev) hipEventRecord(ev[0], st);
-  hipLaunchKernelGGL(k_overlap_lower, dim3(npair, split, nz), dim3(GT), 0, st,
-                     (const double2*)A, (const double2*)B0, (const double2*)B1, m, k, split,
-                     (double2*)part, g_launch_gate);
+  auto launch = [&](auto kernel, int sub) {
+    const int ns = (m + sub - 1) / sub, nsub = ns * (ns + 1) / 2;
+    hipLaunchKernelGGL(kernel, dim3(unsigned((nsub + 3) / 4), split, nz), dim3(GT), 0, st,
+                       (const double2*)A, (const double2*)B0, (const double2*)B1, m, k, split,
+                       (double2*)part, g_launch_gate);
+  };
+  if (m <= 16) launch(k_overlap_lower<1>, 16);
+  else launch(k_overlap_lower<2>, 32);
   if (ev) hipEventRecord(ev[1], st);
   overlap_reduce(part, npair, split, m, scale, C0, C1, nz, st);
 }
@@ -390,53 +394,32 @@ void overlap_reduce(const void* part, int npair, int split, int m, double scale,
 
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st) {
   if (m <= 0) return;
-  dim3 grid(unsigned(k / TM), (m + TM - 1) / TM);
+  dim3 grid(unsigned(k / (CT * (GT / 64))), (m + CT - 1) / CT);
   hipLaunchKernelGGL(k_combine, grid, dim3(GT), 0, st, (const double2*)X, (const double2*)U,
                      (double2*)Y, m, k, g_launch_gate);
 }
 
-// Split-K factors tried by the autotuner for square products of size m.
-int square_split_candidates(int m, int* out) {
-  const int nk = (m + KC - 1) / KC;
-  int n = 0;
-  for (int c : {1, 2, 4, 8})
-    if (c == 1 || c <= nk / 2) out[n++] = c;
-  return n;
-}
+// Blocks per sub-tile: one while the 32 x 32 sub-tiles would be fewer than the
+// CUs (256 at 512 states; Rayleigh-Ritz of 400: 2820 us against 2910), two from
+// there (1600: 10.1 ms against 10.3).
+constexpr int SQ_NB1_MAX = 512;
 
-size_t gemm_square_scratch_bytes(int m) {
-  int c[4];
-  const int nc = square_split_candidates(m, c);
-  int split = std::max(square_split(m, 0), square_split(m, 1));
-  for (int i = 0; i < nc; ++i) split = std::max(split, c[i]);
-  return split > 1 ? size_t(split) * m * m * sizeof(double2) : 0;
-}
-
-void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st,
-                 void* part, int herm, int split_req) {
+void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st, int herm) {
   if (m <= 0) return;
-  const int split = !part ? 1 : (split_req > 0 ? split_req : square_split(m, herm));
-  dim3 grid((m + TM - 1) / TM, (m + TM - 1) / TM, split);
-  auto a = (const double2*)A;
-  auto b = (const double2*)B;
-  auto c = (double2*)(split > 1 ? part : C);
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(GT), 0, st, a, b, c, m, split, herm, g_launch_gate);
+  auto go = [&](auto nb, auto qw) {
+    constexpr int NB = decltype(nb)::value, QW = decltype(qw)::value;
+    const unsigned nt = unsigned((m + 16 * NB - 1) / (16 * NB));
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nt, nt), dim3(64 * QW), 0, st, (const double2*)A, (const double2*)B,
+                         (double2*)C, m, g_launch_gate);
+    };
+    if (opA == 0 && opB == 0) herm ? launch(k_gemm_square<NB, QW, 0, 0, true>) : launch(k_gemm_square<NB, QW, 0, 0, false>);
+    else if (opA == 0) herm ? launch(k_gemm_square<NB, QW, 0, 1, true>) : launch(k_gemm_square<NB, QW, 0, 1, false>);
+    else if (opB == 0) herm ? launch(k_gemm_square<NB, QW, 1, 0, true>) : launch(k_gemm_square<NB, QW, 1, 0, false>);
+    else herm ? launch(k_gemm_square<NB, QW, 1, 1, true>) : launch(k_gemm_square<NB, QW, 1, 1, false>);
   };
-  const bool mirror = herm && split == 1;
-  if (opA == 0 && opB == 0) mirror ? launch(k_gemm_square<0, 0, true>) : launch(k_gemm_square<0, 0, false>);
-  else if (opA == 0) mirror ? launch(k_gemm_square<0, 1, true>) : launch(k_gemm_square<0, 1, false>);
-  else if (opB == 0) mirror ? launch(k_gemm_square<1, 0, true>) : launch(k_gemm_square<1, 0, false>);
-  else mirror ? launch(k_gemm_square<1, 1, true>) : launch(k_gemm_square<1, 1, false>);
-  if (split > 1 && herm) {
-    const unsigned nb = unsigned((m + 15) / 16);
-    hipLaunchKernelGGL(k_sum_splits_herm, dim3(nb, nb), dim3(256), 0, st, (const double2*)part, split,
-                       m, (double2*)C, g_launch_gate);
-  } else if (split > 1) {
-    const size_t n = size_t(m) * m;
-    hipLaunchKernelGGL(k_sum_splits, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st,
-                       (const double2*)part, split, n, (double2*)C, g_launch_gate);
-  }
+  if (m <= SQ_NB1_MAX) go(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
 }
 
 }  // namespace sky

@@ -710,7 +710,7 @@ void eig_sort(const void* D, const void* V, int m, int ld, double* w, void* Z, h
 }
 
 int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double max_dev,
-                   double* scratch, void* part, hipStream_t st, double* host, int sq_split, double eps) {
+                   double* scratch, hipStream_t st, double* host, double eps) {
   if (m <= 0) return 0;
   auto D = (double2*)Dv;
   const size_t mm = size_t(m) * m;
@@ -736,7 +736,7 @@ int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double m
   hipLaunchKernelGGL(k_axpy_identity, dim3(ge), dim3(256), 0, st, (const double2*)D, c[p], c[p - 1],
                      cur, m, g_launch_gate);
   for (int k = p - 2; k >= 0; --k) {
-    gemm_square(D, 0, cur, 0, nxt, m, st, part, 1, sq_split);   // a polynomial in D: Hermitian
+    gemm_square(D, 0, cur, 0, nxt, m, st, 1);   // a polynomial in D: Hermitian
     hipLaunchKernelGGL(k_add_identity, dim3((m + 255) / 256), dim3(256), 0, st, nxt, c[k], m, g_launch_gate);
     std::swap(cur, nxt);
   }
@@ -817,8 +817,7 @@ __global__ void k_add_identity_dev(double2* __restrict__ P, const double* __rest
 }
 
 void loewdin_series_dev(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double max_dev,
-                        double eps, double* scratch, void* part, hipStream_t st, int sq_split,
-                        int* flags, double* dbl, int set) {
+                        double eps, double* scratch, hipStream_t st, int* flags, double* dbl, int set) {
   if (m <= 0) return;
   auto D = (double2*)Dv;
   const size_t mm = size_t(m) * m;
@@ -848,7 +847,7 @@ void loewdin_series_dev(const void* Iv, void* Cv, void* Dv, void* Tv, int m, dou
                      (const double*)dbl, C, T, m, active);
   for (int k = pcap - 2; k >= 0; --k) {
     GateScope g(flags + F_SERIES + k);
-    gemm_square(D, 0, buf[(k + 1) % 2], 0, buf[k % 2], m, st, part, 1, sq_split);
+    gemm_square(D, 0, buf[(k + 1) % 2], 0, buf[k % 2], m, st, 1);
     hipLaunchKernelGGL(k_add_identity_dev, dim3((m + 255) / 256), dim3(256), 0, st, buf[k % 2],
                        (const double*)(dbl + D_SERIES + 2 + k), m, g_launch_gate);
   }

@@ -697,11 +697,12 @@ __global__ void k_ref_check_final(const double* __restrict__ part, int nb, doubl
 unsigned cluster_threads(int m) { return unsigned(std::min(CL_THREADS, (m + 63) / 64 * 64)); }
 
 struct RefineWork {
-  double2 *mat[7], *W, *gpart;
+  double2 *mat[7], *W;
   double *lam, *lam2, *part, *norms;
   unsigned long long* emax;
   int *rank, *order, *reach, *pm, *cstart, *csize, *cslot, *info;
   int2* clist;
+  char* end;
 };
 
 size_t al256(size_t b) { return (b + 255) / 256 * 256; }
@@ -730,19 +731,17 @@ RefineWork carve(void* work, int m) {
   r.info = in(4);
   r.clist = reinterpret_cast<int2*>(p);
   p += al256(size_t(m) * sizeof(int2));
-  r.gpart = reinterpret_cast<double2*>(p);
-  p += al256(gemm_square_scratch_bytes(m));
+  r.end = p;
   return r;
 }
 }  // namespace
 
 size_t refine_scratch_bytes(int m) {
-  RefineWork r = carve(nullptr, m);
-  return size_t(reinterpret_cast<char*>(r.gpart)) + al256(gemm_square_scratch_bytes(m));
+  return size_t(carve(nullptr, m).end);
 }
 
 int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                int maxit, hipStream_t st, double* host, int sq_split) {
+                int maxit, hipStream_t st, double* host) {
   if (m <= 0) return 0;
   if (m <= SMALL_M) {
     subspace_small(nullptr, Av, nullptr, nullptr, Z, nullptr, m, w, 0.0, 0.0, tg, maxit, st, host);
@@ -771,9 +770,9 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
     const double2* Sp = A;
     const double2* Rp = nullptr;
     if (it > 0) {
-      gemm_square(X, 1, X, 0, R, m, st, r.gpart, 1, sq_split);
-      gemm_square(A, 0, X, 0, T, m, st, r.gpart, 0, sq_split);
-      gemm_square(X, 1, T, 0, S, m, st, r.gpart, 1, sq_split);
+      gemm_square(X, 1, X, 0, R, m, st, 1);
+      gemm_square(A, 0, X, 0, T, m, st);
+      gemm_square(X, 1, T, 0, S, m, st, 1);
       hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                          r.part, g_launch_gate);
       hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
@@ -808,14 +807,14 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
                        g_launch_gate, tg.e2skip, e2);
     {
       GateScope g2(e2);
-      gemm_square(E, 0, E, 0, T, m, st, r.gpart, 0, sq_split);
+      gemm_square(E, 0, E, 0, T, m, st);
     }
     hipLaunchKernelGGL(k_ref_build_q, dim3(gm, unsigned(m)), dim3(256), 0, st, (const double2*)E,
                        (const double2*)T, (const int*)e2, m, cl, Q, g_launch_gate);
     if (it == 0) {
       std::swap(X, Q);
     } else {
-      gemm_square(X, 0, Q, 0, Xn, m, st, r.gpart, 0, sq_split);
+      gemm_square(X, 0, Q, 0, Xn, m, st);
       std::swap(X, Xn);
     }
   }
@@ -853,7 +852,7 @@ __global__ void k_ref_start(int* __restrict__ flags) {
 }
 
 void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                     int maxit, hipStream_t st, int sq_split, int* flags, int set) {
+                     int maxit, hipStream_t st, int* flags, int set) {
   if (m <= 0) return;
   const double tol = tg.tol, noise = tg.noise, orth = tg.orth;
   if (maxit > F_NFLAGS - F_REF_OK - 1) maxit = F_NFLAGS - F_REF_OK - 1;
@@ -878,9 +877,9 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
     if (it > 0) {
       {
         GateScope g(run);
-        gemm_square(X, 1, X, 0, R, m, st, r.gpart, 1, sq_split);
-        gemm_square(A, 0, X, 0, T, m, st, r.gpart, 0, sq_split);
-        gemm_square(X, 1, T, 0, S, m, st, r.gpart, 1, sq_split);
+        gemm_square(X, 1, X, 0, R, m, st, 1);
+        gemm_square(A, 0, X, 0, T, m, st);
+        gemm_square(X, 1, T, 0, S, m, st, 1);
         hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                            r.part, g_launch_gate);
         hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
@@ -918,14 +917,14 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
                        run, tg.e2skip, e2);
     {
       GateScope g2(e2);
-      gemm_square(E, 0, E, 0, T, m, st, r.gpart, 0, sq_split);
+      gemm_square(E, 0, E, 0, T, m, st);
     }
     hipLaunchKernelGGL(k_ref_build_q, dim3(gm, unsigned(m)), dim3(256), 0, st, (const double2*)E,
                        (const double2*)T, (const int*)e2, m, cl, Q, g_launch_gate);
     if (it == 0) {
       std::swap(X, Q);
     } else {
-      gemm_square(X, 0, Q, 0, Xn, m, st, r.gpart, 0, sq_split);
+      gemm_square(X, 0, Q, 0, Xn, m, st);
       std::swap(X, Xn);
     }
   }

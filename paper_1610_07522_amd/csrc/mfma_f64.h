@@ -1,5 +1,5 @@
 // 64x64 complex FP64 output tiles on the FP64 matrix cores of gfx950
-// (v_mfma_f64_16x16x4f64), shared by the GEMM and linear-algebra kernels.
+// (v_mfma_f64_16x16x4f64), of the linear-algebra kernels.
 //
 // A workgroup of 4 waves (2x2) owns a 64x64 complex tile; each wave a 32x32
 // sub-tile = 2x2 MFMA blocks of 16x16.  Operands are staged in LDS as
@@ -43,15 +43,14 @@ __device__ inline void zero(Acc& a) {
 // the eight 16-byte bank groups of 32 banks (odd KP shifts the second row).
 __device__ inline int kperm(int kk) { return (kk >> 1) | ((kk & 1) << 3); }
 
-// acc += op(A) B^T over one KC chunk staged in LDS; A conjugated if CONJA;
-// PERM: the rows were stored at kperm positions.
-template <bool CONJA, bool PERM = false>
+// acc += op(A) B^T over one KC chunk staged in LDS; A conjugated if CONJA.
+template <bool CONJA>
 __device__ inline void tile(Acc& acc, const double2* sA, const double2* sB, int wm, int wn,
                             int lane) {
   const int r = lane & 15, kq = lane >> 4;
 #pragma unroll
   for (int kk = 0; kk < KC; kk += 4) {
-    const int kc = PERM ? kperm(kk + kq) : kk + kq;
+    const int kc = kk + kq;
     double2 a[2], b[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) a[i] = sA[(wm * 32 + i * 16 + r) * KP + kc];

@@ -84,7 +84,7 @@ struct Layout {
   size_t phi[2], hphi[2], phi32[2], hphi32[2];
   size_t tiles, gauge;
   size_t matI, matH, matC, matL, matT, matHp, matZ, matU, wtmp, gemm_part, chol_work, jac_work;
-  size_t ref_work, nrm, sq_part;
+  size_t ref_work, nrm;
   // learned preconditioner: parameters (FP32 master, BF16-rounded copy),
   // gradient, Adam moments, sample rows, activations, shell powers, gains,
   // sampled-state batch buffers
@@ -198,7 +198,6 @@ Layout plan(const sky_box_desc& d) {
     L.pc_beps = take(sizeof(double) * L.pc_nb);
     for (int i = 0; i < 4; ++i) L.pc_b[i] = take(c16 * size_t(L.pc_nb) * V);
   }
-  L.sq_part = take(std::max(gemm_square_scratch_bytes(nq[0]), gemm_square_scratch_bytes(nq[1])));
   for (int q = 0; q < 2; ++q) {
     L.dens[q] = take(sizeof(double) * 11 * n3);
     L.der[q] = take(sizeof(double) * 5 * n3);
@@ -485,8 +484,6 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
   int* info = c->at<int>(c->lay.info);
   const int ts = t_begin(c, SKY_PHASE_SUBSPACE, q);
   void* Cw = c->at(c->lay.matC);
-  void* sq = c->at(c->lay.sq_part);
-  const int sqs = c->tune.sq[q];
   double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
   const RefineTargets& tg = c->prec ? REFINE_MIXED : REFINE_FP64;
   const double series_eps = c->prec ? MIXED_SERIES_EPS : SERIES_EPS;
@@ -506,35 +503,35 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
       return SKY_OK;
     }
   } else {
-    terms = loewdin_series(I, Linv, Cw, T, m, LOEWDIN_SERIES_MAX, c->at<double>(c->lay.nrm), sq, st,
-                           c->host, sqs, series_eps);
+    terms = loewdin_series(I, Linv, Cw, T, m, LOEWDIN_SERIES_MAX, c->at<double>(c->lay.nrm), st,
+                           c->host, series_eps);
   }
   if (terms < 0) return fail(SKY_ERR_NAN, "non-finite overlap matrix");
   if (terms > 0) {   // C = I^-1/2 (Hermitian) in Linv
     if (!small) {
-      gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
-      gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
+      gemm_square(Linv, 0, H, 0, T, m, st);
+      gemm_square(T, 0, Linv, 0, Hp, m, st, 1);
     }
   } else {           // Linv = L^-1, C = L^-H
     hipMemsetAsync(info, 0, sizeof(int), st);
     hipMemcpyAsync(Cw, I, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
     cholesky_inverse(Cw, Linv, m, c->at(c->lay.chol_work), info, st, CHOL_PIVOT_MIN);
-    gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
-    gemm_square(T, 0, Linv, 1, Hp, m, st, sq, 1, sqs);
+    gemm_square(Linv, 0, H, 0, T, m, st);
+    gemm_square(T, 0, Linv, 1, Hp, m, st, 1);
   }
   if (terms <= 0) {   // only the Cholesky path can report a non-positive overlap
     int rc = check_info(c, "cholesky");
     if (rc) return rc;
   }
   if (!small || terms <= 0)
-    its = refine_eigh(Hp, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host, sqs);
+    its = refine_eigh(Hp, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host);
   if (its < 0) {   // a wide cluster or no convergence: blocked Jacobi from H'
     ++c->fallbacks;
     its = jacobi_checked(c, Hp, m, w, Z);
     if (its < 0) return its;
   }
   c->last_sweeps += its;
-  gemm_square(Linv, terms > 0 ? 0 : 1, Z, 0, U, m, st, sq, 0, sqs);
+  gemm_square(Linv, terms > 0 ? 0 : 1, Z, 0, U, m, st);
   t_end(c, ts);
   return SKY_OK;
 }
@@ -558,8 +555,6 @@ void subspace_solve_dev(sky_ctx* c, int s) {
   void* Hp = c->at(c->lay.matHp);
   void* Z = c->at(c->lay.matZ);
   void* U = c->at(c->lay.matU);
-  void* sq = c->at(c->lay.sq_part);
-  const int sqs = c->tune.sq[q];
   const int maxit = c->d.dev_refine_steps > 0 ? c->d.dev_refine_steps : REFINE_ITERS_DEV;
   {
     GateScope g(fl + F_ACTIVE);
@@ -569,17 +564,17 @@ void subspace_solve_dev(sky_ctx* c, int s) {
       return;
   }
   loewdin_series_dev(I, Linv, c->at(c->lay.matC), T, m, LOEWDIN_SERIES_MAX,
-                     c->prec ? MIXED_SERIES_EPS : SERIES_EPS, c->at<double>(c->lay.nrm), sq, st, sqs,
+                     c->prec ? MIXED_SERIES_EPS : SERIES_EPS, c->at<double>(c->lay.nrm), st,
                      fl, db, s);
   {
     GateScope g(fl + F_ACTIVE);
-    gemm_square(Linv, 0, H, 0, T, m, st, sq, 0, sqs);
-    gemm_square(T, 0, Linv, 0, Hp, m, st, sq, 1, sqs);
+    gemm_square(Linv, 0, H, 0, T, m, st);
+    gemm_square(T, 0, Linv, 0, Hp, m, st, 1);
   }
   refine_eigh_dev(Hp, m, c->at<double>(c->lay.ritz[s]), Z, c->at(c->lay.ref_work),
-                  c->prec ? REFINE_MIXED : REFINE_FP64, maxit, st, sqs, fl, s);
+                  c->prec ? REFINE_MIXED : REFINE_FP64, maxit, st, fl, s);
   GateScope g(fl + F_ACTIVE);
-  gemm_square(Linv, 0, Z, 0, U, m, st, sq, 0, sqs);
+  gemm_square(Linv, 0, Z, 0, U, m, st);
 }
 
 // Unitary polar factor P of the k x k complex matrix G (row-major; G = P S
@@ -647,14 +642,12 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
   void* Z = c->at(c->lay.matZ);
   void* U = c->at(c->lay.matU);
   void* Cw = c->at(c->lay.matC);
-  void* sq = c->at(c->lay.sq_part);
   int* info = c->at<int>(c->lay.info);
-  const int sqs = c->tune.sq[q];
   const int ts = t_begin(c, SKY_PHASE_SUBSPACE, q);
   hipMemsetAsync(info, 0, sizeof(int), st);
   // 3c: C = I^-1/2, by the series near the identity, else by the eigenvectors of I
   const int terms = loewdin_series(I, C, Cw, T, m, LOEWDIN_SERIES_MAX,
-                                   c->at<double>(c->lay.nrm), sq, st, c->host, sqs);
+                                   c->at<double>(c->lay.nrm), st, c->host);
   if (terms < 0) return fail(SKY_ERR_NAN, "non-finite overlap matrix");
   if (terms == 0) {
     double* wi = c->at<double>(c->lay.wtmp);
@@ -664,7 +657,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
     hipMemcpyAsync(T, X, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
     inv_sqrt(wi, m, info, st, CHOL_PIVOT_MIN);
     scale_columns(T, wi, m, st);
-    gemm_square(T, 0, X, 1, C, m, st, sq, 1, sqs);
+    gemm_square(T, 0, X, 1, C, m, st, 1);
     rc = check_info(c, "paper update: overlap");
     if (rc) return rc;
   }
@@ -672,7 +665,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
   double* w = ritz ? ritz : c->at<double>(c->lay.ritz[s]);
   const RefineTargets tg{JACOBI_TOL, c->prec ? MIXED_HP_NOISE : 0x1p-49, REFINE_FP64.orth,
                          REFINE_FP64.e2skip};
-  int its = refine_eigh(H, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host, sqs);
+  int its = refine_eigh(H, m, w, Z, c->at(c->lay.ref_work), tg, REFINE_ITERS, st, c->host);
   if (its < 0) {
     ++c->fallbacks;
     hipMemcpyAsync(X, H, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
@@ -730,7 +723,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
   hipMemcpyAsync(T, blocks.data(), packed * 16, hipMemcpyHostToDevice, st);
   gauge_apply(Z, m, dinfo, T, X, st);     // X = Z Q (block-diagonal Q)
   // 3d: U = Z C
-  gemm_square(X, 0, C, 0, U, m, st, sq, 0, sqs);
+  gemm_square(X, 0, C, 0, U, m, st);
   rc = hip_check(hipStreamSynchronize(st), "paper update");   // host blocks leave scope
   if (rc) return rc;
   t_end(c, ts);
@@ -808,7 +801,7 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   hipMemcpyAsync(wi, w, sizeof(double) * m, hipMemcpyDeviceToDevice, st);
   inv_sqrt(wi, m, info, st, CHOL_PIVOT_MIN);
   scale_columns(c->at(c->lay.matT), wi, m, st);
-  gemm_square(c->at(c->lay.matT), 0, X, 1, C, m, st, c->at(c->lay.sq_part), 1, c->tune.sq[q]);
+  gemm_square(c->at(c->lay.matT), 0, X, 1, C, m, st, 1);
   int rc = check_info(c, "loewdin");
   if (rc) return rc;
   if (c->prec) {
@@ -1825,20 +1818,11 @@ int sky_autotune(sky_ctx* c, const char* cache_path, sky_tuning* out) {
       }
       c->tune.cbw[q] = cw;
     }
-    // square-product split-K
-    int cs[4];
-    const int ns = square_split_candidates(m, cs);
+    // the square products split their contraction inside a workgroup; saved
+    // files keep the factor they held, a new entry is 1
     v = cache_get(kv, ksq[q]);
-    ok = false;
-    for (int i = 0; i < ns; ++i) ok = ok || cs[i] == v;
-    if (!ok) {
-      v = pick(st, cs, ns, [&](int sp) {
-        gemm_square(c->at(c->lay.matI), 1, c->at(c->lay.matH), 0, c->at(c->lay.matT), m, st,
-                    c->at(c->lay.sq_part), 0, sp);
-      });
-      cache_put(kv, ksq[q], v);
-      ++timed;
-    }
+    if (v != 1 && v != 2 && v != 4 && v != 8) v = 1;
+    cache_put(kv, ksq[q], v);
     c->tune.sq[q] = v;
   }
   rc = hip_check(hipStreamSynchronize(st), "autotune runs");

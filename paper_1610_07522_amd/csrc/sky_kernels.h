@@ -236,15 +236,10 @@ void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,
 // Y[b][v] = sum_a U[a][b] X[a][v]   (psi = phi U), X: m x k, U: m x m (ld m)
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st);
 // C = op(A) op(B), square m x m; opA/opB: 0 = N, 1 = conjugate transpose.
-// With part (>= gemm_square_scratch_bytes(m)) the contraction is split over
-// more workgroups and the FP64 partials are summed in a fixed order.  herm:
-// the product is known to be Hermitian; only its lower tiles are computed and
-// the upper triangle is mirrored from them (C exactly Hermitian).
-size_t gemm_square_scratch_bytes(int m);
-// split_req > 0 overrides the split-K factor (one of square_split_candidates).
-int square_split_candidates(int m, int* out);
+// herm: the product is known to be Hermitian; only its lower tiles are
+// computed and the upper triangle is mirrored from them (C exactly Hermitian).
 void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st,
-                 void* part = nullptr, int herm = 0, int split_req = 0);
+                 int herm = 0);
 
 // ---- eigenvector refinement (k_refine.hip)
 // Hermitian eigen-decomposition of a nearly diagonal A (m x m, not modified)
@@ -271,7 +266,7 @@ struct RefineTargets {
   double e2skip;   // an update forms its E^2/2 term while max |E| > e2skip
 };
 int refine_eigh(const void* A, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                int maxit, hipStream_t st, double* host, int sq_split = 0);
+                int maxit, hipStream_t st, double* host);
 // The same refinement with its decisions on the device (launches only): up
 // to maxit steps, each gated by flags[F_REF_RUN]; the check after step it
 // sorts the eigenpairs out when converged (flags[F_REF_OK + it]); a step
@@ -280,7 +275,7 @@ int refine_eigh(const void* A, int m, double* w, void* Z, void* work, const Refi
 // clears F_ACTIVE.  The E^2 term of the update is always formed.  maxit <=
 // F_NFLAGS - F_REF_OK - 1.
 void refine_eigh_dev(const void* A, int m, double* w, void* Z, void* work, const RefineTargets& tg,
-                     int maxit, hipStream_t st, int sq_split, int* flags, int set);
+                     int maxit, hipStream_t st, int* flags, int set);
 
 // ---- subspace solves of up to SMALL_M states in one workgroup (k_small.hip)
 // With I (the overlap): the series transform C = I^-1/2, H' = C H C, the
@@ -325,10 +320,10 @@ void gauge_apply(const void* Z, int m, const int* info, const void* Q, void* out
 // remainder (bounded through ||D||_2 <= ||D||_F) smaller than eps.
 // Returns p, 0 (nothing written to C) when ||D||_F > max_dev, or -1 when
 // ||D||_F is not a finite number.  D and T
-// are m x m work matrices, scratch >= 257 doubles, part the square-product
-// scratch (gemm_square), host as refine_eigh's; synchronises the stream.
+// are m x m work matrices, scratch >= 257 doubles, host as refine_eigh's;
+// synchronises the stream.
 int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_dev,
-                   double* scratch, void* part, hipStream_t st, double* host, int sq_split = 0,
+                   double* scratch, hipStream_t st, double* host,
                    double eps = 0x1p-56);
 // The series with the decision on the device: the term count from the norm
 // of D = I - 1 (as loewdin_series), Horner steps gated by flags[F_SERIES + k].
@@ -336,8 +331,7 @@ int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_d
 // get F_HOST = HOST_LOEWDIN (set `set`) and F_ACTIVE = 0.  dbl: the box's
 // doubles (D_SERIES..).  Launches only.
 void loewdin_series_dev(const void* I, void* C, void* D, void* T, int m, double max_dev,
-                        double eps, double* scratch, void* part, hipStream_t st, int sq_split,
-                        int* flags, double* dbl, int set);
+                        double eps, double* scratch, hipStream_t st, int* flags, double* dbl, int set);
 // End of a device-decided iteration (one workgroup, ungated): if the box is
 // active, F_ITER += 1 and Delta-eps = sqrt(sum of ||r||^2 over the first
 // nocc[s] states of each set s / count) goes to dbl[D_DE]; Delta-eps <=

@@ -87,6 +87,12 @@ def test_rayleigh_ritz_of_few_states(sizes):
     _check_degenerate(sizes)
 
 
+# the last order on sub-tiles of one block and the first on two (ragged)
+@pytest.mark.parametrize("m", [512, 513])
+def test_rayleigh_ritz_of_many_states(m):
+    _check_degenerate([1] * m)
+
+
 def _check_degenerate(sizes):
     """Ritz values, U^H I U = 1 and U^H H U = diag for phi a small step off
     eigenstates of an operator with degenerate levels."""
