@@ -157,6 +157,8 @@ enum {
                           /* spin-orbit, Coulomb, total (MeV) (q ignored)        */
   SKY_VIEW_EPS = 8,       /* Rayleigh quotients <psi|h|psi> of species q [n_q]   */
   SKY_VIEW_RITZ = 9,      /* ascending subspace eigenvalues of species q [n_q]   */
+                          /* (after sky_init_box: of the trial states' overlap,  */
+                          /* not a number where it was not diagonalised)         */
   SKY_VIEW_R2 = 10,       /* ||h psi - eps psi||^2 of species q [n_q]            */
   /* Subspace matrices of the last sky_orthonormalize / iteration, complex128
    * [n_q][n_q] row-major, valid for the species q of that call:          */

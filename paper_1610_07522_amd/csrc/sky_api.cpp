@@ -768,7 +768,28 @@ int rayleigh_ritz(sky_ctx* c, int s, const void* phi, const void* hphi, void* ps
   return SKY_OK;
 }
 
-int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
+// psi = phi C (C in matU; mixed: the planes of phi^T are in place).
+int loewdin_combine(sky_ctx* c, int q, const void* phi, void* psi_out) {
+  const int m = c->nq[q];
+  hipStream_t st = c->st;
+  void* C = c->at(c->lay.matU);
+  if (c->prec) {
+    unsigned int* mx = c->at<unsigned int>(c->lay.plS);
+    plane_scale(C, 1, size_t(m) * m, mx + 2, st);
+    split_planes_t(C, 1, m, m, mx + 2, c->at(c->lay.plU), st);
+    combine_planes(c->at(c->lay.plU), c->at(c->lay.plT), mx + 2, mx, psi_out, m, c->V, st);
+  } else {
+    combine(phi, C, psi_out, m, c->V, st);
+  }
+  return SKY_OK;
+}
+
+// Loewdin's orthonormalisation of set s.  eigen: by the eigenvectors of the
+// overlap, which the caller can then read; otherwise (above the orders that
+// one Jacobi workgroup solves) by Newton's iteration for I^-1/2, with the
+// eigenvectors where that does not converge; the set's eigenvalues are then
+// not a number.
+int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
   const int q = s & 1;
   const int m = c->nq[q];
   if (m == 0) return SKY_OK;
@@ -793,6 +814,13 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   } else
     overlap_lower(phi, phi, nullptr, m, c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st,
                   nullptr, c->tune.ovl[q]);
+  void* work[6] = {c->at(c->lay.matH),  c->at(c->lay.matHp), c->at(c->lay.matL),
+                   c->at(c->lay.matC), c->at(c->lay.matT),  X};
+  if (!eigen && m > SMALL_M &&
+      inverse_sqrt(I, C, work, m, c->at<double>(c->lay.wtmp), c->at<double>(c->lay.nrm), st, c->host)) {
+    fill(w, NAN, m, st);
+    return loewdin_combine(c, q, phi, psi_out);
+  }
   int its = jacobi_checked(c, I, m, w, X);
   if (its < 0) return its;
   // C = X diag(w^-1/2) X^H
@@ -804,14 +832,7 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out) {
   gemm_square(c->at(c->lay.matT), 0, X, 1, C, m, st, 1);
   int rc = check_info(c, "loewdin");
   if (rc) return rc;
-  if (c->prec) {
-    plane_scale(C, 1, size_t(m) * m, mx + 2, st);
-    split_planes_t(C, 1, m, m, mx + 2, c->at(c->lay.plU), st);
-    combine_planes(c->at(c->lay.plU), c->at(c->lay.plT), mx + 2, mx, psi_out, m, c->V, st);
-  } else {
-    combine(phi, C, psi_out, m, c->V, st);
-  }
-  return SKY_OK;
+  return loewdin_combine(c, q, phi, psi_out);
 }
 
 // Fig. 1 steps 4a, 4b, 5: densities of the occupied states of every set,
@@ -1378,7 +1399,7 @@ int sky_init_box(sky_ctx* c, const void* raw_n, const void* raw_p) {
   for (int q = 0; q < 2; ++q) {
     if (c->nq[q] == 0) continue;
     if (!raw[q]) return fail(SKY_ERR_INVALID, "null trial states");
-    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]));
+    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]), false);
     if (rc) return rc;
     const size_t ne = size_t(c->nq[q]) * c->V;
     for (int t = 1; t < c->ntw; ++t)   // every twist starts from the same states
@@ -1444,7 +1465,7 @@ int sky_orthonormalize(sky_ctx* c, int32_t q, const void* phi, const void* hphi,
   if (!c || q < 0 || q >= c->nset || !phi || !psi_out)
     return fail(SKY_ERR_INVALID, "orthonormalize arguments");
   c->last_sweeps = 0;
-  int rc = hphi ? rayleigh_ritz(c, q, phi, hphi, psi_out, ritz) : loewdin(c, q, phi, psi_out);
+  int rc = hphi ? rayleigh_ritz(c, q, phi, hphi, psi_out, ritz) : loewdin(c, q, phi, psi_out, true);
   if (rc) return rc;
   return hip_check(hipStreamSynchronize(c->st), "orthonormalize");
 }

@@ -325,6 +325,15 @@ void gauge_apply(const void* Z, int m, const int* info, const void* Q, void* out
 int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_dev,
                    double* scratch, hipStream_t st, double* host,
                    double eps = 0x1p-56);
+// C = I^-1/2 of a well-conditioned overlap by Newton's iteration on square
+// products.  work: six m x m matrices, rs: m doubles, scratch >= 257 doubles,
+// host as refine_eigh's; synchronises the stream.  False (C then undefined)
+// when it does not get there: small, zero or negative eigenvalues of I, or
+// values that are not finite.
+bool inverse_sqrt(const void* I, void* C, void* const* work, int m, double* rs, double* scratch,
+                  hipStream_t st, double* host);
+// w[0 .. n) = v
+void fill(double* w, double v, int n, hipStream_t st);
 // The series with the decision on the device: the term count from the norm
 // of D = I - 1 (as loewdin_series), Horner steps gated by flags[F_SERIES + k].
 // If the series does not apply (norm above max_dev or not finite), flags

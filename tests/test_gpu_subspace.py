@@ -118,3 +118,24 @@ def _check_degenerate(sizes):
     assert np.linalg.norm(d - np.diag(np.diag(d))) <= 4e-12 * np.linalg.norm(lam)
     psi = to_host(out).reshape(m, -1)
     assert np.abs(psi - u.T @ phi).max() <= 1e-12
+
+
+# 32: the last order left to the eigenvectors; condition numbers of the overlap that
+# Newton's iteration takes (to 1e6) and one that it leaves to them
+@pytest.mark.parametrize("cond", [1.0, 1e3, 1e6, 1e8])
+@pytest.mark.parametrize("m", [1, 32, 33, 65, 150])
+def test_initial_orthonormalisation(m, cond):
+    """sky_init_box's Loewdin states against numpy, and their overlap."""
+    n = 8
+    rng = np.random.default_rng(500 + m)
+    q = np.linalg.qr(rng.standard_normal((1024, m)) + 1j * rng.standard_normal((1024, m)))[0].T
+    z = np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))[0]
+    phi = (z * np.logspace(0, -0.5 * np.log10(cond), m)) @ q
+    raw = phi.reshape(m, 2, n, n, n)
+    box = _box(n, m)
+    box.init_box(to_dev(raw), to_dev(_states(rng, 1, n, np.complex128)))
+    psi = to_host(box.view("psi")).reshape(m, -1)
+    # rounding of I (m ulps of its norm) over its smallest eigenvalue
+    tol = 2.0 ** -52 * m * cond + 1e-13
+    assert np.abs(psi.conj() @ psi.T - np.eye(m)).max() <= tol
+    assert np.abs(psi - z @ q).max() <= tol
