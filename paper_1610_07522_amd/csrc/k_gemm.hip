@@ -241,7 +241,8 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 }
 
 // ----------------------------------------------------------- square products
-// C = op(A) op(B), op 0 = N, 1 = conjugate transpose; all m x m row-major.
+// C = op(A) op(B) + add 1, op 0 = N, 1 = conjugate transpose; all m x m row-major
+// (addp, if given, holds add).
 // MIRROR: a product known to be Hermitian; only sub-tiles on or below the
 // diagonal are computed, the upper triangle is their mirror image and the
 // diagonal real.  One sub-tile of NB x NB blocks per workgroup, the contraction
@@ -254,7 +255,8 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 template <int NB, int QW, int OPA, int OPB, bool MIRROR>
 __global__ void __launch_bounds__(64 * QW)
 k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
-                  double2* __restrict__ C, int m, const int* __restrict__ sky_gate) {
+                  double2* __restrict__ C, int m, double add, const double* __restrict__ addp,
+              const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   if (MIRROR && blockIdx.x > blockIdx.y) return;
   constexpr int QT = 16 * NB, NTH = 64 * QW;
@@ -326,6 +328,7 @@ k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
     double2 x = v[q];
     if (diag && i < j) x = make_double2(w[q].x, -w[q].y);
     if (diag && i == j) x.y = 0.0;
+    if (r0 + i == c0 + j) x.x += addp ? *addp : add;
     if (r0 + i < m && c0 + j < m) C[size_t(r0 + i) * m + c0 + j] = x;
     if (MIRROR && !diag && c0 + i < m && r0 + j < m)
       C[size_t(c0 + i) * m + r0 + j] = make_double2(w[q].x, -w[q].y);
@@ -404,14 +407,15 @@ void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t s
 // there (1600: 10.1 ms against 10.3).
 constexpr int SQ_NB1_MAX = 512;
 
-void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st, int herm) {
+void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st, int herm,
+                 double add, const double* addp) {
   if (m <= 0) return;
   auto go = [&](auto nb, auto qw) {
     constexpr int NB = decltype(nb)::value, QW = decltype(qw)::value;
     const unsigned nt = unsigned((m + 16 * NB - 1) / (16 * NB));
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(nt, nt), dim3(64 * QW), 0, st, (const double2*)A, (const double2*)B,
-                         (double2*)C, m, g_launch_gate);
+                         (double2*)C, m, add, addp, g_launch_gate);
     };
     if (opA == 0 && opB == 0) herm ? launch(k_gemm_square<NB, QW, 0, 0, true>) : launch(k_gemm_square<NB, QW, 0, 0, false>);
     else if (opA == 0) herm ? launch(k_gemm_square<NB, QW, 0, 1, true>) : launch(k_gemm_square<NB, QW, 0, 1, false>);

@@ -273,13 +273,6 @@ __global__ void k_axpy_identity(const double2* __restrict__ D, double a, double 
   P[e] = make_double2(a * d.x + ((e / m == e % m) ? c : 0.0), a * d.y);
 }
 
-// P += c 1
-__global__ void k_add_identity(double2* __restrict__ P, double c, int m, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m) P[size_t(i) * m + i].x += c;
-}
-
 // ------------------------------------------------------------------ Jacobi
 // Diagonalise the 32x32 pair sub-matrix of blocks (P, Q) of A (ld = mp)
 // and write its unitary J (32x32, row-major, local index l < 16 -> block P).
@@ -736,8 +729,7 @@ int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double m
   hipLaunchKernelGGL(k_axpy_identity, dim3(ge), dim3(256), 0, st, (const double2*)D, c[p], c[p - 1],
                      cur, m, g_launch_gate);
   for (int k = p - 2; k >= 0; --k) {
-    gemm_square(D, 0, cur, 0, nxt, m, st, 1);   // a polynomial in D: Hermitian
-    hipLaunchKernelGGL(k_add_identity, dim3((m + 255) / 256), dim3(256), 0, st, nxt, c[k], m, g_launch_gate);
+    gemm_square(D, 0, cur, 0, nxt, m, st, 1, c[k]);   // a polynomial in D: Hermitian
     std::swap(cur, nxt);
   }
   return p;
@@ -940,14 +932,6 @@ __global__ void k_series_start(const double2* __restrict__ D, const double* __re
   P[e] = make_double2(a * d.x + ((e / m == e % m) ? c : 0.0), a * d.y);
 }
 
-// P += c_k 1 with c_k from the device.
-__global__ void k_add_identity_dev(double2* __restrict__ P, const double* __restrict__ ck, int m,
-                                   const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m) P[size_t(i) * m + i].x += *ck;
-}
-
 void loewdin_series_dev(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double max_dev,
                         double eps, double* scratch, hipStream_t st, int* flags, double* dbl, int set) {
   if (m <= 0) return;
@@ -979,9 +963,7 @@ void loewdin_series_dev(const void* Iv, void* Cv, void* Dv, void* Tv, int m, dou
                      (const double*)dbl, C, T, m, active);
   for (int k = pcap - 2; k >= 0; --k) {
     GateScope g(flags + F_SERIES + k);
-    gemm_square(D, 0, buf[(k + 1) % 2], 0, buf[k % 2], m, st, 1);
-    hipLaunchKernelGGL(k_add_identity_dev, dim3((m + 255) / 256), dim3(256), 0, st, buf[k % 2],
-                       (const double*)(dbl + D_SERIES + 2 + k), m, g_launch_gate);
+    gemm_square(D, 0, buf[(k + 1) % 2], 0, buf[k % 2], m, st, 1, 0.0, dbl + D_SERIES + 2 + k);
   }
 }
 

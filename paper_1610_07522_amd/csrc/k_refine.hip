@@ -43,42 +43,45 @@ using namespace jrot;
 constexpr int KMAX = 48;            // widest cluster diagonalised in one workgroup (LDS: 3 x 48 x 49 x 16 B)
 constexpr int CHECK_BLOCKS = 256;
 
-// lam[i] = Re S_ii / (1 - Re R_ii)  (R may be null: R = 0); clears *emax.
-__global__ void k_ref_lambda(const double2* __restrict__ S, const double2* __restrict__ R, int m,
-                             double* __restrict__ lam, unsigned long long* __restrict__ emax, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *emax = 0ull;
-  if (i >= m) return;
-  const double r = R ? R[size_t(i) * m + i].x : 0.0;
-  lam[i] = S[size_t(i) * m + i].x / (1.0 - r);
-}
-
-// rank[i] = position of i in ascending (lam, index) order; order[rank] = i.
-// A workgroup ranks 64 values; each of its RANK_SPLIT waves counts over one
-// slice of the others, and the slice counts are summed in LDS.
-constexpr int RANK_SPLIT = 16;
+// lam[i] = Re S_ii / (1 - Re R_ii) (R may be null: R = 0), rank[i] = position of
+// i in ascending (lam, index) order, order[rank] = i; clears *e2flag, also
+// where the gate is off.  A workgroup makes the values in LDS, a tile at a
+// time, and ranks 64 of them; each of its RANK_SPLIT waves counts over one
+// slice of a tile, and the counts are summed in LDS.
+constexpr int RANK_SPLIT = 16, RANK_TILE = 2048;
 __global__ void __launch_bounds__(64 * RANK_SPLIT)
-k_ref_rank(const double* __restrict__ lam, int m, int* __restrict__ rank,
-           int* __restrict__ order, const int* __restrict__ sky_gate) {
+k_ref_rank(const double2* __restrict__ S, const double2* __restrict__ R, int m, double* __restrict__ lam,
+           int* __restrict__ e2flag, int* __restrict__ rank, int* __restrict__ order,
+           const int* __restrict__ sky_gate) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *e2flag = 0;
   if (sky_gate != nullptr && *sky_gate == 0) return;
+  __shared__ double tile[RANK_TILE];
   __shared__ int cnt[RANK_SPLIT][64];
+  auto value = [&](int j) {
+    const size_t e = size_t(j) * m + j;
+    return S[e].x / (1.0 - (R ? R[e].x : 0.0));
+  };
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
-  const double li = i < m ? lam[i] : 0.0;
-  const int per = (m + RANK_SPLIT - 1) / RANK_SPLIT;
-  const int j0 = min(m, wv * per), j1 = min(m, j0 + per);
+  const double li = i < m ? value(i) : 0.0;
   int r = 0;
-  if (i < m)
-    for (int j = j0; j < j1; ++j) {
-      const double lj = lam[j];
-      r += (lj < li || (lj == li && j < i)) ? 1 : 0;
+  for (int t0 = 0; t0 < m; t0 += RANK_TILE) {
+    const int nt = min(RANK_TILE, m - t0), per = (nt + RANK_SPLIT - 1) / RANK_SPLIT;
+    if (t0) __syncthreads();
+    for (int j = threadIdx.x; j < nt; j += blockDim.x) tile[j] = value(t0 + j);
+    __syncthreads();
+    const int j1 = min(nt, (wv + 1) * per);
+    for (int j = wv * per; j < j1; ++j) {
+      const double lj = tile[j];
+      r += (lj < li || (lj == li && t0 + j < i)) ? 1 : 0;
     }
+  }
   cnt[wv][lane] = r;
   __syncthreads();
   if (wv != 0 || i >= m) return;
   int t = 0;
   for (int k = 0; k < RANK_SPLIT; ++k) t += cnt[k][lane];
+  lam[i] = li;
   rank[i] = t;
   order[t] = i;
 }
@@ -387,9 +390,10 @@ k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int 
   if (lane == 0) lam2[a] = s2 / (1.0 - r2);
 }
 
-// E in the cluster-rotated sorted basis (m x m, row a, column b), and
-// *emax = max |E_ab|.  A pair of
-// different clusters whose coupling (both orientations) is at the rounding
+// E in the cluster-rotated sorted basis (m x m, row a, column b), and *e2flag
+// = 1 where some |E_ab| > e2skip: below, the E^2/2 term is under the precision
+// that the refinement works to (the flag gates its product and tells
+// k_ref_build_q to use it).  A pair of different clusters whose coupling (both orientations) is at the rounding
 // floor tau of the products is converged: it gets the orthonormality term
 // only.  (Its first-order coefficient would be rounding noise over a gap
 // that can itself be at rounding level, e.g. an exact Kramers pair, and would
@@ -397,7 +401,7 @@ k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int 
 __global__ void __launch_bounds__(256)
 k_ref_update(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
              const double* __restrict__ lam2, const double* __restrict__ taup,
-             double2* __restrict__ E, unsigned long long* __restrict__ emax, const int* __restrict__ sky_gate) {
+             double2* __restrict__ E, double e2skip, int* __restrict__ e2flag, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   const double tau = *taup;
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
@@ -426,23 +430,22 @@ k_ref_update(const double2* __restrict__ S, const double2* __restrict__ R, int m
     E[size_t(a) * m + b] = e;
     mag = hypot(e.x, e.y);
   }
-  // largest |E_ab| (bit patterns of non-negative doubles order like integers)
-#pragma unroll
+  #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mag = fmax(mag, __shfl_xor(mag, o));
-  if ((threadIdx.x & 63) == 0) atomicMax(emax, (unsigned long long)__double_as_longlong(mag));
+  if ((threadIdx.x & 63) == 0 && mag > e2skip) *e2flag = 1;
 }
 
 // k_ref_update with one workgroup per sorted row a: the row a of B^H S (and
 // B^H R), in the original column order, is formed once in LDS from the ka
 // rows of a's cluster (coalesced reads), and column b then combines the kb
-// entries of its own cluster from LDS.  Same E and *emax; the two sums of the
+// entries of its own cluster from LDS.  Same E and flag; the two sums of the
 // sandwich are taken in the other order.  Dynamic LDS: (R ? 2 : 1) * m
 // complex values.
 template <bool HAS_R>
 __global__ void __launch_bounds__(256)
 k_ref_update_rows(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
                   const double* __restrict__ lam2, const double* __restrict__ taup,
-                  double2* __restrict__ E, unsigned long long* __restrict__ emax,
+                  double2* __restrict__ E, double e2skip, int* __restrict__ e2flag,
                   const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   extern __shared__ double2 ref_row[];
@@ -506,27 +509,27 @@ k_ref_update_rows(const double2* __restrict__ S, const double2* __restrict__ R, 
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mag = fmax(mag, __shfl_xor(mag, o));
-  if ((threadIdx.x & 63) == 0) atomicMax(emax, (unsigned long long)__double_as_longlong(mag));
+  if ((threadIdx.x & 63) == 0 && mag > e2skip) *e2flag = 1;
 }
 
 constexpr size_t REF_ROW_LDS_MAX = 65536;   // dynamic LDS of k_ref_update_rows at most
 
-// E and *emax of one refinement step: by rows through LDS where two rows of
+// E and the flag of one refinement step: by rows through LDS where two rows of
 // m complex values fit, else one thread per entry.
 void ref_update(const double2* Sp, const double2* Rp, int m, const Clusters& cl, const double* lam2,
-                const double* tau, double2* E, unsigned long long* emax, hipStream_t st) {
+                const double* tau, double2* E, double e2skip, int* e2flag, hipStream_t st) {
   const size_t lds = size_t(Rp ? 2 : 1) * m * sizeof(double2);
   if (lds <= REF_ROW_LDS_MAX) {
     if (Rp)
       hipLaunchKernelGGL(k_ref_update_rows<true>, dim3(unsigned(m)), dim3(256), lds, st, Sp, Rp, m, cl,
-                         lam2, tau, E, emax, g_launch_gate);
+                         lam2, tau, E, e2skip, e2flag, g_launch_gate);
     else
       hipLaunchKernelGGL(k_ref_update_rows<false>, dim3(unsigned(m)), dim3(256), lds, st, Sp, Rp, m, cl,
-                         lam2, tau, E, emax, g_launch_gate);
+                         lam2, tau, E, e2skip, e2flag, g_launch_gate);
   } else {
     const unsigned gm = unsigned((m + 255) / 256);
     hipLaunchKernelGGL(k_ref_update, dim3(gm, unsigned(m)), dim3(256), 0, st, Sp, Rp, m, cl, lam2, tau,
-                       E, emax, g_launch_gate);
+                       E, e2skip, e2flag, g_launch_gate);
   }
 }
 
@@ -551,17 +554,6 @@ k_ref_build_q(const double2* __restrict__ E, const double2* __restrict__ E2v, co
     acc = cadd(acc, Wc ? cmul(Wc[(s - c) * KMAX + t], q) : q);
   }
   Q[size_t(cl.order[s]) * m + b] = acc;
-}
-
-// Whether the step forms E^2/2: max |E| above e2skip (below, the term is
-// under the precision the refinement works to).  Decided on the device (the
-// flag gates the E^2 product and tells k_ref_build_q to use it); 0 when the
-// run flag is off.
-__global__ void k_ref_e2_flag(const unsigned long long* __restrict__ emax, const int* __restrict__ run,
-                              double e2skip, int* __restrict__ flag) {
-  if (threadIdx.x != 0) return;
-  const double em = __longlong_as_double((long long)*emax);
-  *flag = ((run == nullptr || *run != 0) && !(em <= e2skip)) ? 1 : 0;
 }
 
 // S <- (S + S^H) / 2 and R <- 1 - (G + G^H) / 2 in place (R holds G = X^H X
@@ -649,20 +641,14 @@ k_ref_diag2(const double2* __restrict__ A, int m, double noise, double* __restri
   if (threadIdx.x == 0) tau[0] = noise * sqrt((red[0] + red[1] + red[2] + red[3]) / m);
 }
 
-// tau = noise * rms eigenvalue from the diagonal norm of the last check.
-__global__ void k_ref_tau(const double* __restrict__ norms, int m, double noise,
-                          double* __restrict__ tau, const int* __restrict__ sky_gate) {
-  if (sky_gate != nullptr && *sky_gate == 0) return;
-  if (threadIdx.x == 0) tau[0] = noise * sqrt(norms[1] / m);
-}
-
 // Sums of the check's block partials over 64 lanes (lane t takes blocks
 // t, t + 64, ... in order, then a fixed butterfly), NaN-propagating max.
-// With host (host-visible memory): the norms and the widest cluster of the
-// step, for the host's stop test.
+// out[4] = the noise floor tau of the next step, noise x the rms eigenvalue from
+// the diagonal norm.  With host (host-visible memory): the norms and the
+// widest cluster of the step, for the host's stop test.
 __global__ void k_ref_check_final(const double* __restrict__ part, int nb, double* __restrict__ out,
-                                  const int* __restrict__ info, double* __restrict__ host,
-                                  const int* __restrict__ sky_gate) {
+                                  const int* __restrict__ info, int m, double noise,
+                                  double* __restrict__ host, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   const int t = threadIdx.x;
   if (t >= 64) return;
@@ -684,6 +670,7 @@ __global__ void k_ref_check_final(const double* __restrict__ part, int nb, doubl
     out[0] = o;
     out[1] = d;
     out[2] = r;
+    out[4] = noise * sqrt(d / m);
     if (host != nullptr) {
       host[0] = o;
       host[1] = d;
@@ -699,7 +686,6 @@ unsigned cluster_threads(int m) { return unsigned(std::min(CL_THREADS, (m + 63) 
 struct RefineWork {
   double2 *mat[7], *W;
   double *lam, *lam2, *part, *norms;
-  unsigned long long* emax;
   int *rank, *order, *reach, *pm, *cstart, *csize, *cslot, *info;
   int2* clist;
   char* end;
@@ -720,7 +706,6 @@ RefineWork carve(void* work, int m) {
   r.lam2 = dbl(m);
   r.part = dbl(3 * CHECK_BLOCKS);
   r.norms = dbl(8);   // [0..2] check norms, [4] noise floor tau
-  r.emax = reinterpret_cast<unsigned long long*>(dbl(1));
   r.rank = in(m);
   r.order = in(m);
   r.reach = in(m);
@@ -776,7 +761,7 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
       hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                          r.part, g_launch_gate);
       hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
-                         int(ncheck), r.norms, (const int*)r.info, host, g_launch_gate);
+                         int(ncheck), r.norms, (const int*)r.info, m, noise, host, g_launch_gate);
       if (hipStreamSynchronize(st) != hipSuccess) return -1;
       const double* h = host;
       if (!(h[0] == h[0]) || !(h[1] == h[1]) || !(h[2] == h[2]) || h[3] > KMAX) return -1;
@@ -787,10 +772,10 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
       if (it >= maxit) return -1;
       Sp = S;
       Rp = R;
-      hipLaunchKernelGGL(k_ref_tau, dim3(1), dim3(64), 0, st, (const double*)r.norms, m, noise, tau, g_launch_gate);
     }
-    hipLaunchKernelGGL(k_ref_lambda, dim3(gm), dim3(256), 0, st, Sp, Rp, m, r.lam, r.emax, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, (const double*)r.lam, m, r.rank, r.order, g_launch_gate);
+    int* e2 = r.info + 3;
+    hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, Sp, Rp, m, r.lam, e2,
+                       r.rank, r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
                        (const int*)r.rank, m, REF_THETA, (const double*)tau, r.reach, g_launch_gate);
     hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
@@ -799,12 +784,9 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W, tol * 1e-2, g_launch_gate);
     hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
-    ref_update(Sp, Rp, m, cl, r.lam2, tau, E, r.emax, st);
+    ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     // E^2/2 only while |E| > e2skip, decided on the device (as in the
     // device-decided refinement, so that the two take the same arithmetic)
-    int* e2 = r.info + 3;
-    hipLaunchKernelGGL(k_ref_e2_flag, dim3(1), dim3(64), 0, st, (const unsigned long long*)r.emax,
-                       g_launch_gate, tg.e2skip, e2);
     {
       GateScope g2(e2);
       gemm_square(E, 0, E, 0, T, m, st);
@@ -883,7 +865,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
         hipLaunchKernelGGL(k_ref_check, dim3(ncheck), dim3(256), 0, st, S, R, m, (const double*)tau,
                            r.part, g_launch_gate);
         hipLaunchKernelGGL(k_ref_check_final, dim3(1), dim3(64), 0, st, (const double*)r.part,
-                           int(ncheck), r.norms, (const int*)r.info, (double*)nullptr, g_launch_gate);
+                           int(ncheck), r.norms, (const int*)r.info, m, noise, (double*)nullptr, g_launch_gate);
       }
       hipLaunchKernelGGL(k_ref_decide, dim3(1), dim3(64), 0, st, (const double*)r.norms,
                          (const int*)r.info, tol, orth, it, maxit, flags, set);
@@ -894,14 +876,11 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
       if (it == maxit) break;
       Sp = S;
       Rp = R;
-      GateScope g(run);
-      hipLaunchKernelGGL(k_ref_tau, dim3(1), dim3(64), 0, st, (const double*)r.norms, m, noise, tau,
-                         g_launch_gate);
     }
     GateScope g(run);
-    hipLaunchKernelGGL(k_ref_lambda, dim3(gm), dim3(256), 0, st, Sp, Rp, m, r.lam, r.emax, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, (const double*)r.lam, m, r.rank,
-                       r.order, g_launch_gate);
+    int* e2 = r.info + 3;
+    hipLaunchKernelGGL(k_ref_rank, dim3((m + 63) / 64), dim3(64 * RANK_SPLIT), 0, st, Sp, Rp, m, r.lam, e2,
+                       r.rank, r.order, g_launch_gate);
     hipLaunchKernelGGL(k_ref_reach, dim3(m), dim3(256), 0, st, Sp, Rp, (const double*)r.lam,
                        (const int*)r.rank, m, REF_THETA, (const double*)tau, r.reach, g_launch_gate);
     hipLaunchKernelGGL(k_ref_clusters, dim3(1), dim3(cluster_threads(m)), 0, st, (const int*)r.reach, m, r.pm,
@@ -911,10 +890,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
                        tol * 1e-2, g_launch_gate);
     hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
-    ref_update(Sp, Rp, m, cl, r.lam2, tau, E, r.emax, st);
-    int* e2 = r.info + 3;
-    hipLaunchKernelGGL(k_ref_e2_flag, dim3(1), dim3(64), 0, st, (const unsigned long long*)r.emax,
-                       run, tg.e2skip, e2);
+    ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     {
       GateScope g2(e2);
       gemm_square(E, 0, E, 0, T, m, st);

@@ -235,11 +235,12 @@ void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,
                     int waves = 8);
 // Y[b][v] = sum_a U[a][b] X[a][v]   (psi = phi U), X: m x k, U: m x m (ld m)
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st);
-// C = op(A) op(B), square m x m; opA/opB: 0 = N, 1 = conjugate transpose.
+// C = op(A) op(B) + add 1, square m x m; opA/opB: 0 = N, 1 = conjugate transpose;
+// add from device memory where addp is given.
 // herm: the product is known to be Hermitian; only its lower tiles are
 // computed and the upper triangle is mirrored from them (C exactly Hermitian).
 void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st,
-                 int herm = 0);
+                 int herm = 0, double add = 0.0, const double* addp = nullptr);
 
 // ---- eigenvector refinement (k_refine.hip)
 // Hermitian eigen-decomposition of a nearly diagonal A (m x m, not modified)
