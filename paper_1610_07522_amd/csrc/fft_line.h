@@ -17,10 +17,9 @@
 // loaded the input.  Forward sign: X[k] = sum_n x[n] exp(-2 pi i n k / N);
 // neither direction scales: the 1/N of the inverse goes into the multiplier.
 //
-// The complex64 passes issue as many vector instructions as their memory time
-// holds (48^3: about 1500 per line pair and pass, 1.17 ms for 1600 states at
-// one per cycle, against 1.2 to 1.9 ms per pass), so the transforms are kept
-// lean: twiddle-free and multiply-add forms of the small DFTs, no products
+// The complex64 passes are bound by vector issue as much as by memory (48^3:
+// the z pass of h psi issues in 92% of its cycles, the slice pass in 75%), so the
+// transforms are kept lean: twiddle-free and multiply-add forms of the small DFTs, no products
 // by w^0, one multiplier per frequency, twiddles from a table.
 #pragma once
 
