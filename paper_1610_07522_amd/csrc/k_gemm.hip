@@ -241,8 +241,9 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 }
 
 // ----------------------------------------------------------- square products
-// C = op(A) op(B) + add 1, op 0 = N, 1 = conjugate transpose; all m x m row-major
-// (addp, if given, holds add).
+// C = alpha op(A) op(B) + add 1, op 0 = N, 1 = conjugate transpose; all m x m
+// row-major (addp, if given, holds add).  Grid (column, row sub-tiles, products):
+// one or two independent products of the same form.
 // MIRROR: a product known to be Hermitian; only sub-tiles on or below the
 // diagonal are computed, the upper triangle is their mirror image and the
 // diagonal real.  One sub-tile of NB x NB blocks per workgroup, the contraction
@@ -252,13 +253,19 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 // contraction is zero past it.  64 x 64 tiles staged in LDS, split over
 // workgroups and summed by a second launch, took 13 us at 150 states where this
 // takes 6, and as long at 1600.
+struct SquareArgs {
+  const double2 *A, *B;
+  double2* C;
+};
 template <int NB, int QW, int OPA, int OPB, bool MIRROR>
 __global__ void __launch_bounds__(64 * QW)
-k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
-                  double2* __restrict__ C, int m, double add, const double* __restrict__ addp,
-              const int* __restrict__ sky_gate) {
+k_gemm_square(SquareArgs g0, SquareArgs g1, int m, double alpha, double add,
+              const double* __restrict__ addp, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   if (MIRROR && blockIdx.x > blockIdx.y) return;
+  const double2* __restrict__ A = blockIdx.z ? g1.A : g0.A;
+  const double2* __restrict__ B = blockIdx.z ? g1.B : g0.B;
+  double2* __restrict__ C = blockIdx.z ? g1.C : g0.C;
   constexpr int QT = 16 * NB, NTH = 64 * QW;
   __shared__ double red[QW][QT][QT + 1];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kq = lane >> 4;
@@ -327,11 +334,13 @@ k_gemm_square(const double2* __restrict__ A, const double2* __restrict__ B,
     const bool diag = MIRROR && r0 == c0;
     double2 x = v[q];
     if (diag && i < j) x = make_double2(w[q].x, -w[q].y);
+    x.x *= alpha;
+    x.y *= alpha;
     if (diag && i == j) x.y = 0.0;
     if (r0 + i == c0 + j) x.x += addp ? *addp : add;
     if (r0 + i < m && c0 + j < m) C[size_t(r0 + i) * m + c0 + j] = x;
     if (MIRROR && !diag && c0 + i < m && r0 + j < m)
-      C[size_t(c0 + i) * m + r0 + j] = make_double2(w[q].x, -w[q].y);
+      C[size_t(c0 + i) * m + r0 + j] = make_double2(alpha * w[q].x, -alpha * w[q].y);
   }
 }
 
@@ -407,15 +416,16 @@ void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t s
 // there (1600: 10.1 ms against 10.3).
 constexpr int SQ_NB1_MAX = 512;
 
-void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st, int herm,
-                 double add, const double* addp) {
+namespace {
+void square(const SquareArgs& g0, const SquareArgs& g1, int count, int opA, int opB, int m, hipStream_t st,
+            int herm, double alpha, double add, const double* addp) {
   if (m <= 0) return;
   auto go = [&](auto nb, auto qw) {
     constexpr int NB = decltype(nb)::value, QW = decltype(qw)::value;
     const unsigned nt = unsigned((m + 16 * NB - 1) / (16 * NB));
     auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(nt, nt), dim3(64 * QW), 0, st, (const double2*)A, (const double2*)B,
-                         (double2*)C, m, add, addp, g_launch_gate);
+      hipLaunchKernelGGL(kernel, dim3(nt, nt, unsigned(count)), dim3(64 * QW), 0, st, g0, g1, m, alpha, add,
+                         addp, g_launch_gate);
     };
     if (opA == 0 && opB == 0) herm ? launch(k_gemm_square<NB, QW, 0, 0, true>) : launch(k_gemm_square<NB, QW, 0, 0, false>);
     else if (opA == 0) herm ? launch(k_gemm_square<NB, QW, 0, 1, true>) : launch(k_gemm_square<NB, QW, 0, 1, false>);
@@ -424,6 +434,22 @@ void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m,
   };
   if (m <= SQ_NB1_MAX) go(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
   else go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+}
+
+SquareArgs square_args(const void* A, const void* B, void* C) {
+  return SquareArgs{(const double2*)A, (const double2*)B, (double2*)C};
+}
+}  // namespace
+
+void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st, int herm,
+                 double add, const double* addp, double alpha) {
+  const SquareArgs g = square_args(A, B, C);
+  square(g, g, 1, opA, opB, m, st, herm, alpha, add, addp);
+}
+
+void gemm_square_pair(const void* A0, const void* B0, void* C0, const void* A1, const void* B1, void* C1, int m,
+                      hipStream_t st) {
+  square(square_args(A0, B0, C0), square_args(A1, B1, C1), 2, 0, 0, m, st, 0, 1.0, 0.0, nullptr);
 }
 
 }  // namespace sky

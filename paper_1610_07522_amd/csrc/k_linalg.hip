@@ -744,8 +744,8 @@ int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double m
 // (300 states): 2e-15, 5e-15, 4e-14 against 4e-14, 7e-14, 2e-13 by
 // eigenvectors; near 1e6 the two are level, so the steps are limited to what
 // overlaps to about 1e3 take.
-// Three square products a step against some 40 launches of a Jacobi sweep:
-// 151 + 50 trial states at 24^3, initialisation 4990 -> 880 us.
+// Two launches a step, the two updates in one, against some 40 of a Jacobi sweep:
+// 151 + 50 trial states at 24^3, initialisation 4990 -> 790 us.
 constexpr int NEWTON_STEPS = 13;
 constexpr double NEWTON_DEFECT = 1e-8;   // of C I C before its last step: the square is below rounding
 
@@ -788,23 +788,12 @@ k_scale_by_norm(const double2* __restrict__ X, const double* __restrict__ rs, in
     Y[e] = make_double2(f * X[e].x, f * X[e].y);
 }
 
-// T = 1 + (1 - P) / 2, part[block] = its share of ||1 - P||_F^2.
+// T = 1 + (1 - P) / 2.
 __global__ void __launch_bounds__(256)
-k_newton_half(const double2* __restrict__ P, double2* __restrict__ T, int m, double* __restrict__ part) {
-  double acc = 0.0;
+k_newton_half(const double2* __restrict__ P, double2* __restrict__ T, int m) {
   const size_t n = size_t(m) * m;
-  for (size_t e = size_t(blockIdx.x) * 256 + threadIdx.x; e < n; e += size_t(gridDim.x) * 256) {
-    const double one = e / m == e % m ? 1.0 : 0.0;
-    const double2 p = P[e], r = make_double2(one - p.x, -p.y);
-    T[e] = make_double2(one + 0.5 * r.x, 0.5 * r.y);
-    acc += r.x * r.x + r.y * r.y;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-  __shared__ double red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+  for (size_t e = size_t(blockIdx.x) * 256 + threadIdx.x; e < n; e += size_t(gridDim.x) * 256)
+    T[e] = make_double2((e / m == e % m ? 1.5 : 0.0) - 0.5 * P[e].x, -0.5 * P[e].y);
 }
 
 __global__ void k_fill(double* __restrict__ w, double v, int n) {
@@ -823,34 +812,31 @@ bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs
   for (int i = 0; i < 6; ++i) w[i] = (double2*)work[i];
   double2 *Y = w[0], *Yn = w[1], *Z = w[2], *Zn = w[3], *T = w[4], *P = w[5];
   const int nb = int(std::min<size_t>(256, (size_t(m) * m + 255) / 256));
-  auto half_step = [&](const double2* p, double2* t) {   // t = 1 + (1 - p) / 2
-    hipLaunchKernelGGL(k_newton_half, dim3(nb), dim3(256), 0, st, p, t, m, scratch);
-  };
-  auto norm = [&]() -> double {   // ||1 - p||_F of the last half step
+  // ||1 - Z Y||_F from t = 1 + (1 - Z Y) / 2 (d: work)
+  auto norm = [&](const double2* t, double2* d) -> double {
+    hipLaunchKernelGGL(k_minus_identity, dim3(nb), dim3(256), 0, st, t, d, m, scratch, (const int*)nullptr);
     hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, (const double*)scratch, nb, scratch + nb, host,
                        (const int*)nullptr);
-    return hipStreamSynchronize(st) == hipSuccess ? sqrt(host[0]) : HUGE_VAL;
+    return hipStreamSynchronize(st) == hipSuccess ? 2.0 * sqrt(host[0]) : HUGE_VAL;
   };
   // the order of the factors and the missing symmetrisation matter: rounding
   // errors that do not commute with I then stay bounded
   auto step = [&] {
-    gemm_square(Z, 0, Y, 0, P, m, st);
-    half_step(P, T);
-    gemm_square(T, 0, Z, 0, Zn, m, st);
-    gemm_square(Y, 0, T, 0, Yn, m, st);
+    gemm_square(Z, 0, Y, 0, T, m, st, 0, 1.5, nullptr, -0.5);
+    gemm_square_pair(T, Z, Zn, Y, T, Yn, m, st);
     std::swap(Z, Zn);
     std::swap(Y, Yn);
   };
   hipLaunchKernelGGL(k_row_sums, dim3((m + 3) / 4), dim3(256), 0, st, I, m, rs);
   hipLaunchKernelGGL(k_scale_by_norm<false>, dim3(nb), dim3(256), 0, st, I, (const double*)rs, m, Y);
-  half_step(Y, Z);   // the first step: Z_0 = 1
+  hipLaunchKernelGGL(k_newton_half, dim3(nb), dim3(256), 0, st, (const double2*)Y, Z, m);   // Z_0 = 1
   gemm_square(Y, 0, Z, 0, Yn, m, st, 1);
   std::swap(Y, Yn);
   int done = 0;
   for (int n = 7;; n = 3) {
     for (int k = 0; k < n; ++k) step();
     done += n;
-    double f = norm();   // before the last step
+    double f = norm(T, P);   // before the last step
     if (!std::isfinite(f)) return false;
     if (f < 0.7) {
       // the defect goes from f to at most 3/4 f^2 + 1/4 f^3
@@ -861,10 +847,9 @@ bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs
   }
   hipLaunchKernelGGL(k_scale_by_norm<true>, dim3(nb), dim3(256), 0, st, (const double2*)Z, (const double*)rs, m, Zn);
   gemm_square(Zn, 0, I, 0, T, m, st);
-  gemm_square(T, 0, Zn, 0, P, m, st, 1);
-  half_step(P, Y);
+  gemm_square(T, 0, Zn, 0, Y, m, st, 1, 1.5, nullptr, -0.5);
   gemm_square(Zn, 0, Y, 0, Cv, m, st, 1);
-  return norm() <= NEWTON_DEFECT;   // false for NaN
+  return norm(Y, P) <= NEWTON_DEFECT;   // false for NaN
 }
 
 // ------------------------------------------------------------------ device-decided steps

@@ -235,12 +235,15 @@ void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,
                     int waves = 8);
 // Y[b][v] = sum_a U[a][b] X[a][v]   (psi = phi U), X: m x k, U: m x m (ld m)
 void combine(const void* X, const void* U, void* Y, int m, long k, hipStream_t st);
-// C = op(A) op(B) + add 1, square m x m; opA/opB: 0 = N, 1 = conjugate transpose;
+// C = alpha op(A) op(B) + add 1, square m x m; opA/opB: 0 = N, 1 = conjugate transpose;
 // add from device memory where addp is given.
 // herm: the product is known to be Hermitian; only its lower tiles are
 // computed and the upper triangle is mirrored from them (C exactly Hermitian).
 void gemm_square(const void* A, int opA, const void* B, int opB, void* C, int m, hipStream_t st,
-                 int herm = 0, double add = 0.0, const double* addp = nullptr);
+                 int herm = 0, double add = 0.0, const double* addp = nullptr, double alpha = 1.0);
+// C0 = A0 B0 and C1 = A1 B1 in one launch.
+void gemm_square_pair(const void* A0, const void* B0, void* C0, const void* A1, const void* B1, void* C1, int m,
+                      hipStream_t st);
 
 // ---- eigenvector refinement (k_refine.hip)
 // Hermitian eigen-decomposition of a nearly diagonal A (m x m, not modified)
