@@ -247,8 +247,8 @@ k_combine(const double2* __restrict__ X, const double2* __restrict__ U, double2*
 // MIRROR: a product known to be Hermitian; only sub-tiles on or below the
 // diagonal are computed, the upper triangle is their mirror image and the
 // diagonal real.  One sub-tile of NB x NB blocks per workgroup, the contraction
-// split over its waves (wave g takes the chunks g, g + QW, ..; partials summed
-// in wave order through LDS).  Operands are loaded from L2 as in
+// split over its waves in consecutive ranges of at least two chunks, the
+// partials summed in wave order through LDS.  Operands are loaded from L2 as in
 // k_overlap_lower; the last row or column is repeated past m, and the
 // contraction is zero past it.  64 x 64 tiles staged in LDS, split over
 // workgroups and summed by a second launch, took 13 us at 150 states where this
@@ -290,13 +290,15 @@ k_gemm_square(SquareArgs g0, SquareArgs g1, int m, double alpha, double add,
     }
   };
   Sub<NB> acc;
+  const int split = min(QW, max(1, nk / 2));
+  const int kc0 = g < split ? nk * g / split : 0, kc1 = g < split ? nk * (g + 1) / split : 0;
 #pragma unroll
-  for (int q = 0; q < KQ; ++q) load(g, q);
-  for (int kc = g; kc < nk; kc += QW)
+  for (int q = 0; q < KQ; ++q) load(kc0, q);
+  for (int kc = kc0; kc < kc1; ++kc)
 #pragma unroll
     for (int q = 0; q < KQ; ++q) {
       acc.template step<OPA != 0>(a[q], b[q]);
-      load(kc + QW, q);
+      load(kc + 1, q);
     }
   // real parts, then imaginary parts, through LDS; element e of the thread is
   // (e / QT, e % QT) of the sub-tile

@@ -295,7 +295,7 @@ k_ref_cluster_eig(const double2* __restrict__ S, const double2* __restrict__ R, 
         rr_pair(np, r, lane, p, q);
         if (p > q) { const int t = p; p = q; q = t; }
         pair[wv][lane] = make_int2(p, q);
-        rot[wv][lane] = make_rot_rsq(M[p][p].x, M[q][q].x, M[p][q]);
+        rot[wv][lane] = make_rot(M[p][p].x, M[q][q].x, M[p][q]);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -363,31 +363,20 @@ struct Clusters {
 };
 
 // lam2[a] = Re S2_aa / (1 - Re R2_aa) in the cluster-rotated sorted basis.  One
-// wave per a: lane l takes the products l, l + 64, ... of the k x k sum, then a
-// fixed butterfly (one thread per a was bound by the widest cluster's k^2
-// serial loads: 28 us over the uneven boxes and 46 at 1600 states, now 6 and 5).
-__global__ void __launch_bounds__(256)
-k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
-              double* __restrict__ lam2, const int* __restrict__ sky_gate) {
+// thread per a, in the order of sandwich().  (A wave per a takes 6 us instead
+// of 28 over the uneven boxes, but sums in another order: the last rotations of
+// a cluster act on couplings near rounding, whose phases go into the
+// eigenvectors, and a solve far from diagonal then came out with other phases.)
+__global__ void k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m,
+                              Clusters cl, double* __restrict__ lam2, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int a = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= m) return;
-  const int s0 = cl.cstart[a], k = cl.csize[a], ta = a - s0;
+  const int s0 = cl.cstart[a], k = cl.csize[a];
   const double2* Wa = cl.w(a);
-  double s2 = 0.0, r2 = 0.0;
-  for (int e = lane; e < k * k; e += 64) {
-    const int s = e / k, u = e % k;
-    const size_t at = size_t(cl.order[s0 + s]) * m + cl.order[s0 + u];
-    const double2 w = Wa ? cconjmul(Wa[s * KMAX + ta], Wa[u * KMAX + ta]) : make_double2(1.0, 0.0);
-    s2 += cmul(S[at], w).x;
-    if (R) r2 += cmul(R[at], w).x;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    s2 += __shfl_xor(s2, o);
-    r2 += __shfl_xor(r2, o);
-  }
-  if (lane == 0) lam2[a] = s2 / (1.0 - r2);
+  const double s2 = sandwich(S, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x;
+  const double r2 = R ? sandwich(R, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x : 0.0;
+  lam2[a] = s2 / (1.0 - r2);
 }
 
 // E in the cluster-rotated sorted basis (m x m, row a, column b), and *e2flag
@@ -782,7 +771,7 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W, tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     // E^2/2 only while |E| > e2skip, decided on the device (as in the
@@ -888,7 +877,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W,
                        tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     {

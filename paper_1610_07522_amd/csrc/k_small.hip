@@ -201,7 +201,7 @@ __device__ inline void cluster_eig(const double2* S, const double2* R, const int
         if (p > q) { const int t = p; p = q; q = t; }
         cw.pair[wv][lane] = make_int2(p, q);
         Rot g{1.0, 0.0, 1.0, 0.0};
-        if (q < k) g = make_rot_rsq(M[p * LD + p].x, M[q * LD + q].x, M[p * LD + q]);
+        if (q < k) g = make_rot(M[p * LD + p].x, M[q * LD + q].x, M[p * LD + q]);
         cw.rot[wv][lane] = g;
       }
       wave_sync();
