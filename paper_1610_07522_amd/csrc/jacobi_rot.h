@@ -51,9 +51,8 @@ __device__ inline Rot make_rot(double a, double b, double2 apq) {
 // s = sign(d) r / (2 h c), from three reciprocal square roots.  The rotation
 // is a serial chain on the critical path of every Jacobi round, and divisions
 // and scaled hypots made up most of it (see k_jacobi_pair).  The
-// refinement's cluster solves keep make_rot: the mixed form iterates at the
-// rounding floor of H', where the basis they pick inside a degenerate shell is
-// carried from step to step.
+// refinement's cluster solves keep make_rot: their last rotations act on
+// couplings near rounding, whose phases go into the eigenvectors.
 __device__ inline Rot make_rot_rsq(double a, double b, double2 apq) {
   Rot g;
   // Couplings below 1e-18 of the diagonal scale are treated as converged (no

@@ -363,20 +363,39 @@ struct Clusters {
 };
 
 // lam2[a] = Re S2_aa / (1 - Re R2_aa) in the cluster-rotated sorted basis.  One
-// thread per a, in the order of sandwich().  (A wave per a takes 6 us instead
-// of 28 over the uneven boxes, but sums in another order: the last rotations of
-// a cluster act on couplings near rounding, whose phases go into the
-// eigenvectors, and a solve far from diagonal then came out with other phases.)
-__global__ void k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m,
-                              Clusters cl, double* __restrict__ lam2, const int* __restrict__ sky_gate) {
+// wave per a: lane s forms row s of the sandwich, and the rows are added in
+// order, so that the sums are those of sandwich() bit for bit.  (The last
+// rotations of a cluster act on couplings near rounding, whose phases go into
+// the eigenvectors: with another order a solve far from diagonal came out with
+// other phases.)  One thread per a was bound by the widest cluster's k^2
+// serial loads: 28 us over the uneven boxes, now about 10.
+__global__ void __launch_bounds__(256)
+k_ref_lambda2(const double2* __restrict__ S, const double2* __restrict__ R, int m, Clusters cl,
+              double* __restrict__ lam2, const int* __restrict__ sky_gate) {
+  static_assert(KMAX <= 64, "a lane per row of a cluster");
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+  const int a = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (a >= m) return;
-  const int s0 = cl.cstart[a], k = cl.csize[a];
+  const int s0 = cl.cstart[a], k = cl.csize[a], ta = a - s0;
   const double2* Wa = cl.w(a);
-  const double s2 = sandwich(S, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x;
-  const double r2 = R ? sandwich(R, m, cl.order, Wa, s0, k, a - s0, Wa, s0, k, a - s0).x : 0.0;
-  lam2[a] = s2 / (1.0 - r2);
+  double2 sv = make_double2(0.0, 0.0), rv = make_double2(0.0, 0.0);
+  if (lane < k) {
+    const size_t row = size_t(cl.order[s0 + lane]) * m;
+    for (int u = 0; u < k; ++u) {
+      const size_t at = row + cl.order[s0 + u];
+      sv = cadd(sv, Wa ? cmul(S[at], Wa[u * KMAX + ta]) : S[at]);
+      if (R) rv = cadd(rv, Wa ? cmul(R[at], Wa[u * KMAX + ta]) : R[at]);
+    }
+  }
+  double2 st = make_double2(0.0, 0.0), rt = make_double2(0.0, 0.0);
+  for (int s = 0; s < k; ++s) {
+    const double2 sa = make_double2(__shfl(sv.x, s, 64), __shfl(sv.y, s, 64));
+    const double2 ra = make_double2(__shfl(rv.x, s, 64), __shfl(rv.y, s, 64));
+    st = cadd(st, Wa ? cconjmul(Wa[s * KMAX + ta], sa) : sa);
+    rt = cadd(rt, Wa ? cconjmul(Wa[s * KMAX + ta], ra) : ra);
+  }
+  const double s2 = st.x, r2 = rt.x;
+  if (lane == 0) lam2[a] = s2 / (1.0 - r2);
 }
 
 // E in the cluster-rotated sorted basis (m x m, row a, column b), and *e2flag
@@ -771,7 +790,7 @@ int refine_eigh(const void* Av, int m, double* w, void* Z, void* work, const Ref
                        r.cstart, r.csize, r.cslot, r.clist, r.info, g_launch_gate);
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W, tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     // E^2/2 only while |E| > e2skip, decided on the device (as in the
@@ -877,7 +896,7 @@ void refine_eigh_dev(const void* Av, int m, double* w, void* Z, void* work, cons
     hipLaunchKernelGGL(k_ref_cluster_eig, dim3(unsigned(m / 2 + 1)), dim3(256), 0, st, Sp, Rp, m,
                        (const int*)r.order, (const int2*)r.clist, (const int*)r.info, r.W,
                        tol * 1e-2, g_launch_gate);
-    hipLaunchKernelGGL(k_ref_lambda2, dim3(gm), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
+    hipLaunchKernelGGL(k_ref_lambda2, dim3(unsigned((m + 3) / 4)), dim3(256), 0, st, Sp, Rp, m, cl, r.lam2,
                        g_launch_gate);
     ref_update(Sp, Rp, m, cl, r.lam2, tau, E, tg.e2skip, e2, st);
     {
