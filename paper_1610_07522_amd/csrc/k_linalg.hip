@@ -745,7 +745,7 @@ int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double m
 // eigenvectors; near 1e6 the two are level, so the steps are limited to what
 // overlaps to about 1e3 take.
 // Two launches a step, the two updates in one, against some 40 of a Jacobi sweep:
-// 151 + 50 trial states at 24^3, initialisation 4990 -> 790 us.
+// 151 + 50 trial states at 24^3, initialisation 4990 -> 800 us.
 constexpr int NEWTON_STEPS = 13;
 constexpr double NEWTON_DEFECT = 1e-8;   // of C I C before its last step: the square is below rounding
 
