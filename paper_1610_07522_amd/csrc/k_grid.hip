@@ -57,16 +57,18 @@ __device__ inline void h_local(const MeanFieldPtrs& mf, size_t r, cpx<T> vu, cpx
   dd = gd - B * dd;
 }
 
-// Workgroup sum of one double per thread (blockDim <= 256), result in thread 0.
-__device__ inline double block_sum(double v, double* red) {
+// Workgroup sum of one double per thread of a workgroup of THREADS threads,
+// result in thread 0; red has one entry per wave.
+constexpr int waves_of_threads(int threads) { return (threads + 63) / 64; }
+template <int THREADS>
+__device__ inline double block_sum(double v, double (&red)[waves_of_threads(THREADS)]) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) red[wave] = v;
   __syncthreads();
   double s = 0.0;
   if (threadIdx.x == 0) {
-    int nw = (blockDim.x + 63) >> 6;
-    for (int w = 0; w < nw; ++w) s += red[w];
+    for (int w = 0; w < waves_of_threads(THREADS); ++w) s += red[w];
   }
   __syncthreads();
   return s;
@@ -116,7 +118,7 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   __shared__ cpx<T> tw[N];
   __shared__ cpx<T> Ybuf[C::LPW * YS];
-  __shared__ double red[4];
+  __shared__ double red[waves_of_threads(C::THREADS)];
 
   int line, j;
   thread_role<N, DIR, LP>(threadIdx.x, line, j);
@@ -190,11 +192,11 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
     }
   }
   if (LAST && eps_part != nullptr) {
-    double sum = block_sum(dot, red);
+    double sum = block_sum<C::THREADS>(dot, red);
     if (threadIdx.x == 0) eps_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
   if (LAST && nrm_part != nullptr) {
-    double sum = block_sum(nrm, red);
+    double sum = block_sum<C::THREADS>(nrm, red);
     if (threadIdx.x == 0) nrm_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
   }
   if (LAST && amax != nullptr) block_amax(am, amax);
@@ -234,7 +236,7 @@ k_state_dots(const float2* __restrict__ a, const float2* __restrict__ b, long V,
              double* __restrict__ dot_part, double* __restrict__ nrm_part,
              unsigned int* __restrict__ mx, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
-  __shared__ double red[4];
+  __shared__ double red[waves_of_threads(256)];
   const size_t off = size_t(blockIdx.y) * V;
   double dot = 0.0, nrm = 0.0;
   float ma = 0.0f, mb = 0.0f;
@@ -249,11 +251,11 @@ k_state_dots(const float2* __restrict__ a, const float2* __restrict__ b, long V,
     }
   }
   const size_t at = size_t(blockIdx.y) * gridDim.x + blockIdx.x;
-  const double sn = block_sum(nrm, red);
+  const double sn = block_sum<256>(nrm, red);
   if (threadIdx.x == 0) nrm_part[at] = sn * dV;
   block_amax(ma, mx);
   if (b == nullptr) return;
-  const double sd = block_sum(dot, red);
+  const double sd = block_sum<256>(dot, red);
   if (threadIdx.x == 0) dot_part[at] = sd * dV;
   block_amax(mb, mx + 1);
 }
@@ -637,7 +639,7 @@ k_damp_fwd_x(const cpx<T>* __restrict__ psi, const cpx<T>* __restrict__ hpsi,
   constexpr int R1 = C::R1, R2 = C::R2, N3 = N * N * N;
   __shared__ cpx<T> tw[N];
   __shared__ cpx<T> Ybuf[C::LPW * YS];
-  __shared__ double red[4];
+  __shared__ double red[waves_of_threads(C::THREADS)];
   load_twiddles<T, N>(tw);
   int line, j;
   thread_role<N, 0>(threadIdx.x, line, j);
@@ -670,7 +672,7 @@ k_damp_fwd_x(const cpx<T>* __restrict__ psi, const cpx<T>* __restrict__ hpsi,
       out[soff + N3 + r] = vb[1][k2];
     }
   }
-  double sum = block_sum(r2, red);
+  double sum = block_sum<C::THREADS>(r2, red);
   if (threadIdx.x == 0) r2_part[size_t(blockIdx.y) * gridDim.x + blockIdx.x] = sum * g.dV;
 }
 
