@@ -723,18 +723,6 @@ k_damp_y(cpx<T>* __restrict__ buf, const int* __restrict__ sky_gate) {
   }
 }
 
-// a / b in FP64; for complex64 states, which round the quotient to FP32, from
-// the reciprocal estimate and one Newton step (within 2^-45, a third of the
-// instructions of the exact division).
-template <typename T> __device__ inline double damp_quotient(double a, double b) {
-  if constexpr (sizeof(T) == 4) {
-    const double y = __builtin_amdgcn_rcp(b);
-    return a * (y * (2.0 - b * y));
-  } else {
-    return a / b;
-  }
-}
-
 // forward FFT along z, multiply by x0 / (E0 + hb2m |k|^2), inverse along z.
 // The line's x and y indices are frequency indices at this point.
 //   MODE 0: plain damping.
@@ -795,7 +783,7 @@ k_damp_z(cpx<T>* __restrict__ buf, GridArgs g, DampArgs d, const float* __restri
         for (int s = 0; s < PC_SHELLS; ++s) lpow[s] += (s == sh) ? pw : 0.0;
       } else {
         // the three inverse transforms' 1/N go into the filter
-        double mm = damp_quotient<T>(d.x0 / (double(N) * N * N), d.e0 + d.hb2m * kk);
+        double mm = d.x0 / (double(N) * N * N) / (d.e0 + d.hb2m * kk);
         if (MODE == 2) mm *= double(gain[size_t(blockIdx.y) * PC_SHELLS + k_shell(m2, N)]);
         const T m = T(mm);
 #pragma unroll
