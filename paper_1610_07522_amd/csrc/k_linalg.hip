@@ -748,6 +748,12 @@ int loewdin_series(const void* Iv, void* Cv, void* Dv, void* Tv, int m, double m
 // 151 + 50 trial states at 24^3, initialisation 4990 -> 800 us.
 constexpr int NEWTON_STEPS = 13;
 constexpr double NEWTON_DEFECT = 1e-8;   // of C I C before its last step: the square is below rounding
+// The iteration does not see the overlap's scale, but its caller refuses an
+// eigenvalue at or below 1e-10 and norms that overflow when squared.  A defect
+// below 0.7 within 13 steps means that every eigenvalue of I / s grew to 0.3
+// by at most 2.25 a step, so that it was above 7.9e-6: from s = NEWTON_NORM_MIN
+// on none is near 1e-10.  Other overlaps go by eigenvectors, which decide.
+constexpr double NEWTON_NORM_MIN = 1e-4, NEWTON_NORM_MAX = 1e150;
 
 // rs[i] = sum_j |I_ij|, one wave per row.
 __global__ void __launch_bounds__(256)
@@ -777,12 +783,14 @@ __device__ inline double max_of(const double* __restrict__ rs, int m, double* re
   return v;
 }
 
-// Y = X / s (ROOT: X / sqrt(s)), s = max rs.
+// Y = X / s (ROOT: X / sqrt(s)), s = max rs; host (if given, host-visible) gets s.
 template <bool ROOT>
 __global__ void __launch_bounds__(256)
-k_scale_by_norm(const double2* __restrict__ X, const double* __restrict__ rs, int m, double2* __restrict__ Y) {
+k_scale_by_norm(const double2* __restrict__ X, const double* __restrict__ rs, int m, double2* __restrict__ Y,
+                double* __restrict__ host) {
   __shared__ double red[4];
   const double s = max_of(rs, m, red), f = ROOT ? 1.0 / sqrt(s) : 1.0 / s;
+  if (host != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *host = s;
   const size_t n = size_t(m) * m;
   for (size_t e = size_t(blockIdx.x) * 256 + threadIdx.x; e < n; e += size_t(gridDim.x) * 256)
     Y[e] = make_double2(f * X[e].x, f * X[e].y);
@@ -828,7 +836,7 @@ bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs
     std::swap(Y, Yn);
   };
   hipLaunchKernelGGL(k_row_sums, dim3((m + 3) / 4), dim3(256), 0, st, I, m, rs);
-  hipLaunchKernelGGL(k_scale_by_norm<false>, dim3(nb), dim3(256), 0, st, I, (const double*)rs, m, Y);
+  hipLaunchKernelGGL(k_scale_by_norm<false>, dim3(nb), dim3(256), 0, st, I, (const double*)rs, m, Y, host + 1);
   hipLaunchKernelGGL(k_newton_half, dim3(nb), dim3(256), 0, st, (const double2*)Y, Z, m);   // Z_0 = 1
   gemm_square(Y, 0, Z, 0, Yn, m, st, 1);
   std::swap(Y, Yn);
@@ -837,7 +845,7 @@ bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs
     for (int k = 0; k < n; ++k) step();
     done += n;
     double f = norm(T, P);   // before the last step
-    if (!std::isfinite(f)) return false;
+    if (!std::isfinite(f) || !(host[1] >= NEWTON_NORM_MIN && host[1] <= NEWTON_NORM_MAX)) return false;
     if (f < 0.7) {
       // the defect goes from f to at most 3/4 f^2 + 1/4 f^3
       for (f = 0.75 * f * f + 0.25 * f * f * f; f > 1e-9; f = 0.75 * f * f + 0.25 * f * f * f) step();
@@ -845,7 +853,8 @@ bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs
     }
     if (done >= NEWTON_STEPS) return false;
   }
-  hipLaunchKernelGGL(k_scale_by_norm<true>, dim3(nb), dim3(256), 0, st, (const double2*)Z, (const double*)rs, m, Zn);
+  hipLaunchKernelGGL(k_scale_by_norm<true>, dim3(nb), dim3(256), 0, st, (const double2*)Z, (const double*)rs, m, Zn,
+                     (double*)nullptr);
   gemm_square(Zn, 0, I, 0, T, m, st);
   gemm_square(T, 0, Zn, 0, Y, m, st, 1, 1.5, nullptr, -0.5);
   gemm_square(Zn, 0, Y, 0, Cv, m, st, 1);

@@ -332,8 +332,8 @@ int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_d
 // C = I^-1/2 of a well-conditioned overlap by Newton's iteration on square
 // products.  work: six m x m matrices, rs: m doubles, scratch >= 257 doubles,
 // host as refine_eigh's; synchronises the stream.  False (C then undefined)
-// when it does not get there: small, zero or negative eigenvalues of I, or
-// values that are not finite.
+// when it does not get there: small, zero or negative eigenvalues of I, values
+// that are not finite, or a norm at which an eigenvalue could be near 1e-10.
 bool inverse_sqrt(const void* I, void* C, void* const* work, int m, double* rs, double* scratch,
                   hipStream_t st, double* host);
 // w[0 .. n) = v
