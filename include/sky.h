@@ -157,8 +157,7 @@ enum {
                           /* spin-orbit, Coulomb, total (MeV) (q ignored)        */
   SKY_VIEW_EPS = 8,       /* Rayleigh quotients <psi|h|psi> of species q [n_q]   */
   SKY_VIEW_RITZ = 9,      /* ascending subspace eigenvalues of species q [n_q]   */
-                          /* (after sky_init_box: of the trial states' overlap,  */
-                          /* not a number where it was not diagonalised)         */
+                          /* (after sky_init_box: of the trial states' overlap)  */
   SKY_VIEW_R2 = 10,       /* ||h psi - eps psi||^2 of species q [n_q]            */
   /* Subspace matrices of the last sky_orthonormalize / iteration, complex128
    * [n_q][n_q] row-major, valid for the species q of that call:          */
@@ -275,7 +274,11 @@ int sky_iterate(sky_ctx* c, int32_t max_iter, double tol_mev, sky_report* report
 
 /* Device pointer and element count (complex or f64 elements, see SKY_VIEW_*)
  * of one of the context's buffers.  The memory stays owned by the caller's
- * workspace. */
+ * workspace.  After sky_init_box the eigenpairs of the trial states' overlap
+ * (RITZ, EVEC) are formed by the first request for one of them, which then
+ * waits for the stream (during a capture of the stream they are left for the
+ * next request); once one has been requested, sky_init_box forms them itself.
+ * Errors: INVALID, HIP. */
 int sky_get_view(sky_ctx* c, int32_t what, int32_t q, void** ptr_dev, int64_t* count);
 
 /* Fig. 1 step 6 and its inverse: state I/O for checkpoint and resume.

@@ -804,15 +804,6 @@ k_newton_half(const double2* __restrict__ P, double2* __restrict__ T, int m) {
     T[e] = make_double2((e / m == e % m ? 1.5 : 0.0) - 0.5 * P[e].x, -0.5 * P[e].y);
 }
 
-__global__ void k_fill(double* __restrict__ w, double v, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) w[i] = v;
-}
-
-void fill(double* w, double v, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill, dim3((n + 255) / 256), dim3(256), 0, st, w, v, n);
-}
-
 bool inverse_sqrt(const void* Iv, void* Cv, void* const* work, int m, double* rs, double* scratch,
                   hipStream_t st, double* host) {
   auto I = (const double2*)Iv;

@@ -85,6 +85,7 @@ struct Layout {
   size_t tiles, gauge;
   size_t matI, matH, matC, matL, matT, matHp, matZ, matU, wtmp, gemm_part, chol_work, jac_work;
   size_t ref_work, nrm;
+  size_t trialI[2];   // overlaps whose eigenpairs are due (sky_ctx::ritz_due)
   // learned preconditioner: parameters (FP32 master, BF16-rounded copy),
   // gradient, Adam moments, sample rows, activations, shell powers, gains,
   // sampled-state batch buffers
@@ -154,6 +155,7 @@ Layout plan(const sky_box_desc& d) {
   L.matZ = take(mm);
   L.matU = take(mm);
   L.wtmp = take(sizeof(double) * nmax);
+  for (int q = 0; q < 2; ++q) L.trialI[q] = take(nq[q] > SMALL_M ? size_t(nq[q]) * nq[q] * c16 : 0);
   size_t gp = 0;
   for (int q = 0; q < 2; ++q) {
     gp = std::max(gp, overlap_scratch_bytes(std::max(1, nq[q]), long(V)));
@@ -266,6 +268,14 @@ struct sky_ctx {
   // of a norm is then a wait for the stream, without a copy kernel and a staged
   // transfer.  Allocated at the first solve, freed with the context.
   double* host = nullptr;
+  // Eigenpairs of the trial states' overlap after sky_init_box.  Where the
+  // orthonormalisation did not need them they are formed when their view is
+  // asked for; from then on (a caller may hold the buffers) sky_init_box forms
+  // them itself.  due: species whose eigenvalues are not in ritz[q] yet, and
+  // the one whose eigenvectors are not in matZ (-1: none).
+  bool eig_held = false;
+  bool ritz_due[2] = {};
+  int evec_due = -1;
   int last_sweeps;     // eigensolver iterations of the last iteration
   int fallbacks;       // refinement -> Jacobi fallbacks in the current call
   int unconverged;     // Jacobi solves of the current call stopped at the sweep limit
@@ -457,6 +467,13 @@ int need_host(sky_ctx* c) {
                    "status memory");
 }
 
+// Eigenvalues of set s (unless they go to the caller, ritz) and eigenvectors are
+// about to be written: those of the trial states' overlap are not due any more.
+void eig_written(sky_ctx* c, int s, const double* ritz) {
+  if (s < 2 && !ritz) c->ritz_due[s] = false;
+  c->evec_due = -1;
+}
+
 int jacobi_checked(sky_ctx* c, void* A, int m, double* w, void* Z) {
   const int its = jacobi_eigh(A, m, w, Z, c->at(c->lay.jac_work), JACOBI_TOL, JACOBI_SWEEPS, c->st, c->host);
   if (its == -2) return fail(SKY_ERR_NAN, "non-finite subspace matrix");
@@ -470,6 +487,7 @@ int jacobi_checked(sky_ctx* c, void* A, int m, double* w, void* Z) {
 int subspace_solve(sky_ctx* c, int s, double* ritz) {
   int rch = need_host(c);
   if (rch) return rch;
+  eig_written(c, s, ritz == c->at<double>(c->lay.ritz[s]) ? nullptr : ritz);
   if (c->d.update == SKY_UPDATE_PAPER) return paper_solve(c, s, ritz);
   const int q = s & 1;
   const int m = c->nq[q];
@@ -785,10 +803,10 @@ int loewdin_combine(sky_ctx* c, int q, const void* phi, void* psi_out) {
 }
 
 // Loewdin's orthonormalisation of set s.  eigen: by the eigenvectors of the
-// overlap, which the caller can then read; otherwise (above the orders that
-// one Jacobi workgroup solves) by Newton's iteration for I^-1/2, with the
-// eigenvectors where that does not converge; the set's eigenvalues are then
-// not a number.
+// overlap, which the caller can then read; otherwise (sets of the first twist,
+// above the orders that one Jacobi workgroup solves) by Newton's iteration for
+// I^-1/2, with the eigenvectors where that does not converge; the overlap's
+// eigenpairs are then due.
 int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
   const int q = s & 1;
   const int m = c->nq[q];
@@ -818,9 +836,12 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
                    c->at(c->lay.matC), c->at(c->lay.matT),  X};
   if (!eigen && m > SMALL_M &&
       inverse_sqrt(I, C, work, m, c->at<double>(c->lay.wtmp), c->at<double>(c->lay.nrm), st, c->host)) {
-    fill(w, NAN, m, st);
+    hipMemcpyAsync(c->at(c->lay.trialI[q]), I, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
+    c->ritz_due[q] = true;
+    c->evec_due = q;
     return loewdin_combine(c, q, phi, psi_out);
   }
+  eig_written(c, s, nullptr);
   int its = jacobi_checked(c, I, m, w, X);
   if (its < 0) return its;
   // C = X diag(w^-1/2) X^H
@@ -833,6 +854,30 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
   int rc = check_info(c, "loewdin");
   if (rc) return rc;
   return loewdin_combine(c, q, phi, psi_out);
+}
+
+// The eigenpairs of the trial states' overlap that are due, as sky_init_box would
+// have left them; waits for the stream.  Nothing during a capture of the stream,
+// where the solver cannot wait.
+int form_due_eigenpairs(sky_ctx* c) {
+  if (!c->ritz_due[0] && !c->ritz_due[1] && c->evec_due < 0) return SKY_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->st, &cap) != hipSuccess) {
+    (void)hipGetLastError();   // the default stream beside a capture: as a capture
+    return SKY_OK;
+  }
+  if (cap != hipStreamCaptureStatusNone) return SKY_OK;
+  for (int q = 0; q < 2; ++q) {
+    const bool vec = c->evec_due == q;
+    if (!c->ritz_due[q] && !vec) continue;
+    double* w = c->at<double>(c->ritz_due[q] ? c->lay.ritz[q] : c->lay.wtmp);
+    const int rc = jacobi_checked(c, c->at(c->lay.trialI[q]), c->nq[q], w,
+                                  c->at(vec ? c->lay.matZ : c->lay.matT));
+    if (rc < 0) return rc;
+    c->ritz_due[q] = false;
+    if (vec) c->evec_due = -1;
+  }
+  return hip_check(hipStreamSynchronize(c->st), "overlap eigenpairs");
 }
 
 // Fig. 1 steps 4a, 4b, 5: densities of the occupied states of every set,
@@ -1245,6 +1290,8 @@ int dev_start(DevRun& r) {
   set_double(c->at<double>(c->lay.gdbl), D_TOL, r.tol > 0.0 ? r.tol : 0.0, c->st);
   set_double(c->at<double>(c->lay.gdbl), D_DE, 0.0, c->st);
   if (r.max_iter == 0) r.finished = true;
+  else   // the replays write them
+    for (int s = 0; s < 2; ++s) eig_written(c, s, nullptr);
   return capture_full(c);
 }
 
@@ -1399,7 +1446,7 @@ int sky_init_box(sky_ctx* c, const void* raw_n, const void* raw_p) {
   for (int q = 0; q < 2; ++q) {
     if (c->nq[q] == 0) continue;
     if (!raw[q]) return fail(SKY_ERR_INVALID, "null trial states");
-    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]), false);
+    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]), c->eig_held);
     if (rc) return rc;
     const size_t ne = size_t(c->nq[q]) * c->V;
     for (int t = 1; t < c->ntw; ++t)   // every twist starts from the same states
@@ -1598,6 +1645,11 @@ int sky_get_view(sky_ctx* c, int32_t what, int32_t q, void** ptr, int64_t* count
   if (q < 0 || q >= c->nset) return fail(SKY_ERR_INVALID, "set index out of range");
   const int m = c->m_of(q);
   const int64_t st = int64_t(m) * c->V;
+  if (what == SKY_VIEW_RITZ || what == SKY_VIEW_EVEC) {
+    const int rc = form_due_eigenpairs(c);
+    if (rc) return rc;
+    c->eig_held = true;
+  }
   switch (what) {
     case SKY_VIEW_PSI: *ptr = c->psi(q); *count = st; break;
     case SKY_VIEW_HPSI: *ptr = c->hpsi(q); *count = st; break;

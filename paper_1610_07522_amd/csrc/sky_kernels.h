@@ -336,8 +336,6 @@ int loewdin_series(const void* I, void* C, void* D, void* T, int m, double max_d
 // that are not finite, or a norm at which an eigenvalue could be near 1e-10.
 bool inverse_sqrt(const void* I, void* C, void* const* work, int m, double* rs, double* scratch,
                   hipStream_t st, double* host);
-// w[0 .. n) = v
-void fill(double* w, double v, int n, hipStream_t st);
 // The series with the decision on the device: the term count from the norm
 // of D = I - 1 (as loewdin_series), Horner steps gated by flags[F_SERIES + k].
 // If the series does not apply (norm above max_dev or not finite), flags
