@@ -1212,20 +1212,14 @@ void damped_step(int n, int prec, const void* psi, const void* hpsi, const doubl
   if (r2) sum_partials(r2_part, nullptr, nt, nstate, r2, nullptr, st);
 }
 
-// Workgroups of a density pass that the card holds at once.
-template <typename T, int N> static int dens_capacity() {
-  static const int cap = [] {
-    int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_dens_pass<T, N, 1>,
-                                                     LineCfg<N>::THREADS, 0) != hipSuccess)
-      per_cu = 2;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 256;
-    return std::max(1, per_cu) * std::max(1, cus);
-  }();
-  return cap;
+// Workgroups of a density pass that a CU holds at once, by registers (the y
+// pass; where it matters, the chunk bound of the caller being larger).  A
+// constant, so that the order of the sums is that of the grid and form alone.
+template <typename T, int N> constexpr int dens_groups_per_cu() {
+  if (sizeof(T) == 8) return N >= 48 ? 1 : N >= 24 ? 2 : 3;
+  return N >= 48 ? 2 : N == 32 ? 3 : 4;
 }
+constexpr int CUS = 256;
 
 // Chunks of states: as many as fill the card once.  More only add partial
 // sums (16 doubles per point and chunk, written and read: as much as six
@@ -1233,10 +1227,13 @@ template <typename T, int N> static int dens_capacity() {
 // empty.  640 + 160 complex64 states at 32^3: 32 chunks per species and launches
 // of its own took 386 us for the passes and 62 for the sums, now 301 (4.2 TB/s
 // per pass) and 25; 1600 + 400 at 48^3 3.1 and 0.16 ms, now 2.6 and 0.02.
+// The chunks are those of all species, whether they are launched together or
+// (only >= 0) one species alone.
 template <typename T, int N>
-static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g, double* part,
-                        hipStream_t st) {
-  const int want = std::min(nchunk_max, std::max(nspecies, dens_capacity<T, N>() / ntiles<N>()));
+static void launch_dens(DensArgs& grp, int nspecies, int only, int nchunk_max, GridArgs g,
+                        double* part, hipStream_t st) {
+  const int want =
+      std::min(nchunk_max, std::max(nspecies, dens_groups_per_cu<T, N>() * CUS / ntiles<N>()));
   int total = 0;
   for (int q = 0; q < nspecies; ++q) total += grp.ngroup * grp.sp[q].nstate;
   // the smallest chunk whose count over both species does not exceed `want`
@@ -1250,7 +1247,12 @@ static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g,
   grp.chunk = chunk;
   for (int q = 0; q < nspecies; ++q)
     grp.sp[q].nchunk = (grp.ngroup * grp.sp[q].nstate + chunk - 1) / chunk;
-  const int nchunk = chunks(chunk);
+  int nchunk = chunks(chunk);
+  if (only >= 0) {
+    grp.sp[0] = grp.sp[only];
+    nchunk = grp.sp[0].nchunk;
+    nspecies = 1;
+  }
   if (nchunk > 0) {
     dim3 grid(ntiles<N>(), nchunk), block(LineCfg<N>::THREADS);
     hipLaunchKernelGGL((k_dens_pass<T, N, 0>), grid, block, 0, st, grp, g, part, g_launch_gate);
@@ -1264,8 +1266,9 @@ static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g,
 
 int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
               const int* nstate, double* const* dens, const GridArgs* g, int ngroup,
-              int nchunk_max, double* part, hipStream_t st) {
-  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nspecies < 1 || nspecies > 2 || nchunk_max < nspecies)
+              int nchunk_max, double* part, hipStream_t st, int only) {
+  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nspecies < 1 || nspecies > 2 ||
+      nchunk_max < nspecies || only >= nspecies)
     return 0;
   // one launch per pass over all species and groups (twists): each species'
   // flat (group, state) index is cut into chunks of consecutive states
@@ -1278,8 +1281,8 @@ int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_G
     grp.sp[q].nstate = std::max(0, nstate[q]);
     grp.sp[q].dens = dens[q];
   }
-  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nspecies, nchunk_max, g[0], part, st))
-  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nspecies, nchunk_max, g[0], part, st))
+  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nspecies, only, nchunk_max, g[0], part, st))
+  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nspecies, only, nchunk_max, g[0], part, st))
   return 1;
 }
 

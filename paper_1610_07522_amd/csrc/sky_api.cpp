@@ -891,12 +891,12 @@ void fields(sky_ctx* c) {
     gs[t] = c->gset(2 * t);   // the twist; the same for both species
     for (int q = 0; q < 2; ++q) ps[q][t] = c->psi(2 * t + q);
   }
-  // both species in one launch per pass; one after the other only to be timed
-  const int per = c->timing ? 1 : 2;
-  for (int q = 0; q < 2; q += per) {
+  // both species in one launch per pass; one after the other (with the same
+  // chunks and sums) only to be timed
+  for (int q = 0; q < (c->timing ? 2 : 1); ++q) {
     const int td = t_begin(c, SKY_PHASE_DENSITIES, q);
-    (void)sky::densities(c->n, c->prec, per, ps + q, c->nocc + q, dens + q, gs, c->ntw, DENS_CHUNKS,
-                         c->at<double>(c->lay.dens_part), st);
+    (void)sky::densities(c->n, c->prec, 2, ps, c->nocc, dens, gs, c->ntw, DENS_CHUNKS,
+                         c->at<double>(c->lay.dens_part), st, c->timing ? q : -1);
     t_end(c, td);
   }
   const int tmf = t_begin(c, SKY_PHASE_MEANFIELD, 0);
