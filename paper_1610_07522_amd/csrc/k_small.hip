@@ -267,16 +267,16 @@ k_subspace_small(SmallArgs p, const int* __restrict__ sky_gate) {
   auto store = [&](double2* d, const double2* src) {
     for (int e = tid; e < m * m; e += NT) d[e] = src[(e / m) * LD + e % m];
   };
-  // the outcome: series terms (-1 not finite, 0 too far from orthonormality)
-  // and refinement steps (-1: none that converged)
-  auto finish = [&](int terms, int its) {
+  // the outcome: series terms (-1 not finite, 0 too far from orthonormality),
+  // refinement steps (-1: none that converged) and the steps taken
+  auto finish = [&](int terms, int its, int taken) {
     if (p.host != nullptr && tid == 0) {
       p.host[0] = double(terms);
       p.host[1] = double(its);
     }
     if (p.flags != nullptr && tid == 0) {
       p.flags[F_REF_RUN] = 0;
-      p.flags[F_REF_STEPS] = its < 0 ? p.maxit : its;
+      p.flags[F_REF_STEPS] = taken;
       if (terms <= 0 || its < 0) {
         p.flags[F_HOST] = terms <= 0 ? HOST_LOEWDIN : HOST_REFINE;
         p.flags[F_HOST_SET] = p.set;
@@ -298,7 +298,7 @@ k_subspace_small(SmallArgs p, const int* __restrict__ sky_gate) {
     reduce<1, false>(f2, red);
     const double f = sqrt(f2[0]);
     if (!isfinite(f) || !(f <= p.max_dev)) {
-      finish(isfinite(f) ? 0 : -1, -1);
+      finish(isfinite(f) ? 0 : -1, -1, 0);
       return;
     }
     double c[15];
@@ -348,8 +348,8 @@ k_subspace_small(SmallArgs p, const int* __restrict__ sky_gate) {
   reduce<1, false>(dia, red);
   double tau = p.tg.noise * sqrt(dia[0] / m);
   if (tid < SM) order[tid] = tid;
-  int its = -1;
-  for (int it = 0;; ++it) {
+  int its = -1, it = 0;
+  for (;; ++it) {
     const double2 *Sp = A, *Rp = nullptr;
     if (it > 0) {
       product<MP, true, true>(R, X, X);
@@ -517,7 +517,7 @@ k_subspace_small(SmallArgs p, const int* __restrict__ sky_gate) {
     }
   }
   if (its < 0) {
-    finish(terms, -1);
+    finish(terms, -1, it);
     return;
   }
   // ---- eigenpairs in ascending order (Z in T), U = C Z
@@ -544,7 +544,7 @@ k_subspace_small(SmallArgs p, const int* __restrict__ sky_gate) {
     product<MP, false, false>(Q, A, T);
     store(p.U, Q);
   }
-  finish(terms, its);
+  finish(terms, its, its);
 }
 
 }  // namespace
