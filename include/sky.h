@@ -325,8 +325,8 @@ typedef struct {
                              /* z-slices (where they fit), 0 = line passes,     */
                              /* -1 = the default (slices where they fit)        */
   int32_t overlap_split[2];  /* split-K factor of the I/H product per species    */
-  int32_t square_split[2];   /* not used any more: the subspace products split  */
-                             /* inside a workgroup; 1, or what a saved file held*/
+  int32_t square_split[2];   /* subspace products: 1 once tuned (no launch shape */
+                             /* left: they split inside a workgroup)            */
   int32_t from_cache;        /* 1: every shape came from the cache file          */
   int32_t overlap_waves[2];  /* mixed: waves per 128 x 128 tile of the overlap   */
                              /* product, 8 (32 x 64 each) or 4 (64 x 64 each)  */

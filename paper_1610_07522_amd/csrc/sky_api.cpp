@@ -1762,11 +1762,9 @@ int sky_autotune(sky_ctx* c, const char* cache_path, sky_tuning* out) {
   const char* pr = c->prec ? "mixed" : "fp64";
   const std::string klines = "h_lines/n" + std::to_string(c->n) + "/" + pr;
   const std::string kdamp = "damp_xy/n" + std::to_string(c->n) + "/" + pr;
-  std::string kovl[2], ksq[2];
-  for (int q = 0; q < 2; ++q) {
+  std::string kovl[2];
+  for (int q = 0; q < 2; ++q)
     kovl[q] = "overlap_split/m" + std::to_string(c->nq[q]) + "/k" + std::to_string(c->V) + "/" + pr;
-    ksq[q] = "square_split/m" + std::to_string(c->nq[q]);
-  }
   int timed = 0;
   if (c->prec) {   // FP64 shapes for a later ladder switch: cached entries only, not timed
     const std::string sn = "/n" + std::to_string(c->n) + "/fp64";
@@ -1891,12 +1889,7 @@ int sky_autotune(sky_ctx* c, const char* cache_path, sky_tuning* out) {
       }
       c->tune.cbw[q] = cw;
     }
-    // the square products split their contraction inside a workgroup; saved
-    // files keep the factor they held, a new entry is 1
-    v = cache_get(kv, ksq[q]);
-    if (v != 1 && v != 2 && v != 4 && v != 8) v = 1;
-    cache_put(kv, ksq[q], v);
-    c->tune.sq[q] = v;
+    c->tune.sq[q] = 1;   // nothing to tune: split inside a workgroup, whatever a file holds
   }
   rc = hip_check(hipStreamSynchronize(st), "autotune runs");
   if (rc) return rc;
