@@ -18,10 +18,8 @@
 namespace sky {
 
 namespace {
-using mfma::Acc;
 using mfma::GT;
 using mfma::KC;
-using mfma::KP;
 using mfma::TM;
 
 constexpr int NXCD = 8;   // workgroups are dealt to the XCDs in turn, each has its own L2

@@ -294,7 +294,15 @@ template <typename T, int N> constexpr int plane_buf() {
 template <typename T, int N> constexpr bool plane_fits() {
   return PlaneCfg<N>::THREADS <= 1024 && (plane_buf<T, N>() + N) * int(sizeof(cpx<T>)) <= 80 * 1024;
 }
-// Waves per SIMD the h slice kernel is compiled for.
+// Waves per SIMD the h slice kernel is compiled for: the compiler's own choice
+// (1: no demand), but at 48^3 complex64 five, three workgroups per CU, where
+// its choice is four and two.  The registers are 96 then and six spill
+// (400 states, with the z pass: 1114 to 1120 us; with four 1124 to 1131).
+// Elsewhere one more does not fit the LDS (64^3: 78 KB a workgroup; 8^3 and
+// 16^3 complex64) or spills more than it hides: complex64 24^3 x 200 85 us
+// with eight, 74 with its own six; 32^3 x 200 208 with eight and 138 with
+// six, 138 with its own five; complex128 24^3 x 100 122 with five and 79 with
+// four, 74 with its own three; 32^3 x 160 320 with four, 227 with its own three.
 template <typename T, int N> constexpr int plane_waves() {
   return sizeof(T) == 4 && N == 48 ? 5 : 1;
 }

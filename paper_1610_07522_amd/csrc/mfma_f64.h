@@ -37,6 +37,9 @@ __device__ inline void zero(Acc& a) {
     }
 }
 
+// No kernel stores through this any more (the FP64 overlap's operands come from
+// L2 in the layout of the matrix instruction); kept as the conflict-free
+// layout for tiles staged in LDS.
 // Position in an LDS row of contraction index kk < 16 for loaders that store
 // 4 consecutive indices per thread: kk = 4 q + e goes to 2 q + (e >> 1) +
 // 8 (e & 1), so that one store (fixed e) of two rows x four threads covers

@@ -278,8 +278,8 @@ int refine_eigh(const void* A, int m, double* w, void* Z, void* work, const Refi
 // sorts the eigenpairs out when converged (flags[F_REF_OK + it]); a step
 // that would make the host version give up (maxit reached, a cluster over
 // the limit, a non-finite check) sets F_HOST = HOST_REFINE (set `set`) and
-// clears F_ACTIVE.  The E^2 term of the update is always formed.  maxit <=
-// F_NFLAGS - F_REF_OK - 1.
+// clears F_ACTIVE.  The E^2 term of the update is formed where the host-driven
+// refinement forms it.  maxit <= F_NFLAGS - F_REF_OK - 1.
 void refine_eigh_dev(const void* A, int m, double* w, void* Z, void* work, const RefineTargets& tg,
                      int maxit, hipStream_t st, int* flags, int set);
 
