@@ -93,8 +93,11 @@ template <typename T> __device__ inline float cabs_max(cpx<T> z) {
 // A pointer the compiler takes as new: loads through it are not merged with
 // earlier ones (whose values would stay in registers across the transforms).
 // The complex64 kernels read psi anew (from the L2) where the local terms need
-// it: 24 registers fewer at 48^3, a wave more per SIMD.  In complex128 the line
-// passes are no faster with it (48^3, 100 states: 592 us with, 570 without).
+// it: 24 registers fewer at 48^3, a wave more per SIMD.  The complex128 line
+// passes, two waves per SIMD either way, hold it in registers of their own; a
+// second load in the source is one in the kernel too, the barriers between
+// keep the two apart (48^3, 400 states: 2420 us with it, 2220 without; 64^3,
+// 150 states: 2360 and 1950).
 template <typename P> __device__ inline P* reread(P* p) {
   asm volatile("" : "+s"(p));
   return p;
@@ -131,13 +134,18 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   cpx<T>* Y = Ybuf + line * YS;
   const T kun = T(g.kunit * (1.0 / N)), ksn = T(g.tw[DIR] * (1.0 / N));
 
-  cpx<T> d[2][R1];
+  constexpr bool HOLD = sizeof(T) == 8;   // psi in registers through the pass (see reread)
+  cpx<T> d[2][R1], v[2][HOLD ? R1 : 1];
   if (j < R2) {
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
       d[0][j1] = p[r];
       d[1][j1] = p[N3 + r];
+      if constexpr (HOLD) {
+        v[0][j1] = d[0][j1];
+        v[1][j1] = d[1][j1];
+      }
     }
   }
   load_twiddles<T, N>(tw);
@@ -146,11 +154,18 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
   // g (into d) and the accumulated local terms (into acc)
   cpx<T> acc[2][R1];
   if (j < R2) {
-    const cpx<T>* q = sizeof(T) == 4 ? reread(p) : p;
+    const cpx<T>* q = reread(p);
 #pragma unroll
     for (int j1 = 0; j1 < R1; ++j1) {
       int r = base + (j + R2 * j1) * stride;
-      const cpx<T> vu = q[r], vd = q[N3 + r];
+      cpx<T> vu, vd;
+      if constexpr (HOLD) {
+        vu = v[0][j1];
+        vd = v[1][j1];
+      } else {
+        vu = q[r];
+        vd = q[N3 + r];
+      }
       h_local<T, N, DIR>(mf, r, vu, vd, d[0][j1], d[1][j1], acc[0][j1], acc[1][j1]);
       if (FIRST) {
         const T U = fld_U<T>(mf, r);
@@ -179,14 +194,17 @@ k_h_pass(const cpx<T>* __restrict__ psi, cpx<T>* __restrict__ hpsi, MeanFieldPtr
       }
     }
     if (LAST && (eps_part != nullptr || nrm_part != nullptr)) {
-      const cpx<T>* q = sizeof(T) == 4 ? reread(p) : p;
+      const cpx<T>* q = reread(p);
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          const cpx<T> v = q[s * N3 + base + (j + R2 * j1) * stride], t = acc[s][j1];
-          dot += double(v.re) * double(t.re) + double(v.im) * double(t.im);
-          nrm += double(v.re) * double(v.re) + double(v.im) * double(v.im);
+          const cpx<T> t = acc[s][j1];
+          cpx<T> w;
+          if constexpr (HOLD) w = v[s][j1];
+          else w = q[s * N3 + base + (j + R2 * j1) * stride];
+          dot += double(w.re) * double(t.re) + double(w.im) * double(t.im);
+          nrm += double(w.re) * double(w.re) + double(w.im) * double(w.im);
         }
       }
     }
