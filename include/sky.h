@@ -309,7 +309,9 @@ int sky_set_timing(sky_ctx* c, int32_t enable);
 /* Accumulated device time (ms) and number of timed launches per phase and
  * species since sky_set_timing: ms[2*phase + q], launches[2*phase + q]
  * (host arrays of 2*SKY_NPHASE; launches may be NULL; phases that are not
- * per species use q = 0).  Waits for the stream. */
+ * per species use q = 0).  The densities of both species run in the same
+ * launches, whose time is shared out by the numbers of occupied states.
+ * Waits for the stream. */
 int sky_get_timing(sky_ctx* c, double* ms, int64_t* launches);
 
 /* Current precision of the context's states (SKY_FP64 or SKY_MIXED). */

@@ -1253,11 +1253,9 @@ constexpr int CUS = 256;
 // empty.  640 + 160 complex64 states at 32^3: 32 chunks per species and launches
 // of its own took 386 us for the passes and 62 for the sums, now 301 (4.2 TB/s
 // per pass) and 25; 1600 + 400 at 48^3 3.1 and 0.16 ms, now 2.6 and 0.02.
-// The chunks are those of all species, whether they are launched together or
-// (only >= 0) one species alone.
 template <typename T, int N>
-static void launch_dens(DensArgs& grp, int nspecies, int only, int nchunk_max, GridArgs g,
-                        double* part, hipStream_t st) {
+static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g, double* part,
+                        hipStream_t st) {
   const int want =
       std::min(nchunk_max, std::max(nspecies, dens_groups_per_cu<T, N>() * CUS / ntiles<N>()));
   int total = 0;
@@ -1273,12 +1271,7 @@ static void launch_dens(DensArgs& grp, int nspecies, int only, int nchunk_max, G
   grp.chunk = chunk;
   for (int q = 0; q < nspecies; ++q)
     grp.sp[q].nchunk = (grp.ngroup * grp.sp[q].nstate + chunk - 1) / chunk;
-  int nchunk = chunks(chunk);
-  if (only >= 0) {
-    grp.sp[0] = grp.sp[only];
-    nchunk = grp.sp[0].nchunk;
-    nspecies = 1;
-  }
+  const int nchunk = chunks(chunk);
   if (nchunk > 0) {
     dim3 grid(ntiles<N>(), nchunk), block(LineCfg<N>::THREADS);
     hipLaunchKernelGGL((k_dens_pass<T, N, 0>), grid, block, 0, st, grp, g, part, g_launch_gate);
@@ -1292,9 +1285,8 @@ static void launch_dens(DensArgs& grp, int nspecies, int only, int nchunk_max, G
 
 int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
               const int* nstate, double* const* dens, const GridArgs* g, int ngroup,
-              int nchunk_max, double* part, hipStream_t st, int only) {
-  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nspecies < 1 || nspecies > 2 ||
-      nchunk_max < nspecies || only >= nspecies)
+              int nchunk_max, double* part, hipStream_t st) {
+  if (ngroup < 0 || ngroup > DENS_MAX_GROUPS || nspecies < 1 || nspecies > 2 || nchunk_max < nspecies)
     return 0;
   // one launch per pass over all species and groups (twists): each species'
   // flat (group, state) index is cut into chunks of consecutive states
@@ -1307,8 +1299,8 @@ int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_G
     grp.sp[q].nstate = std::max(0, nstate[q]);
     grp.sp[q].dens = dens[q];
   }
-  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nspecies, only, nchunk_max, g[0], part, st))
-  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nspecies, only, nchunk_max, g[0], part, st))
+  if (prec == 0) SKY_DISPATCH_N(n, launch_dens<double, NN>(grp, nspecies, nchunk_max, g[0], part, st))
+  else SKY_DISPATCH_N(n, launch_dens<float, NN>(grp, nspecies, nchunk_max, g[0], part, st))
   return 1;
 }
 

@@ -377,6 +377,10 @@ hipEvent_t take_event(sky_ctx* c) {
 }
 
 // Start a timed phase; returns the mark index or -1 when timing is off.
+// q of a phase whose launches serve both species: its time is shared out by
+// their occupied states.
+constexpr int BOTH_SPECIES = 2;
+
 int t_begin(sky_ctx* c, int phase, int q) {
   if (!c->timing) return -1;
   sky_ctx::Mark m{phase, q, take_event(c), take_event(c)};
@@ -394,8 +398,12 @@ void t_flush(sky_ctx* c) {
   for (auto& m : c->marks) {
     float t = 0.f;
     if (hipEventElapsedTime(&t, m.a, m.b) == hipSuccess) {
-      c->ms[m.phase][m.q] += t;
-      c->cnt[m.phase][m.q] += 1;
+      const double all = c->nocc[0] + c->nocc[1];
+      for (int q = 0; q < 2; ++q) {
+        if (m.q != q && m.q != BOTH_SPECIES) continue;
+        c->ms[m.phase][q] += m.q == q ? t : all > 0.0 ? t * (c->nocc[q] / all) : 0.5 * t;
+        c->cnt[m.phase][q] += 1;
+      }
     }
     c->pool.push_back(m.a);
     c->pool.push_back(m.b);
@@ -891,14 +899,10 @@ void fields(sky_ctx* c) {
     gs[t] = c->gset(2 * t);   // the twist; the same for both species
     for (int q = 0; q < 2; ++q) ps[q][t] = c->psi(2 * t + q);
   }
-  // both species in one launch per pass; one after the other (with the same
-  // chunks and sums) only to be timed
-  for (int q = 0; q < (c->timing ? 2 : 1); ++q) {
-    const int td = t_begin(c, SKY_PHASE_DENSITIES, q);
-    (void)sky::densities(c->n, c->prec, 2, ps, c->nocc, dens, gs, c->ntw, DENS_CHUNKS,
-                         c->at<double>(c->lay.dens_part), st, c->timing ? q : -1);
-    t_end(c, td);
-  }
+  const int td = t_begin(c, SKY_PHASE_DENSITIES, BOTH_SPECIES);   // one launch per pass
+  (void)sky::densities(c->n, c->prec, 2, ps, c->nocc, dens, gs, c->ntw, DENS_CHUNKS,
+                       c->at<double>(c->lay.dens_part), st);
+  t_end(c, td);
   const int tmf = t_begin(c, SKY_PHASE_MEANFIELD, 0);
   mean_field(c->n, c->g, c->sk, c->taps, dens[0], dens[1], c->at<double>(c->lay.der[0]),
              c->at<double>(c->lay.der[1]), c->at<double>(c->lay.mf[0]),

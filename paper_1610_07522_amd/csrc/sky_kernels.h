@@ -121,10 +121,8 @@ void precond_targets(int prec, const void* bpsi, const void* bh, const void* bd,
 // of nspecies species, summed over the first nstate[q] states of each of ngroup
 // state arrays psi[q][t] (each with its own grid arguments g[t], i.e. its
 // twist; spacing from g[0]) and divided by ngroup (the twist average); part
-// holds nchunk_max * 16 * n^3 doubles.  only >= 0: that species alone, to the
-// same bits.  Returns 0 (nothing launched) for ngroup outside
-// [0, DENS_MAX_GROUPS], nspecies outside 1..2, nchunk_max < nspecies or
-// only >= nspecies.
+// holds nchunk_max * 16 * n^3 doubles.  Returns 0 (nothing launched) for ngroup
+// outside [0, DENS_MAX_GROUPS], nspecies outside 1..2 or nchunk_max < nspecies.
 constexpr int DENS_MAX_GROUPS = 32;
 struct DensSpecies {
   const void* psi[DENS_MAX_GROUPS];
@@ -139,7 +137,7 @@ struct DensArgs {
 };
 int densities(int n, int prec, int nspecies, const void* const (*psi)[DENS_MAX_GROUPS],
               const int* nstate, double* const* dens, const GridArgs* g, int ngroup,
-              int nchunk_max, double* part, hipStream_t st, int only = -1);
+              int nchunk_max, double* part, hipStream_t st);
 // n complex values between precisions (0 = complex128, 1 = complex64).
 void convert_states(const void* src, int src_prec, void* dst, int dst_prec, size_t n,
                     hipStream_t st);
