@@ -3,6 +3,7 @@
 // (fft_line.h); one workgroup takes LPW lines of one state (h, damping) or of
 // a chunk of states (densities).
 #include <algorithm>
+#include <cmath>
 
 #include "fft_line.h"
 #include "sky_kernels.h"
@@ -1247,27 +1248,44 @@ template <typename T, int N> constexpr int dens_groups_per_cu() {
 }
 constexpr int CUS = 256;
 
-// Chunks of states: as many as fill the card once.  More only add partial
-// sums (16 doubles per point and chunk, written and read: as much as six
-// complex64 states' reads) and a last round of workgroups that is mostly
-// empty.  640 + 160 complex64 states at 32^3: 32 chunks per species and launches
-// of its own took 386 us for the passes and 62 for the sums, now 301 (4.2 TB/s
-// per pass) and 25; 1600 + 400 at 48^3 3.1 and 0.16 ms, now 2.6 and 0.02.
+// Chunks of states: each is a row of workgroups over the grid's lines, the card
+// holds `rows` of them at once, and a pass takes about ceil(chunks / rows) times
+// a chunk's states.  More chunks cost partial sums (16 doubles per point and
+// chunk, written and read: as much as the three passes' reads of 16/3
+// complex64 or 8/3 complex128 states).  The count, up to the caller's bound,
+// is the one whose estimate is least: where many rows fit, as many as fill the
+// card once, where few do (48^3 and 64^3), several rounds of shorter ones,
+// since one round cannot be cut to fit two species.
+// 640 + 160 complex64 states at 32^3: 32 chunks per species and launches of its
+// own took 386 us for the passes and 62 for the sums, now 301 and 25.
+// Densities and mean field by 32 chunks per species, by one round and by this
+// rule (ms): complex128 48^3 x 1600 + 400 6.27, 6.72 and 5.03, x 1000 + 1000 6.32,
+// 8.26 and 4.99; 64^3 x 300 + 75 3.45, 3.21 and 2.28; complex64 48^3 x 1600 + 400
+// 3.14, 2.65 and 2.60, x 1000 + 1000 3.14, 2.73 and 2.58.
 template <typename T, int N>
 static void launch_dens(DensArgs& grp, int nspecies, int nchunk_max, GridArgs g, double* part,
                         hipStream_t st) {
-  const int want =
-      std::min(nchunk_max, std::max(nspecies, dens_groups_per_cu<T, N>() * CUS / ntiles<N>()));
   int total = 0;
   for (int q = 0; q < nspecies; ++q) total += grp.ngroup * grp.sp[q].nstate;
-  // the smallest chunk whose count over both species does not exceed `want`
   auto chunks = [&](int c) {
     int k = 0;
     for (int q = 0; q < nspecies; ++q) k += (grp.ngroup * grp.sp[q].nstate + c - 1) / c;
     return k;
   };
-  int chunk = std::max(1, (total + want - 1) / want);
-  while (chunks(chunk) > want) ++chunk;
+  const double rows = double(dens_groups_per_cu<T, N>() * CUS) / ntiles<N>();
+  const double sums = sizeof(T) == 8 ? 8.0 / 3.0 : 16.0 / 3.0;
+  int chunk = 1;
+  double best = HUGE_VAL;
+  for (int want = nchunk_max; want >= nspecies; --want) {
+    // the smallest chunk whose count over all species does not exceed `want`
+    int c = std::max(1, (total + want - 1) / want);
+    while (chunks(c) > want) ++c;
+    const double cost = std::ceil(chunks(c) / rows) * c + sums * chunks(c) / rows;
+    if (cost <= best) {
+      best = cost;
+      chunk = c;
+    }
+  }
   grp.chunk = chunk;
   for (int q = 0; q < nspecies; ++q)
     grp.sp[q].nchunk = (grp.ngroup * grp.sp[q].nstate + chunk - 1) / chunk;
