@@ -1450,7 +1450,7 @@ int sky_init_box(sky_ctx* c, const void* raw_n, const void* raw_p) {
   for (int q = 0; q < 2; ++q) {
     if (c->nq[q] == 0) continue;
     if (!raw[q]) return fail(SKY_ERR_INVALID, "null trial states");
-    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]), c->eig_held);
+    int rc = loewdin(c, q, raw[q], c->at(c->lay.psi[q]), false);
     if (rc) return rc;
     const size_t ne = size_t(c->nq[q]) * c->V;
     for (int t = 1; t < c->ntw; ++t)   // every twist starts from the same states
@@ -1463,6 +1463,10 @@ int sky_init_box(sky_ctx* c, const void* raw_n, const void* raw_p) {
   }
   c->prec = prec;
   c->hpsi_lagged = false;
+  if (c->eig_held) {
+    int rc = form_due_eigenpairs(c);
+    if (rc) return rc;
+  }
   fields(c);
   return hip_check(hipStreamSynchronize(c->st), "init");
 }

@@ -96,6 +96,20 @@ def test_overlap_eigenpairs_after_initialisation(mn, mp, held):
     assert np.abs(I @ v - v * to_host(w[1])).max() <= tol
 
 
+def test_views_leave_the_states_alone():
+    """The initial states do not depend on whether a caller has asked for eigenvalues."""
+    raw = _pair(40, 35)
+    out = []
+    for held in (False, True):
+        box = _pair_box(40, 35)
+        if held:
+            box.view("evec", 0)
+        box.init_box(*map(to_dev, raw))
+        out.append([to_host(box.view("psi", q)) for q in range(2)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
 def test_overlap_eigenvalues_give_way_to_the_next_solve():
     torch = pytest.importorskip("torch")
     mn, mp = 40, 35
