@@ -148,6 +148,29 @@ def test_overlap_eigenvalues_give_way_to_the_next_solve():
         assert np.abs(to_host(box.view("ritz", q)) - ref).max() <= tol[q], q
 
 
+def test_eigenvalues_asked_for_during_a_capture():
+    """They are left for the next request; the capture is not disturbed."""
+    torch = pytest.importorskip("torch")
+    raw = _pair(40, 35)
+    dev = [to_dev(r) for r in raw]
+    x = torch.zeros(64, device="cuda:0")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    box = _pair_box(40, 35, stream)
+    box.init_box(*dev)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        x.add_(1.0)
+        box.view("ritz", 0)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (x == k + 1.0).all()
+    for q in range(2):
+        lam = np.linalg.eigvalsh(_overlap(raw[q]))
+        assert np.abs(to_host(box.view("ritz", q)) - lam).max() <= 2e-12 * np.linalg.norm(lam), q
+
+
 # thirteen steps of at most 2.25 each: Newton's iteration takes 1e3 and cannot take 1e5;
 # up to 32 states it is not tried
 @pytest.mark.parametrize("cond,newton", [(1.0, True), (1e3, True), (1e5, False), (1e8, False)])
