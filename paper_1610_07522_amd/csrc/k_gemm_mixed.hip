@@ -570,6 +570,15 @@ k_overlap_planes(const unsigned short* __restrict__ PA, const unsigned short* __
 // do not average out (the dropped l l' products are all of one sign, and a
 // nearly constant state repeats one rounding at every point); to first order
 // the subspace eigenvalues are these diagonals' ratios.
+//
+// C0 is a Gram matrix whose definiteness decides whether the states are
+// independent, and the planes' product is one (up to the dropped l l': equal
+// states give equal elements).  New diagonals alone would not be: a state taken
+// twice would leave a pivot of the split's error, 1e-7.  So C0 is D P D with the
+// planes' product P and D = (diag0 / P_aa)^1/2, which has the diagonal diag0 and
+// P's inertia (1600 and 400 states at 48^3: the strided reads of P_aa take the
+// kernel from 156 to 171 and from 22 to 28 us).  A state too faint for the planes
+// beside the largest amplitude (P_aa = 0) keeps its zero.
 constexpr int RB = BT / 16;   // 16 x 16 blocks per tile side
 __global__ void __launch_bounds__(256)
 k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, int m, double scale,
@@ -579,8 +588,10 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
                         double2* __restrict__ C1, const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   __shared__ double2 T[16][17];
+  __shared__ double D[2][16];   // D of the block's rows and columns
   const int pair = blockIdx.x / (RB * RB), sub = blockIdx.x % (RB * RB), z = blockIdx.y;
   double2* C = z ? C1 : C0;
+  const double* dg = z ? diag1 : diag0;
   int ta, tb;
   tri_pair(pair, ta, tb);
   const int br = (sub / RB) * 16, bc = (sub % RB) * 16;
@@ -590,6 +601,17 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
   const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
   const int row = row0 + r, col = col0 + c;
   const float2* p = part + (size_t(z) * npair + pair) * split * BT * BT + (br + r) * BT + bc + c;
+  // P_aa of the block's rows and columns: eight threads each, their loads in
+  // flight with the element's own
+  const bool gram = z == 0 && dg != nullptr;
+  const int side = threadIdx.x >> 7, e = (threadIdx.x >> 3) & 15;
+  const int t = side ? tb : ta, i = (side ? bc : br) + e, a = t * BT + i;
+  double paa = 0.0;
+  if (gram && a < m) {
+    const float2* q = part + size_t(t * (t + 1) / 2 + t) * split * BT * BT + i * (BT + 1);
+#pragma unroll 4
+    for (int s = threadIdx.x & 7; s < split; s += 8) paa += double(q[size_t(s) * BT * BT].x);
+  }
   double re = 0.0, im = 0.0;
   if (row < m && col <= row) {
     int s = 0;
@@ -608,10 +630,21 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
       re += double(v.x);
       im += double(v.y);
     }
+  }
+  if (gram) {
+    for (int w = 4; w > 0; w >>= 1) paa += __shfl_xor(paa, w);
+    paa *= sc;
+    if ((threadIdx.x & 7) == 0)
+      D[side][e] = a < m && paa > 0.0 && dg[a] > 0.0 ? sqrt(dg[a] / paa) : 1.0;
+    __syncthreads();
+  }
+  if (row < m && col <= row) {
     double2 v = make_double2(sc * re, sc * im);
     if (col == row) {
-      const double* dg = z ? diag1 : diag0;
-      v = make_double2(dg != nullptr ? dg[row] : v.x, 0.0);
+      v = make_double2(dg != nullptr && !(gram && v.x == 0.0) ? dg[row] : v.x, 0.0);
+    } else if (gram) {
+      const double d = D[0][r] * D[1][c];
+      v = make_double2(d * v.x, d * v.y);
     }
     C[size_t(row) * m + col] = v;
     T[r][c] = v;

@@ -217,7 +217,8 @@ void split_planes_both(const void* x, int rows, long k, const unsigned int* mx, 
 // triangle, mirrored to the upper one.
 // split_req > 0 overrides the split-K factor (one of overlap_split_candidates_mixed).
 // diag0, diag1 (optional): the diagonals of C0 and C1, formed from the complex64
-// operands in FP64, in place of the planes' ones.
+// operands in FP64, in place of the planes' ones; with diag0 (A and B0 the same
+// matrix) C0's rows and columns are scaled to it, so that it stays a Gram matrix.
 int overlap_split_candidates_mixed(int m, long k, int* out);
 void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
                           const unsigned int* mxA, const unsigned int* mxB0,
