@@ -569,29 +569,22 @@ k_overlap_planes(const unsigned short* __restrict__ PA, const unsigned short* __
 // states themselves.  A state's overlap with itself is where the split's errors
 // do not average out (the dropped l l' products are all of one sign, and a
 // nearly constant state repeats one rounding at every point); to first order
-// the subspace eigenvalues are these diagonals' ratios.
-//
-// C0 is a Gram matrix whose definiteness decides whether the states are
-// independent, and the planes' product is one (up to the dropped l l': equal
-// states give equal elements).  New diagonals alone would not be: a state taken
-// twice would leave a pivot of the split's error, 1e-7.  So C0 is D P D with the
-// planes' product P and D = (diag0 / P_aa)^1/2, which has the diagonal diag0 and
-// P's inertia (1600 and 400 states at 48^3: the strided reads of P_aa take the
-// kernel from 156 to 171 and from 22 to 28 us).  A state too faint for the planes
-// beside the largest amplitude (P_aa = 0) keeps its zero.
+// the subspace eigenvalues are these diagonals' ratios.  gap0 gets by how much
+// diag0 exceeds the planes' own diagonal: the planes' C0 is what tells dependent
+// states (equal states give it equal elements; with the other diagonal they leave
+// a pivot of the split's error, 1e-7).
 constexpr int RB = BT / 16;   // 16 x 16 blocks per tile side
 __global__ void __launch_bounds__(256)
 k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, int m, double scale,
                         const unsigned int* __restrict__ mxA, const unsigned int* __restrict__ mxB0,
                         const unsigned int* __restrict__ mxB1, const double* __restrict__ diag0,
-                        const double* __restrict__ diag1, double2* __restrict__ C0,
-                        double2* __restrict__ C1, const int* __restrict__ sky_gate) {
+                        const double* __restrict__ diag1, double* __restrict__ gap0,
+                        double2* __restrict__ C0, double2* __restrict__ C1,
+                        const int* __restrict__ sky_gate) {
   if (sky_gate != nullptr && *sky_gate == 0) return;
   __shared__ double2 T[16][17];
-  __shared__ double D[2][16];   // D of the block's rows and columns
   const int pair = blockIdx.x / (RB * RB), sub = blockIdx.x % (RB * RB), z = blockIdx.y;
   double2* C = z ? C1 : C0;
-  const double* dg = z ? diag1 : diag0;
   int ta, tb;
   tri_pair(pair, ta, tb);
   const int br = (sub / RB) * 16, bc = (sub % RB) * 16;
@@ -601,17 +594,6 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
   const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
   const int row = row0 + r, col = col0 + c;
   const float2* p = part + (size_t(z) * npair + pair) * split * BT * BT + (br + r) * BT + bc + c;
-  // P_aa of the block's rows and columns: eight threads each, their loads in
-  // flight with the element's own
-  const bool gram = z == 0 && dg != nullptr;
-  const int side = threadIdx.x >> 7, e = (threadIdx.x >> 3) & 15;
-  const int t = side ? tb : ta, i = (side ? bc : br) + e, a = t * BT + i;
-  double paa = 0.0;
-  if (gram && a < m) {
-    const float2* q = part + size_t(t * (t + 1) / 2 + t) * split * BT * BT + i * (BT + 1);
-#pragma unroll 4
-    for (int s = threadIdx.x & 7; s < split; s += 8) paa += double(q[size_t(s) * BT * BT].x);
-  }
   double re = 0.0, im = 0.0;
   if (row < m && col <= row) {
     int s = 0;
@@ -630,21 +612,11 @@ k_overlap_reduce_planes(const float2* __restrict__ part, int npair, int split, i
       re += double(v.x);
       im += double(v.y);
     }
-  }
-  if (gram) {
-    for (int w = 4; w > 0; w >>= 1) paa += __shfl_xor(paa, w);
-    paa *= sc;
-    if ((threadIdx.x & 7) == 0)
-      D[side][e] = a < m && paa > 0.0 && dg[a] > 0.0 ? sqrt(dg[a] / paa) : 1.0;
-    __syncthreads();
-  }
-  if (row < m && col <= row) {
     double2 v = make_double2(sc * re, sc * im);
     if (col == row) {
-      v = make_double2(dg != nullptr && !(gram && v.x == 0.0) ? dg[row] : v.x, 0.0);
-    } else if (gram) {
-      const double d = D[0][r] * D[1][c];
-      v = make_double2(d * v.x, d * v.y);
+      const double* dg = z ? diag1 : diag0;
+      if (z == 0 && gap0 != nullptr) gap0[row] = dg[row] - v.x;
+      v = make_double2(dg != nullptr ? dg[row] : v.x, 0.0);
     }
     C[size_t(row) * m + col] = v;
     T[r][c] = v;
@@ -823,7 +795,7 @@ void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
                           const unsigned int* mxA, const unsigned int* mxB0,
                           const unsigned int* mxB1, int m, long k, double scale, void* C0,
                           void* C1, void* part, hipStream_t st, hipEvent_t* ev, int split_req,
-                          int waves, const double* diag0, const double* diag1) {
+                          int waves, const double* diag0, const double* diag1, double* gap0) {
   if (m <= 0) return;
   const int nt = (m + BT - 1) / BT;
   const int npair = nt * (nt + 1) / 2;
@@ -845,7 +817,7 @@ void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
   if (ev) hipEventRecord(ev[1], st);
   hipLaunchKernelGGL(k_overlap_reduce_planes, dim3(unsigned(npair * RB * RB), nz), dim3(256), 0, st,
                      (const float2*)part, npair, split, m, scale, mxA, mxB0, PB1 ? mxB1 : mxB0,
-                     diag0, diag1, (double2*)C0, (double2*)C1, g_launch_gate);
+                     diag0, diag1, diag0 ? gap0 : nullptr, (double2*)C0, (double2*)C1, g_launch_gate);
 }
 
 void combine_planes(const void* PU, const void* PX, const unsigned int* mxU,

@@ -569,6 +569,45 @@ __global__ void k_inv_sqrt(double* __restrict__ w, int m, int* info, double floo
   w[i] = 1.0 / sqrt(v);
 }
 
+// The pivot k of A - diag(gap) is the least v^H (A - diag(gap)) v over v with v_k = 1
+// and nothing past k; A's own v, row k of L^-1 over its last element, gives it to
+// first order (the next term is gap^2 over the leading block's least eigenvalue).
+// One wave per row; one read of L^-1, a launch's latency beside the factorisation.
+__global__ void __launch_bounds__(256)
+k_gap_pivots(const double2* __restrict__ Linv, const double* __restrict__ gap, int m, int* info,
+             double floor_v, const int* __restrict__ sky_gate) {
+  if (sky_gate != nullptr && *sky_gate == 0) return;
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (k >= m) return;
+  const double2* u = Linv + size_t(k) * m;
+  double s = 0.0;
+  for (int i = lane; i <= k; i += 64) s += (u[i].x * u[i].x + u[i].y * u[i].y) * gap[i];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0 && !((1.0 - s) / (u[k].x * u[k].x) > floor_v)) atomicExch(info, 1);
+}
+
+// The eigenvalue k of A - diag(gap) to first order, w_k - sum_i gap_i |X_ik|^2.
+// 64 columns per workgroup, every fourth row per wave: one read of X after a Jacobi solve.
+__global__ void __launch_bounds__(256)
+k_gap_eigenvalues(const double2* __restrict__ X, const double* __restrict__ w,
+                  const double* __restrict__ gap, int m, int* info, double floor_v,
+                  const int* __restrict__ sky_gate) {
+  if (sky_gate != nullptr && *sky_gate == 0) return;
+  __shared__ double part[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = blockIdx.x * 64 + lane;
+  double s = 0.0;
+  if (k < m)
+    for (int i = wave; i < m; i += 4) {
+      const double2 x = X[size_t(i) * m + k];
+      s += (x.x * x.x + x.y * x.y) * gap[i];
+    }
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || k >= m) return;
+  s = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+  if (!(w[k] - s > floor_v)) atomicExch(info, 1);
+}
+
 int jacobi_dims(int m, int& nb) {
   nb = (m + JB - 1) / JB;
   if (nb < 2) nb = 2;
@@ -1038,6 +1077,19 @@ void scale_columns(void* X, const double* d, int m, hipStream_t st) {
   const size_t mm = size_t(m) * m;
   hipLaunchKernelGGL(k_scale_columns, dim3(unsigned((mm + 255) / 256)), dim3(256), 0, st,
                      (double2*)X, d, m, g_launch_gate);
+}
+
+void gap_pivots(const void* Linv, const double* gap, int m, int* info, hipStream_t st, double floor_v) {
+  if (m <= 0) return;
+  hipLaunchKernelGGL(k_gap_pivots, dim3((m + 3) / 4), dim3(256), 0, st, (const double2*)Linv, gap, m, info,
+                     floor_v, g_launch_gate);
+}
+
+void gap_eigenvalues(const void* X, const double* w, const double* gap, int m, int* info, hipStream_t st,
+                     double floor_v) {
+  if (m <= 0) return;
+  hipLaunchKernelGGL(k_gap_eigenvalues, dim3((m + 63) / 64), dim3(256), 0, st, (const double2*)X, w, gap, m,
+                     info, floor_v, g_launch_gate);
 }
 
 void inv_sqrt(double* w, int m, int* info, hipStream_t st, double floor_v) {

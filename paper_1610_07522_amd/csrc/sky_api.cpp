@@ -93,7 +93,8 @@ struct Layout {
       pc_gain, pc_dscr, pc_gram, pc_idx, pc_beps, pc_b[4], pc_gpart;
   int pc_nb;   // largest sampled-state batch (states x shells)
   size_t plA, plB, plT, plU, plS;                  // FP16 split planes, scales (mixed only)
-  size_t sdiag;   // FP64 diagonals of I and H (mixed only, 2 x the most states of a set)
+  // mixed only, of the most states of a set: FP64 diagonals of I and H, I's gap to the planes' own
+  size_t sdiag;
   size_t dens[2], der[2], mf[2], mf32[2], vc, fscratch, dens_part, epart, energy, info;
   size_t gflags, gdbl;   // flags and doubles of the device-decided iteration
   size_t total;
@@ -168,7 +169,7 @@ Layout plan(const sky_box_desc& d) {
   L.plB = take(mixed ? planes_bytes_nt(nmax, long(V)) : 0);
   L.plT = take(mixed ? planes_bytes_t(nmax, long(V)) : 0);
   L.plU = take(mixed ? planes_bytes_t(nmax, nmax) : 0);
-  L.sdiag = take(mixed ? sizeof(double) * 2 * nmax : 0);
+  L.sdiag = take(mixed ? sizeof(double) * 3 * nmax : 0);
   L.plS = take(sizeof(unsigned int) * 4);   // largest |component| of phi, h phi, U
   L.chol_work = take(size_t((nmax + 63) / 64 + 1) * 64 * 64 * c16);
   L.jac_work = take(jacobi_scratch_bytes(nmax));
@@ -345,6 +346,7 @@ struct sky_ctx {
   // diagonals of I and H of the set in flight (mixed)
   double* diagI() const { return at<double>(lay.sdiag); }
   double* diagH() const { return at<double>(lay.sdiag) + std::max(nq[0], nq[1]); }
+  double* gapI() const { return at<double>(lay.sdiag) + 2 * std::max(nq[0], nq[1]); }
   // mean field of the species of set s (shared by every twist)
   MeanFieldPtrs mfp(int s) const {
     const double* m = at<double>(lay.mf[s & 1]);
@@ -454,7 +456,7 @@ void subspace_matrices(sky_ctx* c, int s, const void* phi, const void* hphi,
     overlap_lower_planes(c->at(c->lay.plA), c->at(c->lay.plA), c->at(c->lay.plB), mx, mx, mx + 1,
                          m, c->V, c->g.dV, I, H, c->at(c->lay.gemm_part), st,
                          c->timing ? ev : nullptr, c->tune.ovl[q], waves_of(c->tune.ovw[q]),
-                         c->diagI(), c->diagH());
+                         c->diagI(), c->diagH(), c->gapI());
   else
     overlap_lower(phi, phi, hphi, m, c->V, c->g.dV, I, H, c->at(c->lay.gemm_part), st,
                   c->timing ? ev : nullptr, c->tune.ovl[q]);
@@ -542,6 +544,7 @@ int subspace_solve(sky_ctx* c, int s, double* ritz) {
     hipMemsetAsync(info, 0, sizeof(int), st);
     hipMemcpyAsync(Cw, I, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
     cholesky_inverse(Cw, Linv, m, c->at(c->lay.chol_work), info, st, CHOL_PIVOT_MIN);
+    if (c->prec) gap_pivots(Linv, c->gapI(), m, info, st, CHOL_PIVOT_MIN);
     gemm_square(Linv, 0, H, 0, T, m, st);
     gemm_square(T, 0, Linv, 1, Hp, m, st, 1);
   }
@@ -681,6 +684,7 @@ int paper_solve(sky_ctx* c, int s, double* ritz) {
     int rc = jacobi_checked(c, Cw, m, wi, X);
     if (rc < 0) return rc;
     hipMemcpyAsync(T, X, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
+    if (c->prec) gap_eigenvalues(X, wi, c->gapI(), m, info, st, CHOL_PIVOT_MIN);
     inv_sqrt(wi, m, info, st, CHOL_PIVOT_MIN);
     scale_columns(T, wi, m, st);
     gemm_square(T, 0, X, 1, C, m, st, 1);
@@ -836,7 +840,7 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
     split_planes_both(phi, m, c->V, mx, c->at(c->lay.plA), c->at(c->lay.plT), st);
     overlap_lower_planes(c->at(c->lay.plA), c->at(c->lay.plA), nullptr, mx, mx, nullptr, m,
                          c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st, nullptr,
-                         c->tune.ovl[q], 8, c->diagI());
+                         c->tune.ovl[q], 8, c->diagI(), nullptr, c->gapI());
   } else
     overlap_lower(phi, phi, nullptr, m, c->V, c->g.dV, I, nullptr, c->at(c->lay.gemm_part), st,
                   nullptr, c->tune.ovl[q]);
@@ -856,6 +860,7 @@ int loewdin(sky_ctx* c, int s, const void* phi, void* psi_out, bool eigen) {
   double* wi = c->at<double>(c->lay.wtmp);
   hipMemcpyAsync(c->at(c->lay.matT), X, size_t(m) * m * 16, hipMemcpyDeviceToDevice, st);
   hipMemcpyAsync(wi, w, sizeof(double) * m, hipMemcpyDeviceToDevice, st);
+  if (c->prec) gap_eigenvalues(X, w, c->gapI(), m, info, st, CHOL_PIVOT_MIN);
   inv_sqrt(wi, m, info, st, CHOL_PIVOT_MIN);
   scale_columns(c->at(c->lay.matT), wi, m, st);
   gemm_square(c->at(c->lay.matT), 0, X, 1, C, m, st, 1);

@@ -217,15 +217,15 @@ void split_planes_both(const void* x, int rows, long k, const unsigned int* mx, 
 // triangle, mirrored to the upper one.
 // split_req > 0 overrides the split-K factor (one of overlap_split_candidates_mixed).
 // diag0, diag1 (optional): the diagonals of C0 and C1, formed from the complex64
-// operands in FP64, in place of the planes' ones; with diag0 (A and B0 the same
-// matrix) C0's rows and columns are scaled to it, so that it stays a Gram matrix.
+// operands in FP64, in place of the planes' ones; gap0 (optional): diag0 less the
+// planes' diagonal of C0.
 int overlap_split_candidates_mixed(int m, long k, int* out);
 void overlap_lower_planes(const void* PA, const void* PB0, const void* PB1,
                           const unsigned int* mxA, const unsigned int* mxB0,
                           const unsigned int* mxB1, int m, long k, double scale, void* C0,
                           void* C1, void* part, hipStream_t st, hipEvent_t* ev = nullptr,
                           int split_req = 0, int waves = 8, const double* diag0 = nullptr,
-                          const double* diag1 = nullptr);
+                          const double* diag1 = nullptr, double* gap0 = nullptr);
 // Y[b][v] = sum_a U[a][b] X[a][v] from the transposed planes of U (m x m)
 // and of X (m x k).  waves, for both plane products: 8 (32 x 64 per wave)
 // or 4 (64 x 64 per wave) per 128 x 128 output tile; both load their tiles
@@ -358,6 +358,12 @@ void eig_sort(const void* D, const void* V, int m, int ld, double* w, void* Z, h
 void scale_columns(void* X, const double* d, int m, hipStream_t st);
 // w <- w^-1/2 elementwise (Loewdin), flags info if any w <= floor_v.
 void inv_sqrt(double* w, int m, int* info, hipStream_t st, double floor_v = 0.0);
+// info = 1 where A - diag(gap) has, to first order in gap, a Cholesky pivot
+// (gap_pivots, from Linv = L^-1 with A = L L^H) or an eigenvalue (gap_eigenvalues,
+// from A's w and X) not above floor_v.
+void gap_pivots(const void* Linv, const double* gap, int m, int* info, hipStream_t st, double floor_v);
+void gap_eigenvalues(const void* X, const double* w, const double* gap, int m, int* info, hipStream_t st,
+                     double floor_v);
 // fill n doubles (floats) with zero (a kernel, so it can be captured in graphs)
 void zero(double* p, size_t n, hipStream_t st);
 void zero_f32(float* p, size_t n, hipStream_t st);

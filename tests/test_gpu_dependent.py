@@ -1,6 +1,6 @@
 """Linearly dependent states are refused in both precisions, by every path that
-orthonormalises: a state taken twice, one of zeros, one whose norm is below the
-bound of 1e-10; independent ones are taken."""
+orthonormalises: a state taken twice, a combination of the others, one of zeros,
+one whose norm is below the bound of 1e-10; independent ones are taken."""
 import numpy as np
 import pytest
 import torch
@@ -19,6 +19,8 @@ def _states(m, kind, a, b):
     x /= np.sqrt((abs(x) ** 2).sum(axis=(1, 2, 3, 4), keepdims=True))
     if kind == "twice":
         x[b] = x[a]
+    elif kind == "combination":
+        x[b] = np.delete(x, b, axis=0).sum(axis=0) / np.sqrt(m - 1)
     elif kind == "faint":
         x[b] *= 2.0 ** -40
     elif kind == "zero":
@@ -58,6 +60,8 @@ def _orthonormalise(precision, x, how):
 @pytest.mark.parametrize("precision", sorted(DTYPES))
 def test_dependent_states_are_refused(precision, how, m):
     cases = [("twice", 0, 1), ("twice", 0, m - 1), ("faint", 0, m - 1), ("zero", 0, m // 2)]
+    if how in ("loewdin", "ritz"):   # the damped step is another one for each state
+        cases.append(("combination", 0, m // 2))
     for kind, a, b in cases:
         with pytest.raises(sky.SkyError) as e:
             _orthonormalise(precision, _states(m, kind, a, b), how)
